@@ -25,9 +25,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "gbla_device.h"
 #include "gbla_ext.h"
 #include "gbla_plan.h"
+#include "gbla_rows.h"
 
 namespace gbla {
 namespace {
@@ -41,15 +44,6 @@ __device__ __forceinline__ float act<uint16_t>(const uint16_t* p, int64_t i) {
   return __uint_as_float((uint32_t)p[i] << 16);
 }
 
-// Orders a wave's LDS stores before its later LDS loads of other lanes'
-// slots (one wave's LDS operations complete in order; this keeps the
-// compiler from moving them).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ float phi_f(float u) { return u > 0.0f ? u + 1.0f : expf(u); }
 
 // Gate logit i, or 0 without gate logits (the no-key-gating switch: uniform
@@ -58,11 +52,21 @@ template <typename T>
 __device__ __forceinline__ float logit(const T* a, int64_t i) { return a ? act<T>(a, i) : 0.0f; }
 // Hardware-exp forms for the matrix-core kernels (a few ulp; the gradients
 // are held to fp32-sum accuracy, far above that).
-__device__ __forceinline__ float phi_fast(float u) { return u > 0.0f ? u + 1.0f : __expf(u); }
+__device__ __forceinline__ float phi_fast(float u) {
+  const float e = __expf(u);  // formed for every u, so that no branch is
+  return u > 0.0f ? u + 1.0f : e;
+}
 __device__ __forceinline__ float sigmoid_fast(float x) {
   return __builtin_amdgcn_rcpf(1.0f + __expf(-x));
 }
+// x^(-1/2): the hardware's (1 ulp) with one Newton step.
+__device__ __forceinline__ float rsqrt_nr(float x) {
+  const float r = __builtin_amdgcn_rsqf(x);
+  return fmaf(0.5f * r, fmaf(-x * r, r, 1.0f), r);
+}
 __device__ __forceinline__ float dphi_f(float u) { return u > 0.0f ? 1.0f : expf(u); }
+
+constexpr int kBwdUnit = 512;  // tokens of the channel-layout kernels' units, at most
 
 template <int D>
 struct BW {
@@ -565,15 +569,16 @@ bwd_conv_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ kin,
 // are added in wave order.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(kThreads)
-bwd_param_kernel(Plan P, const int32_t* __restrict__ cu, const float* __restrict__ dgp,
-                 const float* __restrict__ dcp, float* __restrict__ dgamma,
-                 float* __restrict__ dconv) {
+__device__ __forceinline__ void bwd_params(const Plan& P, const int32_t* __restrict__ cu,
+                                           const float* __restrict__ dgp,
+                                           const float* __restrict__ dcp,
+                                           float* __restrict__ dgamma, float* __restrict__ dconv,
+                                           int h, int slice) {
   __shared__ float red[4][64];
-  const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int total = P.ragged ? units_before(cu, P.nseq, P.chunk) : P.chunks_per_seq * P.nseq;
   const int nout = D + (dconv ? 3 * D * P.W : 0);
-  const int e = blockIdx.y * 64 + lane;
+  const int e = slice * 64 + lane;
   const bool live = e < nout;
   size_t off = 0, stride = 0;
   if (e < D) {
@@ -611,927 +616,612 @@ bwd_param_kernel(Plan P, const int32_t* __restrict__ cu, const float* __restrict
     }
   }
 }
+template <int D>
+__global__ void __launch_bounds__(kThreads)
+bwd_param_kernel(Plan P, const int32_t* __restrict__ cu, const float* __restrict__ dgp,
+                 const float* __restrict__ dcp, float* __restrict__ dgamma,
+                 float* __restrict__ dconv) {
+  bwd_params<D>(P, cu, dgp, dcp, dgamma, dconv, blockIdx.x, blockIdx.y);
+}
 
 // ===========================================================================
-// Matrix-core path (every head dim; at d = 128 one workgroup per CU).
+// Channel-layout path (gbla_rows.h): every head dim, slices below 2^31 bytes.
 //
 // Every contraction runs on v_mfma_f32_16x16x4_f32: fp32 operands, exact
 // products, fp32 accumulation, so the results carry fp32 rounding only (the
 // gradients cancel strongly -- dQh = S dnum + z dden, t = dS vt + dz -- and
-// a bf16 split of the operands would show through that cancellation).
+// a two-way bf16 split of the operands would show through that cancellation).
 //
-// Lane layout.  A wave works on 16 tokens at a time; lane (n, g) = (lane &
-// 15, lane >> 4) holds token n and the channel set
-//     Sigma(g) = { 16 kq + 4 g + i : kq < d/16, i < 4 },
-// which is the row set that a 16x16 MFMA output hands lane (n, g) when the M
-// index is the channel.  The K index of every channel contraction is ordered
-// the same way (K step 4 kq + i gives lane group g channel 16 kq + 4 g + i),
-// so a lane's Sigma(g) values are directly its B operands and the outputs
-// land where the next step needs them.  The constant A operands (S^T, S,
-// dS, dS^T) are laid out once per workgroup in LDS in that K order, four K
-// steps per 16-byte lane vector.
+// The conv's transpose is fused into the two passes.  A wave walks its
+// contiguous quarter of the unit from its last tile to its first, so the three
+// later tokens that a tile's dx needs are at hand: the next lane group's rows,
+// or, for the last group, the first rows of the tile done before (LDS).  At
+// the wave's own end those rows belong to another wave or unit: its last three
+// tokens' dx are stored without them, every wave leaves the gradients of its
+// first three convolved tokens in an edge buffer, and bwd_finish_kernel adds
+// the missing products.  A separate conv pass over dqt, dkt, dvt in memory
+// cost 1,920 bytes a token and head at d = 64, 92 of 321 us at n = 32768.
 //
-// Token sums (S_p and dS) contract over tokens: a wave stages its 16 tokens'
-// fp32 rows in its own LDS area and reads them back as K steps of four
-// tokens, accumulating its own d x d partial; the four waves' partials are
-// added in wave order at the end.  Waves never wait for each other inside
-// the token loop, and each one loads its next 16-token block before working
-// on the current one.
+// Measured (query + key + conv of the kernels that these replaced, against
+// query + dsum + key): n = 32768, H = 8, d = 64 bf16 280 -> 165 us; 57,511
+// packed tokens, H = 8, d = 128 bf16 1810 -> 1250 us.
 // ===========================================================================
-template <int D>
-struct MF {
-  static constexpr int NMB = D / 16;          // 16-channel blocks
-  // staging row stride (floats): the four lane groups' rows start 16 banks apart
-  static constexpr int kRow = D + 16;
-  static constexpr int kStage = 16 * kRow;    // one wave's 16-token array
-  static constexpr int kBlocks = NMB * NMB;   // 16x16 blocks of a d x d result
-  static constexpr int kStep = 64;            // tokens between a wave's blocks
-};
 
-__device__ __forceinline__ f32x4_t mfma4(float a, float b, f32x4_t acc) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
-}
-
-// acc[mb] += A_mb v over the d channels: A fragments f32x4 at
-// frag[(mb * NMB + kq) * 64 + lane] (K steps 4 kq .. 4 kq + 3), B = the
-// lane's Sigma values v[kq][i].
-template <int D, int NM>
-__device__ __forceinline__ void contract(const f32x4_t* __restrict__ frag, int lane,
-                                         const float (*v)[4], f32x4_t* acc) {
-  constexpr int NMB = D / 16;
+// Rows of the tile's dx: dx_m = sum_t w_t dxt_{m+3-t}, and the tap sums
+// dw_t += dxt_i x_{i-3+t}.  d: dxt of the tile (channel layout), x: its
+// windows; stage: the wave's LDS area; later: [3][D] floats
+// of LDS, dxt of the three tokens after the tile on entry, of its first three
+// tokens on return.  dx of token tile + 4 g + i is stored at out row off + i.
+template <typename T, int D, typename Taps>
+__device__ __forceinline__ void conv_back(const float (*d)[4], const Window<T, D>& x,
+                                          const Taps& taps, float* stage, float* later,
+                                          __amdgpu_buffer_rsrc_t out, uint32_t off, int lane,
+                                          float (*dw)[4]) {
+  using C = CL<D>;
+  const int n = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int kq = 0; kq < NMB; ++kq)
+  for (int k = 0; k < C::NV; ++k) {
+    wave_lds_sync();
 #pragma unroll
-    for (int mb = 0; mb < NM; ++mb) {
-      const f32x4_t a = frag[(mb * NMB + kq) * 64 + lane];
+    for (int i = 0; i < 3; ++i) put_vec<D>(stage + (4 * g + i) * C::kPitch + C::V * n, d, k, i);
+    wave_lds_sync();
+    const float* src = g < 3 ? stage + 4 * (g + 1) * C::kPitch : later + k * 16 * C::V;
+    const int pitch = g < 3 ? C::kPitch : D;
+    float nx[3][C::V];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[mb] = mfma4(a[i], v[kq][i], acc[mb]);
+    for (int i = 0; i < 3; ++i) get_vec<D>(src + i * pitch + C::V * n, nx[i]);
+    wave_lds_sync();
+    if (g == 0) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) put_vec<D>(later + i * D + k * 16 * C::V + C::V * n, d, k, i);
     }
-}
-
-// Sum over the four lane groups (the lanes n, n+16, n+32, n+48 of one token).
-__device__ __forceinline__ float sum_groups(float x) {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
-}
-
-// Sum over the 16 lanes of a lane group (fixed tree), result in every lane.
-__device__ __forceinline__ float sum_tokens(float x) {
-  x += __shfl_xor(x, 8);
-  x += __shfl_xor(x, 4);
-  x += __shfl_xor(x, 2);
-  return x + __shfl_xor(x, 1);
-}
-
-// A-operand fragments of the d x d matrix X in the K order above:
-// X[row][k] = src[k * D + row] (kTrans) or src[row * D + k].  Every thread of
-// the block takes part.
-template <int D, bool kTrans>
-__device__ __forceinline__ void build_frags(const float* __restrict__ src, f32x4_t* frag) {
-  constexpr int NMB = D / 16;
-  for (int idx = threadIdx.x; idx < NMB * NMB * 64; idx += kThreads) {
-    const int f = idx >> 6, l = idx & 63;
-    const int mb = f / NMB, kq = f % NMB;
-    const int row = 16 * mb + (l & 15), k0 = 16 * kq + 4 * (l >> 4);
-    f32x4_t v;
+    float y[C::V][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      v[i] = kTrans ? src[(size_t)(k0 + i) * D + row] : src[(size_t)row * D + k0 + i];
-    frag[idx] = v;
-  }
-}
-
-// The fragments of build_frags<D, false> for S' = S - z m^T: X[row][k] =
-// src[row * D + k] - zv[row] mv[k] (zv, mv in LDS).
-template <int D>
-__device__ __forceinline__ void build_frags_centred(const float* __restrict__ src, const float* zv,
-                                                    const float* mv, f32x4_t* frag) {
-  constexpr int NMB = D / 16;
-  for (int idx = threadIdx.x; idx < NMB * NMB * 64; idx += kThreads) {
-    const int f = idx >> 6, l = idx & 63;
-    const int mb = f / NMB, kq = f % NMB;
-    const int row = 16 * mb + (l & 15), k0 = 16 * kq + 4 * (l >> 4);
-    f32x4_t v;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = fmaf(-zv[row], mv[k0 + i], src[(size_t)row * D + k0 + i]);
-    frag[idx] = v;
-  }
-}
-
-// Loads four consecutive channels of one row (element offset `off` of a
-// buffer resource; out of range reads 0) as fp32.
-template <typename T>
-__device__ __forceinline__ f32x4_t load4(__amdgpu_buffer_rsrc_t r, uint32_t off);
-template <>
-__device__ __forceinline__ f32x4_t load4<float>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, off * 4u, 0, 0));
-}
-template <>
-__device__ __forceinline__ f32x4_t load4<uint16_t>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  const u32x2_t w = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, off * 2u, 0, 0));
-  return (f32x4_t){bf16_lo(w[0]), bf16_hi(w[0]), bf16_lo(w[1]), bf16_hi(w[1])};
-}
-template <typename T>
-__device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, uint32_t off);
-template <>
-__device__ __forceinline__ float load1<float>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off * 4u, 0, 0));
-}
-template <>
-__device__ __forceinline__ float load1<uint16_t>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return bf16_lo((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, off * 2u, 0, 0));
-}
-__device__ __forceinline__ void store4(__amdgpu_buffer_rsrc_t r, uint32_t off, const float* v) {
-  const f32x4_t x = {v[0], v[1], v[2], v[3]};
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, x), r, off * 4u, 0, 0);
-}
-
-// Slice-relative element offset of channel c of token `tok` (tok may be
-// negative: the unsigned offset is then past any range and reads 0).
-template <int D>
-__device__ __forceinline__ uint32_t eoff(int tok, int c) {
-  return (uint32_t)(tok * D + c);
-}
-
-// Four consecutive channels as loaded (raw bf16 pairs or fp32), widened only
-// where they are used, so that loads issued a block ahead stay in flight.
-template <typename T>
-struct Raw;
-template <>
-struct Raw<uint16_t> {
-  using type = u32x2_t;
-  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, off * 2u, 0, 0));
-  }
-  static __device__ __forceinline__ f32x4_t widen(type w) {
-    return (f32x4_t){bf16_lo(w[0]), bf16_hi(w[0]), bf16_lo(w[1]), bf16_hi(w[1])};
-  }
-};
-template <>
-struct Raw<float> {
-  using type = u32x4_t;
-  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, off * 4u, 0, 0);
-  }
-  static __device__ __forceinline__ f32x4_t widen(type w) { return __builtin_bit_cast(f32x4_t, w); }
-};
-
-// Value of token n - K for lane n of a 16-lane row: lane n - K of `cur`, or
-// lane n - K + 16 of `prev` (the preceding 16 tokens) when n < K.  DPP
-// row_shr:K moves cur up by K lanes inside each row; the lanes it leaves
-// empty keep the row_ror:K rotation of prev.
-template <int K>
-__device__ __forceinline__ float shifted(float cur, float prev) {
-  const int old = __builtin_amdgcn_mov_dpp(__float_as_int(prev), 0x120 + K, 0xF, 0xF, false);
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(old, __float_as_int(cur), 0x110 + K, 0xF, 0xF, false));
-}
-
-// One input tensor streamed 16 tokens at a time along a wave's contiguous
-// token range: lane (n, g) loads only its own row (its Sigma(g) channels)
-// one block ahead; the conv window's three earlier tokens come from the
-// neighbouring lanes and, across the block edge, from the previous block.
-template <typename T, int D>
-struct RowStream {
-  static constexpr int NMB = D / 16;
-  typename Raw<T>::type nxt[NMB];  // raw row of the block to come (in flight)
-  float prev[NMB][4];              // rows of the previous block
-  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t r, int tok, int g) {
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) nxt[kq] = Raw<T>::load(r, eoff<D>(tok, 16 * kq + 4 * g));
-  }
-  // prev <- the 16 tokens before `tok` (row tok - 16 of the lane), then the
-  // first block's rows are issued.
-  __device__ __forceinline__ void start(__amdgpu_buffer_rsrc_t r, int tok, int g) {
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) {
-      const f32x4_t p = Raw<T>::widen(Raw<T>::load(r, eoff<D>(tok - 16, 16 * kq + 4 * g)));
-#pragma unroll
-      for (int i = 0; i < 4; ++i) prev[kq][i] = p[i];
-    }
-    issue(r, tok, g);
-  }
-  // Consumes the issued rows: out[kq][i] = sum_t taps[c][t] x_{tok - 3 + t}[c]
-  // (c = 16 kq + 4 g + i); they become prev.
-  __device__ __forceinline__ void conv(const f32x4_t* taps, int g, float (*out)[4]) {
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) {
-      const f32x4_t c = Raw<T>::widen(nxt[kq]);
+    for (int j = 0; j < C::V; ++j) {
+      const int b = k * C::V + j;
+      const f32x4_t w = taps(b);
+      const float dd[7] = {d[b][0], d[b][1], d[b][2], d[b][3], nx[0][j], nx[1][j], nx[2][j]};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const f32x4_t w = taps[16 * kq + 4 * g + i];
-        float acc = w[0] * shifted<3>(c[i], prev[kq][i]);
-        acc = fmaf(w[1], shifted<2>(c[i], prev[kq][i]), acc);
-        acc = fmaf(w[2], shifted<1>(c[i], prev[kq][i]), acc);
-        out[kq][i] = fmaf(w[3], c[i], acc);
-        prev[kq][i] = c[i];
+        float acc = w[3] * dd[i];
+        acc = fmaf(w[2], dd[i + 1], acc);
+        acc = fmaf(w[1], dd[i + 2], acc);
+        y[j][i] = fmaf(w[0], dd[i + 3], acc);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) dw[b][t] = fmaf(dd[i], x.x[i + t].at(b), dw[b][t]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t o = off + (uint32_t)(i * D * 4 + k * 16 * C::V * 4);
+      if constexpr (C::V == 4) {
+        const f32x4_t v = {y[0][i], y[1][i], y[2][i], y[3][i]};
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), out, o, 0, 0);
+      } else {
+        const f32x2_t v = {y[0][i], y[1][i]};
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), out, o, 0, 0);
       }
     }
   }
-};
-
-// Writes a lane's Sigma values as row n of a wave's fp32 staging array.
-template <int D>
-__device__ __forceinline__ void stage_sigma(float* arr, int n, int g, const float (*v)[4]) {
-#pragma unroll
-  for (int kq = 0; kq < D / 16; ++kq)
-    *reinterpret_cast<f32x4_t*>(arr + n * MF<D>::kRow + 16 * kq + 4 * g) =
-        (f32x4_t){v[kq][0], v[kq][1], v[kq][2], v[kq][3]};
 }
 
-// acc[mb * NMB + nb] += sum over the wave's 16 staged tokens of X[tok][c]
-// Y[tok][e] for c block mb, e block nb (K step kk is token 4 kk + g of lane
-// group g).
-// With zpart, also zpart[b] += X[tok][16 b + j] over the lane's tokens
-// (tokens g, g + 4, ... of lane (j, g)): the column sums of X.
+// Writes a unit's tap-gradient partial [D][4] from the lanes' sums (every
+// thread calls; red: 4 x D f32x4 of LDS).
 template <int D>
-__device__ __forceinline__ void token_product(const float* X, const float* Y, int lane,
-                                              f32x4_t* acc, float* zpart = nullptr) {
-  using C = MF<D>;
-  const int j = lane & 15, g = lane >> 4;
-  // at d = 128 (64 products per K step) the K steps are not unrolled, so that
-  // their reads are not all hoisted into registers at once
-#pragma unroll(D >= 128 ? 1 : 4)
-  for (int kk = 0; kk < 4; ++kk) {
-    const int row = (4 * kk + g) * C::kRow;
-    float xv[C::NMB], yv[C::NMB];
-#pragma unroll
-    for (int b = 0; b < C::NMB; ++b) {
-      xv[b] = X[row + 16 * b + j];
-      yv[b] = Y[row + 16 * b + j];
-    }
-#pragma unroll
-    for (int mb = 0; mb < C::NMB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < C::NMB; ++nb)
-        acc[mb * C::NMB + nb] = mfma4(xv[mb], yv[nb], acc[mb * C::NMB + nb]);
-    if (zpart) {
-#pragma unroll
-      for (int b = 0; b < C::NMB; ++b) zpart[b] += xv[b];
-    }
-  }
-}
-
-// Adds the four waves' d x d accumulators in wave order (through `buf`, d*d
-// floats of LDS) and writes the sum to dst[c * D + e].  Every thread calls.
-template <int D>
-__device__ __forceinline__ void wave_ordered_sum(const f32x4_t* acc, float* buf, float* dst) {
-  using C = MF<D>;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
-  for (int w = 0; w < 4; ++w) {
-    if (wave == w) {
-#pragma unroll
-      for (int mb = 0; mb < C::NMB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < C::NMB; ++nb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int x = (16 * mb + 4 * g + i) * D + 16 * nb + n;
-            const float v = acc[mb * C::NMB + nb][i];
-            buf[x] = w == 0 ? v : buf[x] + v;
-          }
-    }
-    __syncthreads();
-  }
-  for (int x = threadIdx.x; x < D * D; x += kThreads) dst[x] = buf[x];
-  __syncthreads();
-}
-
-// Copies the d x d matrix src (global) to buf (LDS) with 16-byte loads.
-template <int D>
-__device__ __forceinline__ void stage_matrix(const float* __restrict__ src, float* buf) {
-  for (int x = 4 * threadIdx.x; x < D * D; x += 4 * kThreads)
-    *reinterpret_cast<f32x4_t*>(buf + x) = *reinterpret_cast<const f32x4_t*>(src + x);
-}
-
-// Sums per-lane Sigma accumulators over the tokens (lanes) and the waves in
-// a fixed order and writes the d sums to dst (every thread must call).
-template <int D>
-__device__ __forceinline__ void reduce_sigma(const float (*v)[4], float (*red)[D], float* dst) {
+__device__ __forceinline__ void sum_taps(const float (*dw)[4], f32x4_t (*red)[D], float* __restrict__ dst) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int kq = 0; kq < D / 16; ++kq)
+  for (int b = 0; b < CL<D>::NMB; ++b) {
+    f32x4_t s;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float s = sum_tokens(v[kq][i]);
-      if (n == 0) red[wave][16 * kq + 4 * g + i] = s;
-    }
+    for (int t = 0; t < 4; ++t) s[t] = sum_groups(dw[b][t]);
+    if (g == 0) red[wave][slot_chan<D>(b, n)] = s;
+  }
   __syncthreads();
   if (threadIdx.x < D) {
-    float acc = 0.0f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) acc += red[w][threadIdx.x];
-    dst[threadIdx.x] = acc;
+    const int x = threadIdx.x;
+    *reinterpret_cast<f32x4_t*>(dst + 4 * x) = (red[0][x] + red[1][x]) + (red[2][x] + red[3][x]);
   }
   __syncthreads();
 }
 
-// ---------------------------------------------------------------------------
-// State, matrix-core version: the record [S_p | z_p | m_p | l_p] of a unit.
-// ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ void __launch_bounds__(kThreads, D >= 128 ? 1 : 2)
-bwd_state_mfma_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
-                      const T* __restrict__ ain, const float* __restrict__ conv_w,
-                      const int32_t* __restrict__ cu, float* __restrict__ partials) {
-  using C = MF<D>;
-  constexpr int NMB = C::NMB;
-  __shared__ __attribute__((aligned(16))) float stg[4][2][C::kStage];  // [wave][kt or vt]
-  __shared__ f32x4_t tk[D], tv[D];
-  __shared__ float red[4][D];
-  __shared__ float red4[4];
-  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int h = blockIdx.y, unit = blockIdx.x;
-  int s, chunk;
-  if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
-  int64_t len, base_row;
-  seq_geometry(P, cu, s, h, &len, &base_row);
-  const int t0 = chunk * P.chunk;
-  const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
-  if (tid < D) {
-    float w4[4];
-    load_taps4(conv_w, P.heads, h, 1, D, P.W, tid, w4);
-    tk[tid] = (f32x4_t){w4[0], w4[1], w4[2], w4[3]};
-    load_taps4(conv_w, P.heads, h, 2, D, P.W, tid, w4);
-    tv[tid] = (f32x4_t){w4[0], w4[1], w4[2], w4[3]};
-  }
-  float ml = -INFINITY;
-  for (int j = t0 + tid; j < t1; j += kThreads) ml = fmaxf(ml, logit<T>(ain, base_row + j));
-  const float m = block_max(ml, red4);  // its barriers also publish tk, tv
-
-  const uint32_t rows = (uint32_t)len * D;
-  const __amdgpu_buffer_rsrc_t rk = make_rsrc(kin + base_row * D, rows * sizeof(T));
-  const __amdgpu_buffer_rsrc_t rv = make_rsrc(vin + base_row * D, rows * sizeof(T));
-  // no gate logits: an empty range, so every logit reads as 0
-  const __amdgpu_buffer_rsrc_t ra =
-      ain ? make_rsrc(ain + base_row, (uint32_t)len * sizeof(T)) : make_rsrc(kin, 0u);
-  f32x4_t acc[C::kBlocks];
-#pragma unroll
-  for (int k = 0; k < C::kBlocks; ++k) acc[k] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-  // z: the column sums of the staged gated keys, per lane (channel 16 b + j,
-  // tokens g, g + 4, ...), summed over the lane groups and waves at the end
-  float zpart[NMB];
-#pragma unroll
-  for (int b = 0; b < NMB; ++b) zpart[b] = 0.0f;
-  float lacc = 0.0f;
-  float* X = stg[wave][0];
-  float* Y = stg[wave][1];
-
-  // the wave's contiguous quarter of the unit, 16 tokens at a time
-  const int q4 = P.chunk / 4, w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
-  RowStream<T, D> sk, sv;
-  int tok = w0 + n;
-  sk.start(rk, tok, g);
-  sv.start(rv, tok, g);
-  float al = load1<T>(ra, (uint32_t)tok);
-  for (int b0 = w0; b0 < w1; b0 += 16) {
-    float kt[NMB][4], vt[NMB][4];
-    __asm__ volatile("" ::: "memory");  // taps are re-read from LDS, not held
-    sk.conv(tk, g, kt);
-    sv.conv(tv, g, vt);
-    const float w = tok < t1 ? __expf(al - m) : 0.0f;
-    // the next block's rows (out of range past the slice: read as 0, unused)
-    tok += 16;
-    sk.issue(rk, tok, g);
-    sv.issue(rv, tok, g);
-    al = load1<T>(ra, (uint32_t)tok);
-    if (g == 0) lacc += w;
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) kt[kq][i] = w * phi_fast(kt[kq][i]);
-    wave_lds_sync();  // the previous block's reads of X, Y are done
-    stage_sigma<D>(X, n, g, kt);
-    stage_sigma<D>(Y, n, g, vt);
-    wave_lds_sync();
-    token_product<D>(X, Y, lane, acc, zpart);
-  }
-
-  float* rec = partials + ((size_t)h * P.units + unit) * P.rec_floats;
-  __syncthreads();  // every wave is done with its staging area
-  wave_ordered_sum<D>(acc, &stg[0][0][0], rec);
-#pragma unroll
-  for (int b = 0; b < NMB; ++b) {
-    const float zs = sum_groups(zpart[b]);
-    if (g == 0) red[wave][16 * b + n] = zs;
-  }
-  __syncthreads();
-  if (tid < D) rec[D * D + tid] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
-  const float lsum = sum_tokens(lacc);  // lanes of group 0 hold the weights
-  if (lane == 0) red4[wave] = lsum;
-  __syncthreads();
-  if (tid == 0) {
-    rec[D * D + D] = m;
-    rec[D * D + D + 1] = (red4[0] + red4[1]) + (red4[2] + red4[3]);
-  }
+// Edge rows of the wave of a unit: dxt of the wave's first three tokens.
+template <int D>
+__device__ __forceinline__ size_t edge_off(const Plan& P, int tensor, int h, int unit, int wave) {
+  return ((((size_t)tensor * P.heads + h) * P.units + unit) * 4 + wave) * (3 * D);
+}
+template <int D>
+__device__ __forceinline__ void store_edge(const float* later, float* __restrict__ dst, int lane) {
+  for (int x = lane; x < 3 * D; x += 64) dst[x] = later[x];
 }
 
 // ---------------------------------------------------------------------------
-// Query pass, matrix-core version.
+// Query pass: grid (units, H).
 // ---------------------------------------------------------------------------
-// kDS: the unit's dS partial is summed here (d <= 64).  At d = 128 the
-// token-sum accumulators and the two d x d operand layouts do not fit one
-// CU together, so this kernel writes dnum (to dnum_out, the layout of dy)
-// and bwd_dsum_mfma_kernel forms dS from it.
+// kDS: the unit's dS partial is summed here (d <= 64).  At d = 128 its 256
+// accumulators leave too few registers for the rest (the compiler then moved
+// and spilled some 900 of them a tile: 1207 us against 677 for this and
+// bwd_dsum_rows_kernel together, 16 sequences of 57,511 tokens, H = 8), so this
+// kernel writes dnum (to dnum_out, in the layout of dy) for that one.
 template <typename T, int D, bool kNorm, bool kDS>
 __global__ void __launch_bounds__(kThreads, D >= 128 ? 1 : 2)
-bwd_query_mfma_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ rin,
+bwd_query_rows_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ rin,
                       const float* __restrict__ dy, const float* __restrict__ conv_w,
                       const float* __restrict__ gamma, const int32_t* __restrict__ cu,
                       const float* __restrict__ Sg, const float* __restrict__ zg,
-                      float* __restrict__ dqt, float* __restrict__ dr, float* __restrict__ dsp,
-                      float* __restrict__ dgp, float* __restrict__ dnum_out) {
-  using C = MF<D>;
+                      float* __restrict__ dq, float* __restrict__ dr, float* __restrict__ dsp,
+                      float* __restrict__ dgp, float* __restrict__ dcp, float* __restrict__ edge,
+                      float* __restrict__ dnum_out) {
+  using C = CL<D>;
   constexpr int NMB = C::NMB;
-  __shared__ f32x4_t a1[NMB * NMB * 64];  // num: A[e][c] = S[c][e]
-  __shared__ f32x4_t a2[NMB * NMB * 64];  // dQh: A[c][e] = S[c][e]
-  __shared__ __attribute__((aligned(16))) float stg[4][2][kDS ? C::kStage : 4];  // [wave][Qh or dnum]
+  __shared__ f32x4_t f1[C::kFrag];  // num: B[c][e] = S[c][e]; later the waves' sums
+  __shared__ f32x4_t f2[C::kFrag];  // dQh: B[e][c] = S'[c][e]
+  __shared__ __attribute__((aligned(16))) float stg[4][C::kStage];
+  __shared__ __attribute__((aligned(16))) float later[4][3 * D];
   __shared__ f32x4_t tq[D];
-  __shared__ __attribute__((aligned(16))) float zs[D], gs[D], ms[D];
-  __shared__ float red[4][D];
-  static_assert(!kDS || sizeof(stg) >= D * D * sizeof(float), "staging holds a d x d matrix");
+  __shared__ __attribute__((aligned(16))) float zs[D], gs[D], ms[D];  // by channel
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.y, unit = blockIdx.x;
   int s, chunk;
   if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
+  s = __builtin_amdgcn_readfirstlane(s);
+  chunk = __builtin_amdgcn_readfirstlane(chunk);
   int64_t len, base_row;
   seq_geometry(P, cu, s, h, &len, &base_row);
   const int t0 = chunk * P.chunk;
   const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
-  const size_t sh = (size_t)s * P.heads + h;
-  const float* z = zg + sh * D;
-  float* sbuf = &stg[0][0][0];
-  if constexpr (kDS) stage_matrix<D>(Sg + sh * D * D, sbuf);
-  if (tid < D) {
-    float w4[4];
-    load_taps4(conv_w, P.heads, h, 0, D, P.W, tid, w4);
-    tq[tid] = (f32x4_t){w4[0], w4[1], w4[2], w4[3]};
-    zs[tid] = z[tid];
-    gs[tid] = kNorm ? gamma[(size_t)h * D + tid] : 1.0f;
-  }
-  float dzacc[NMB][4], dgacc[NMB][4];
-#pragma unroll
-  for (int kq = 0; kq < NMB; ++kq)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      dzacc[kq][i] = 0.0f;
-      dgacc[kq][i] = 0.0f;
-    }
-  __syncthreads();
-  // dQh = S dnum + z dden is formed as S' dnum + z (dden + m . dnum) with
-  // S' = S - z m^T, m = (sum_c S[c][.]) / (sum_c z[c]) (the gate-weighted
-  // mean value row): the same quantity, but without the cancellation
-  // between the two terms when the value rows share a mean (then
-  // S dnum ~ z (m . dnum) and o ~ m, and the no-norm dden + m . dnum is
-  // formed as -((o - m) . dy) / den directly).
-  const float* Ssrc = kDS ? sbuf : Sg + sh * D * D;
-  if (tid < D) {
-    float cs = 0.0f, zsum = 0.0f;
-    for (int c = 0; c < D; ++c) {
-      cs += Ssrc[(size_t)c * D + tid];
-      zsum += zs[c];
-    }
-    ms[tid] = zsum > 0.0f ? cs / zsum : 0.0f;
-  }
-  __syncthreads();
-  // the operand layouts, from the staged S, or at d = 128 straight from memory
-  build_frags<D, true>(Ssrc, a1);
-  build_frags_centred<D>(Ssrc, zs, ms, a2);
-  f32x4_t acc3[kDS ? C::kBlocks : 1];
-#pragma unroll
-  for (int k = 0; k < (kDS ? C::kBlocks : 1); ++k) acc3[k] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-
   const uint32_t rows = (uint32_t)len * D;
   const __amdgpu_buffer_rsrc_t rq = make_rsrc(qin + base_row * D, rows * sizeof(T));
   // without the gated norm r is not read (an empty range) and dr not written
   const __amdgpu_buffer_rsrc_t rr =
       kNorm ? make_rsrc(rin + base_row * D, rows * sizeof(T)) : make_rsrc(qin, 0u);
   const __amdgpu_buffer_rsrc_t rdy = make_rsrc(dy + base_row * D, rows * 4u);
-  const __amdgpu_buffer_rsrc_t rdq = make_rsrc(dqt + base_row * D, rows * 4u);
+  const __amdgpu_buffer_rsrc_t rdq = make_rsrc(dq + base_row * D, rows * 4u);
   const __amdgpu_buffer_rsrc_t rdr =
-      kNorm ? make_rsrc(dr + base_row * D, rows * 4u) : make_rsrc(dqt, 0u);
+      kNorm ? make_rsrc(dr + base_row * D, rows * 4u) : make_rsrc(dq, 0u);
   const __amdgpu_buffer_rsrc_t rdn =
-      kDS ? make_rsrc(dqt, 0u) : make_rsrc(dnum_out + base_row * D, rows * 4u);
-  float* X = stg[wave][0];
-  float* Y = stg[wave][1];
-  __syncthreads();  // fragments built; the staging area is free again
+      kDS ? make_rsrc(dq, 0u) : make_rsrc(dnum_out + base_row * D, rows * 4u);
+  // the wave's quarter of the unit, in whole tiles
+  const int q4 = quarter_tokens(t1 - t0);
+  const int w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
+  int b0 = w0 + (w1 > w0 ? (w1 - w0 - 1) / 16 * 16 : 0);  // the wave's last tile
+  Window<T, D> nq;
+  nq.load(rq, b0 + 4 * g, n);
 
-  // the wave's contiguous quarter of the unit, 16 tokens at a time
-  const int q4 = P.chunk / 4, w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
-  RowStream<T, D> sq;
-  typename Raw<T>::type rraw[NMB];
-  u32x4_t dyraw[NMB];
-  int tok = w0 + n;
-  auto issue_rd = [&](int tk) {
+  const size_t sh = (size_t)s * P.heads + h;
+  const float* S = Sg + sh * D * D;
+  Frags<D> fa, fb;
+  fb.load_transposed(S);  // S[c][e .. e + 3]
+  fa.load(S);
+  stage_taps<D>(conv_w, P.heads, h, 0, P.W, tq);
+  if (tid < D) {
+    zs[tid] = zg[sh * D + tid];
+    gs[tid] = kNorm ? gamma[(size_t)h * D + tid] : 1.0f;
+  }
+  for (int x = lane; x < 3 * D; x += 64) later[wave][x] = 0.0f;
+  // dQh = S dnum + z dden is formed as S' dnum + z (dden + m . dnum) with
+  // S' = S - z m^T, m = (sum_c S[c][.]) / (sum_c z[c]) (the gate-weighted
+  // mean value row): the same quantity, but without the cancellation between
+  // the two terms when the value rows share a mean (then S dnum ~ z (m . dnum)
+  // and o ~ m, and the no-norm dden + m . dnum is formed as
+  // -((o - m) . dy) / den directly).
+  // Column sums of S from fb: a wave's vectors have the K blocks kq = wave +
+  // 4 j alone (d = 32: waves w and w + 2 share block w); sixteen lanes of a
+  // vector hold the block's columns c.
+  constexpr int kQ = NMB > 4 ? NMB / 4 : 1, kShare = NMB < 4 ? 4 / NMB : 1;
+  float* part = &stg[0][0];  // [kShare][D]
 #pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) {
-      rraw[kq] = Raw<T>::load(rr, eoff<D>(tk, 16 * kq + 4 * g));
-      dyraw[kq] = Raw<float>::load(rdy, eoff<D>(tk, 16 * kq + 4 * g));
+  for (int j = 0; j < kQ; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float cs = 0.0f;
+#pragma unroll
+      for (int u = j; u < Frags<D>::kPer; u += kQ) cs += fb.v[u][i];
+      cs = sum_row16(cs);
+      if (n == 0) part[(wave / NMB) * D + fb.k0(j) + i] = cs;
     }
-  };
-  sq.start(rq, tok, g);
-  issue_rd(tok);
-  for (int b0 = w0; b0 < w1; b0 += 16) {
-    float qh[NMB][4];
-    f32x4_t rv[NMB], dyv[NMB];
-    // the A fragments and taps are re-read from LDS each block rather than
-    // held in registers across the loop
+  __syncthreads();
+  if (tid < D) {
+    float cs = part[tid], zsum = 0.0f;
+    if constexpr (kShare == 2) cs += part[D + tid];
+    for (int c = 0; c < D; ++c) zsum += zs[c];
+    ms[tid] = zsum > 0.0f ? cs / zsum : 0.0f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < Frags<D>::kPer; ++u) {
+    const float z = zs[fb.col(u)];
+    const f32x4_t m = *reinterpret_cast<const f32x4_t*>(&ms[fb.k0(u)]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fb.v[u][i] = fmaf(-z, m[i], fb.v[u][i]);
+  }
+  fa.put(f1);
+  fb.put(f2);
+  f32x4_t acc3[kDS ? C::kBlocks : 1];
+#pragma unroll
+  for (int k = 0; k < (kDS ? C::kBlocks : 1); ++k) acc3[k] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+  float dzacc[NMB], dgacc[NMB], dw[NMB][4];
+#pragma unroll
+  for (int b = 0; b < NMB; ++b) {
+    dzacc[b] = dgacc[b] = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) dw[b][t] = 0.0f;
+  }
+  __syncthreads();
+
+  for (; b0 >= w0 && w1 > w0; b0 -= 16) {
+    float qh[NMB][4], o[NMB][4], dn[NMB][4];
+    // operands and taps are re-read from LDS each tile, not held in registers
     __asm__ volatile("" ::: "memory");
-    sq.conv(tq, g, qh);
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) {
-      rv[kq] = Raw<T>::widen(rraw[kq]);
-      dyv[kq] = Raw<float>::widen(dyraw[kq]);
-    }
-    const int cur = tok;
-    tok += 16;
-    sq.issue(rq, tok, g);  // the next block's rows (out of range past the slice: 0, unused)
-    issue_rd(tok);
-    float zd = 0.0f;
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) {
-      const f32x4_t zr = *reinterpret_cast<const f32x4_t*>(&zs[16 * kq + 4 * g]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        qh[kq][i] = phi_fast(qh[kq][i]);
-        zd = fmaf(qh[kq][i], zr[i], zd);
-      }
-    }
-    // num = S^T Qh (MFMA), den = z . Qh
-    f32x4_t acc1[NMB];
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) acc1[mb] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-    contract<D, NMB>(a1, lane, qh, acc1);
-    const float inv_den = 1.0f / sum_groups(zd);
-    float o[NMB][4], ss = 0.0f;
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        o[kq][i] = acc1[kq][i] * inv_den;
-        ss = fmaf(o[kq][i], o[kq][i], ss);
-      }
-    float dnum[NMB][4], dden, dcen;  // dcen = dden + m . dnum
+    const Window<T, D> xq = nq;
+    const int tb = b0 + 4 * g;
+    Row<T, D> rw[4];
+    Row<float, D> dyw[4];
     if constexpr (kNorm) {
-      const float rs = 1.0f / sqrtf(sum_groups(ss) / D + P.eps);
-      // gated RMSNorm backward
-      float doh[NMB][4], s1 = 0.0f;
 #pragma unroll
-      for (int kq = 0; kq < NMB; ++kq) {
-        const f32x4_t gm = *reinterpret_cast<const f32x4_t*>(&gs[16 * kq + 4 * g]);
-        float drv[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float r = rv[kq][i], d = dyv[kq][i];
-          const float sig = sigmoid_fast(r), silu = r * sig;
-          const float oh = o[kq][i] * rs;
-          doh[kq][i] = d * gm[i] * silu;
-          dgacc[kq][i] = fmaf(d * oh, silu, dgacc[kq][i]);
-          drv[i] = d * oh * gm[i] * sig * (1.0f + r * (1.0f - sig));
-          s1 = fmaf(doh[kq][i], o[kq][i], s1);
-        }
-        store4(rdr, eoff<D>(cur, 16 * kq + 4 * g), drv);
-      }
-      s1 = sum_groups(s1);
-      const float c3 = rs * rs * rs / D * s1;
-#pragma unroll
-      for (int kq = 0; kq < NMB; ++kq)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dnum[kq][i] = (rs * doh[kq][i] - c3 * o[kq][i]) * inv_den;
-      // do . o = rs s1 (1 - rs^2 |o|^2 / d) = eps rs^3 s1 exactly (rs^-2 = |o|^2/d + eps):
-      // the RMSNorm leaves almost nothing along o, and summing do . o would
-      // return mostly the rounding of its terms.
-      dden = -P.eps * rs * rs * rs * s1 * inv_den;
-      float md = 0.0f;
-#pragma unroll
-      for (int kq = 0; kq < NMB; ++kq) {
-        const f32x4_t mr = *reinterpret_cast<const f32x4_t*>(&ms[16 * kq + 4 * g]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) md = fmaf(mr[i], dnum[kq][i], md);
-      }
-      dcen = dden + sum_groups(md);
-    } else {  // y = o: do = dy
-      float s2 = 0.0f, s2c = 0.0f;
-#pragma unroll
-      for (int kq = 0; kq < NMB; ++kq) {
-        const f32x4_t mr = *reinterpret_cast<const f32x4_t*>(&ms[16 * kq + 4 * g]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          dnum[kq][i] = dyv[kq][i] * inv_den;
-          s2 = fmaf(dyv[kq][i], o[kq][i], s2);
-          s2c = fmaf(dyv[kq][i], o[kq][i] - mr[i], s2c);
-        }
-      }
-      dden = -sum_groups(s2) * inv_den;
-      dcen = -sum_groups(s2c) * inv_den;
+      for (int i = 0; i < 4; ++i) rw[i].load(rr, row_off<T, D>(tb, n) + (uint32_t)(i * D * sizeof(T)));
     }
-    // dQh = S' dnum + z (dden + m . dnum)
-    f32x4_t acc2[NMB];
 #pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) acc2[mb] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-    contract<D, NMB>(a2, lane, dnum, acc2);
+    for (int i = 0; i < 4; ++i) dyw[i].load(rdy, row_off<float, D>(tb, n) + (uint32_t)(i * D * 4));
+    xq.conv(LdsTaps<D>{tq, n}, qh);
+    nq.load(rq, b0 - 16 + 4 * g, n);  // the tile before (before the slice: reads 0, unused)
+    float den[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) {
-      const f32x4_t zr = *reinterpret_cast<const f32x4_t*>(&zs[16 * kq + 4 * g]);
-      float dq[4];
+    for (int b = 0; b < NMB; ++b) {
+      const float z = zs[slot_chan<D>(b, n)];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        // phi'(u) = 1 for u > 0 and e^u = phi(u) <= 1 otherwise: min(phi(u), 1)
-        dq[i] = fmaf(zr[i], dcen, acc2[kq][i]) * fminf(qh[kq][i], 1.0f);
-        dzacc[kq][i] = fmaf(qh[kq][i], dden, dzacc[kq][i]);
+        qh[b][i] = phi_fast(qh[b][i]);
+        den[i] = fmaf(qh[b][i], z, den[i]);
       }
-      store4(rdq, eoff<D>(cur, 16 * kq + 4 * g), dq);
     }
+    // num = S^T Qh, den = z . Qh
+    {
+      f32x4_t acc[NMB];
+#pragma unroll
+      for (int b = 0; b < NMB; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+      contract_rows<D>(qh, stg[wave], f1, lane, acc);
+#pragma unroll
+      for (int b = 0; b < NMB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[b][i] = acc[b][i];
+    }
+    float dden[4], dcen[4];  // dcen = dden + m . dnum
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float inv_den = 1.0f / sum_row16(den[i]);
+      float ss = 0.0f;
+#pragma unroll
+      for (int b = 0; b < NMB; ++b) {
+        o[b][i] *= inv_den;
+        ss = fmaf(o[b][i], o[b][i], ss);
+      }
+      if constexpr (kNorm) {
+        const float rs = rsqrt_nr(sum_row16(ss) * (1.0f / D) + P.eps);
+        float s1 = 0.0f, drv[NMB][4];
+#pragma unroll
+        for (int b = 0; b < NMB; ++b) {
+          const float r = rw[i].at(b), d = dyw[i].at(b), gm = gs[slot_chan<D>(b, n)];
+          const float sig = sigmoid_fast(r), silu = r * sig;
+          const float dyoh = d * (o[b][i] * rs);
+          dn[b][i] = d * gm * silu;  // doh
+          dgacc[b] = fmaf(dyoh, silu, dgacc[b]);
+          drv[b][0] = dyoh * gm * sig * (1.0f + r * (1.0f - sig));
+          s1 = fmaf(dn[b][i], o[b][i], s1);
+        }
+        store_row<D>(rdr, row_off<float, D>(tb, n) + (uint32_t)(i * D * 4), drv, 0);
+        s1 = sum_row16(s1);
+        const float c3 = rs * rs * rs / D * s1;
+        // do . o = rs s1 (1 - rs^2 |o|^2 / d) = eps rs^3 s1 exactly (rs^-2 = |o|^2/d + eps):
+        // the RMSNorm leaves almost nothing along o, and summing do . o would
+        // return mostly the rounding of its terms.
+        dden[i] = -P.eps * rs * rs * rs * s1 * inv_den;
+        float md = 0.0f;
+#pragma unroll
+        for (int b = 0; b < NMB; ++b) {
+          dn[b][i] = (rs * dn[b][i] - c3 * o[b][i]) * inv_den;
+          md = fmaf(ms[slot_chan<D>(b, n)], dn[b][i], md);
+        }
+        dcen[i] = dden[i] + sum_row16(md);
+      } else {  // y = o: do = dy
+        float s2 = 0.0f, s2c = 0.0f;
+#pragma unroll
+        for (int b = 0; b < NMB; ++b) {
+          const float d = dyw[i].at(b);
+          dn[b][i] = d * inv_den;
+          s2 = fmaf(d, o[b][i], s2);
+          s2c = fmaf(d, o[b][i] - ms[slot_chan<D>(b, n)], s2c);
+        }
+        dden[i] = -sum_row16(s2) * inv_den;
+        dcen[i] = -sum_row16(s2c) * inv_den;
+      }
+    }
+    // dS += Qh dnum^T; dQh = S' dnum + z (dden + m . dnum)
     if constexpr (kDS) {
-      // dS += sum over the block's tokens of Qh dnum^T
-      wave_lds_sync();  // the previous block's reads of X, Y are done
-      stage_sigma<D>(X, n, g, qh);
-      stage_sigma<D>(Y, n, g, dnum);
-      wave_lds_sync();
-      token_product<D>(X, Y, lane, acc3);
+      token_product<D>(qh, dn, acc3);
     } else {
 #pragma unroll
-      for (int kq = 0; kq < NMB; ++kq) store4(rdn, eoff<D>(cur, 16 * kq + 4 * g), dnum[kq]);
+      for (int i = 0; i < 4; ++i)
+        store_row<D>(rdn, row_off<float, D>(tb, n) + (uint32_t)(i * D * 4), dn, i);
     }
+    {
+      f32x4_t acc[NMB];
+#pragma unroll
+      for (int b = 0; b < NMB; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+      contract_rows<D>(dn, stg[wave], f2, lane, acc);
+#pragma unroll
+      for (int b = 0; b < NMB; ++b) {
+        const float z = zs[slot_chan<D>(b, n)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          // phi'(u) = 1 for u > 0 and e^u = phi(u) <= 1 otherwise: min(phi(u), 1)
+          o[b][i] = fmaf(z, dcen[i], acc[b][i]) * fminf(qh[b][i], 1.0f);
+          dzacc[b] = fmaf(qh[b][i], dden[i], dzacc[b]);
+        }
+      }
+    }
+    conv_back<T, D>(o, xq, LdsTaps<D>{tq, n}, stg[wave], later[wave], rdq, row_off<float, D>(tb, n), lane, dw);
   }
 
-  float* rec = dsp + ((size_t)h * P.units + unit) * P.rec_floats;
-  __syncthreads();  // every wave is done with its staging area
-  if constexpr (kDS) wave_ordered_sum<D>(acc3, sbuf, rec);
-  reduce_sigma<D>(dzacc, red, rec + D * D);
-  reduce_sigma<D>(dgacc, red, dgp + ((size_t)h * P.units + unit) * D);
+  wave_lds_sync();
+  store_edge<D>(later[wave], edge + edge_off<D>(P, 0, h, unit, wave), lane);
+  const size_t ui = (size_t)h * P.units + unit;
+  float* rec = dsp + ui * P.rec_floats;
+  __syncthreads();  // every wave is done with the operands
+  static_assert(2 * sizeof(f1) >= 2 * D * D * sizeof(float), "f1, f2 hold the waves' sums");
+  if constexpr (kDS) {
+    sum_waves<D>(acc3, reinterpret_cast<float*>(f1), reinterpret_cast<float*>(f2), rec);
+    __syncthreads();
+  }
+  sum_channels<D>(dzacc, reinterpret_cast<float(*)[D]>(f1), rec + D * D);
+  sum_channels<D>(dgacc, reinterpret_cast<float(*)[D]>(f1), dgp + ui * D);
+  sum_taps<D>(dw, reinterpret_cast<f32x4_t(*)[D]>(f1), dcp + (ui * 3 + 0) * D * 4);
 }
 
 // ---------------------------------------------------------------------------
 // dS of a unit from the query pass's dnum (d = 128): dS_p = sum_i Qh_i dnum_i^T
-// with Qh recomputed exactly as the query pass forms it, the tokens taken in
-// the same order (each wave its contiguous quarter, 16 at a time; the four
-// waves' partials added in wave order).  Writes S-part of the unit's record;
-// the query pass wrote its dz part.
-// ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ void __launch_bounds__(kThreads, 1)
-bwd_dsum_mfma_kernel(Plan P, const T* __restrict__ qin, const float* __restrict__ dnum,
-                     const float* __restrict__ conv_w, const int32_t* __restrict__ cu,
-                     float* __restrict__ dsp) {
-  using C = MF<D>;
-  constexpr int NMB = C::NMB;
-  __shared__ __attribute__((aligned(16))) float stg[4][2][C::kStage];  // [wave][Qh or dnum]
-  __shared__ f32x4_t tq[D];
-  static_assert(sizeof(stg) >= D * D * sizeof(float), "staging holds a d x d matrix");
-  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int h = blockIdx.y, unit = blockIdx.x;
-  int s, chunk;
-  if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
-  int64_t len, base_row;
-  seq_geometry(P, cu, s, h, &len, &base_row);
-  const int t0 = chunk * P.chunk;
-  const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
-  if (tid < D) {
-    float w4[4];
-    load_taps4(conv_w, P.heads, h, 0, D, P.W, tid, w4);
-    tq[tid] = (f32x4_t){w4[0], w4[1], w4[2], w4[3]};
-  }
-  __syncthreads();
-  const uint32_t rows = (uint32_t)len * D;
-  const __amdgpu_buffer_rsrc_t rq = make_rsrc(qin + base_row * D, rows * sizeof(T));
-  const __amdgpu_buffer_rsrc_t rdn = make_rsrc(dnum + base_row * D, rows * 4u);
-  f32x4_t acc[C::kBlocks];
-#pragma unroll
-  for (int k = 0; k < C::kBlocks; ++k) acc[k] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-  float* X = stg[wave][0];
-  float* Y = stg[wave][1];
-
-  const int q4 = P.chunk / 4, w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
-  RowStream<T, D> sq;
-  u32x4_t dnraw[NMB];
-  int tok = w0 + n;
-  auto issue_dn = [&](int tk) {
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) dnraw[kq] = Raw<float>::load(rdn, eoff<D>(tk, 16 * kq + 4 * g));
-  };
-  sq.start(rq, tok, g);
-  issue_dn(tok);
-  for (int b0 = w0; b0 < w1; b0 += 16) {
-    float qh[NMB][4], dn[NMB][4];
-    __asm__ volatile("" ::: "memory");  // taps are re-read from LDS, not held
-    sq.conv(tq, g, qh);
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) {
-      const f32x4_t d = Raw<float>::widen(dnraw[kq]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        qh[kq][i] = phi_fast(qh[kq][i]);
-        dn[kq][i] = d[i];
-      }
-    }
-    tok += 16;
-    sq.issue(rq, tok, g);  // the next block's rows (out of range past the slice: 0, unused)
-    issue_dn(tok);
-    wave_lds_sync();  // the previous block's reads of X, Y are done
-    stage_sigma<D>(X, n, g, qh);
-    stage_sigma<D>(Y, n, g, dn);
-    wave_lds_sync();
-    token_product<D>(X, Y, lane, acc);
-  }
-  float* rec = dsp + ((size_t)h * P.units + unit) * P.rec_floats;
-  __syncthreads();  // every wave is done with its staging area
-  wave_ordered_sum<D>(acc, &stg[0][0][0], rec);
-}
-
-// ---------------------------------------------------------------------------
-// Key pass, matrix-core version: no token sums, so the waves run their
-// 16-token blocks independently.
+// with Qh formed as the query pass forms it.  Writes the S part of the unit's
+// record; the query pass wrote its dz part.
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 __global__ void __launch_bounds__(kThreads, D >= 128 ? 1 : 2)
-bwd_key_mfma_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
-                    const T* __restrict__ ain, const float* __restrict__ conv_w,
-                    const int32_t* __restrict__ cu, const float* __restrict__ dSg,
-                    const float* __restrict__ mz, float* __restrict__ dkt,
-                    float* __restrict__ dvt, float* __restrict__ da) {
-  using C = MF<D>;
+bwd_dsum_rows_kernel(Plan P, const T* __restrict__ qin, const float* __restrict__ dnum,
+                     const float* __restrict__ conv_w, const int32_t* __restrict__ cu,
+                     float* __restrict__ dsp) {
+  using C = CL<D>;
   constexpr int NMB = C::NMB;
-  __shared__ f32x4_t a4[NMB * NMB * 64];  // t = dS vt: A[c][e] = dS[c][e]
-  __shared__ f32x4_t a5[NMB * NMB * 64];  // dvt = dS^T P: A[e][c] = dS[c][e]
-  // dS staged for the layouts (d <= 64; at d = 128 they are built from memory)
-  constexpr bool kStaged = D <= 64;
-  __shared__ __attribute__((aligned(16))) float sbuf[kStaged ? D * D : 4];
-  __shared__ f32x4_t tk[D], tv[D];
-  __shared__ __attribute__((aligned(16))) float dzs[D];
+  __shared__ __attribute__((aligned(16))) float buf[2 * D * D];  // the waves' sums
+  __shared__ f32x4_t tq[D];
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.y, unit = blockIdx.x;
   int s, chunk;
   if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
+  s = __builtin_amdgcn_readfirstlane(s);
+  chunk = __builtin_amdgcn_readfirstlane(chunk);
   int64_t len, base_row;
   seq_geometry(P, cu, s, h, &len, &base_row);
   const int t0 = chunk * P.chunk;
   const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
-  const size_t sh = (size_t)s * P.heads + h;
-  const float* dS = dSg + sh * (D * D + D);
-  if constexpr (kStaged) stage_matrix<D>(dS, sbuf);
-  if (tid < D) {
-    float w4[4];
-    load_taps4(conv_w, P.heads, h, 1, D, P.W, tid, w4);
-    tk[tid] = (f32x4_t){w4[0], w4[1], w4[2], w4[3]};
-    load_taps4(conv_w, P.heads, h, 2, D, P.W, tid, w4);
-    tv[tid] = (f32x4_t){w4[0], w4[1], w4[2], w4[3]};
-    dzs[tid] = dS[D * D + tid];
-  }
-  const float M = mz[2 * sh], Z = mz[2 * sh + 1];
-  const float invZ = Z > 0.0f ? 1.0f / Z : 0.0f;
-  __syncthreads();
-  build_frags<D, false>(kStaged ? sbuf : dS, a4);
-  build_frags<D, true>(kStaged ? sbuf : dS, a5);
-  __syncthreads();
-
   const uint32_t rows = (uint32_t)len * D;
-  const __amdgpu_buffer_rsrc_t rk = make_rsrc(kin + base_row * D, rows * sizeof(T));
-  const __amdgpu_buffer_rsrc_t rv = make_rsrc(vin + base_row * D, rows * sizeof(T));
-  // absent gate logits read as 0 and an absent da is not written (empty ranges)
-  const __amdgpu_buffer_rsrc_t ra =
-      ain ? make_rsrc(ain + base_row, (uint32_t)len * sizeof(T)) : make_rsrc(kin, 0u);
-  const __amdgpu_buffer_rsrc_t rdk = make_rsrc(dkt + base_row * D, rows * 4u);
-  const __amdgpu_buffer_rsrc_t rdv = make_rsrc(dvt + base_row * D, rows * 4u);
-  const __amdgpu_buffer_rsrc_t rda =
-      da ? make_rsrc(da + base_row, (uint32_t)t1 * 4u) : make_rsrc(dkt, 0u);
-
-  // the wave's contiguous quarter of the unit, 16 tokens at a time
-  const int q4 = P.chunk / 4, w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
-  RowStream<T, D> sk, sv;
-  int tok = w0 + n;
-  sk.start(rk, tok, g);
-  sv.start(rv, tok, g);
-  float al = load1<T>(ra, (uint32_t)tok);
+  const __amdgpu_buffer_rsrc_t rq = make_rsrc(qin + base_row * D, rows * sizeof(T));
+  // dnum past the unit's end reads 0
+  const __amdgpu_buffer_rsrc_t rdn = make_rsrc(dnum + base_row * D, (uint32_t)t1 * (uint32_t)(D * 4));
+  const int q4 = quarter_tokens(t1 - t0);
+  const int w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
+  Window<T, D> nq;
+  Row<float, D> nd[4];
+  auto issue = [&](int b0) {
+    nq.load(rq, b0 + 4 * g, n);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) nd[i].load(rdn, row_off<float, D>(b0 + 4 * g, n) + (uint32_t)(i * D * 4));
+  };
+  issue(w0);
+  stage_taps<D>(conv_w, P.heads, h, 0, P.W, tq);
+  f32x4_t acc[C::kBlocks];
+#pragma unroll
+  for (int k = 0; k < C::kBlocks; ++k) acc[k] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+  __syncthreads();
   for (int b0 = w0; b0 < w1; b0 += 16) {
-    float kt[NMB][4], vt[NMB][4];
-    // the A fragments are re-read from LDS each block rather than held in
-    // registers across the loop
-    __asm__ volatile("" ::: "memory");
-    sk.conv(tk, g, kt);
-    sv.conv(tv, g, vt);
-    const float gj = __expf(al - M) * invZ;
-    const int cur = tok;
-    tok += 16;
-    sk.issue(rk, tok, g);  // the next block's rows (out of range past the slice: 0, unused)
-    sv.issue(rv, tok, g);
-    al = load1<T>(ra, (uint32_t)tok);
-    // t = dS vt + dz
-    f32x4_t acc4[NMB];
+    float qh[NMB][4], dn[NMB][4];
+    __asm__ volatile("" ::: "memory");  // taps are re-read from LDS, not held
+    nq.conv(LdsTaps<D>{tq, n}, qh);
 #pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) acc4[mb] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-    contract<D, NMB>(a4, lane, vt, acc4);
-    float pk[NMB][4], dgl = 0.0f;
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) {
-      const f32x4_t dzr = *reinterpret_cast<const f32x4_t*>(&dzs[16 * kq + 4 * g]);
-      float dk[4];
+    for (int b = 0; b < NMB; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float u = kt[kq][i];
-        const float p = phi_fast(u);
-        const float t = acc4[kq][i] + dzr[i];
-        dk[i] = gj * t * (u > 0.0f ? 1.0f : p);
-        dgl = fmaf(p, t, dgl);
-        pk[kq][i] = p;
+        qh[b][i] = phi_fast(qh[b][i]);
+        dn[b][i] = nd[i].at(b);
       }
-      store4(rdk, eoff<D>(cur, 16 * kq + 4 * g), dk);
-    }
-    const float dg = sum_groups(dgl);
-    if (g == 0)
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, gj * dg), rda,
-                                            (uint32_t)cur * 4u, 0, 0);
-    // dvt = g dS^T P
-    f32x4_t acc5[NMB];
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) acc5[mb] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-    contract<D, NMB>(a5, lane, pk, acc5);
-#pragma unroll
-    for (int kq = 0; kq < NMB; ++kq) {
-      float dv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) dv[i] = gj * acc5[kq][i];
-      store4(rdv, eoff<D>(cur, 16 * kq + 4 * g), dv);
-    }
+    issue(b0 + 16);
+    token_product<D>(qh, dn, acc);
   }
+  sum_waves<D>(acc, buf, buf + D * D, dsp + ((size_t)h * P.units + unit) * P.rec_floats);
 }
 
 // ---------------------------------------------------------------------------
-// Conv1D backward, streaming version: grid (units, H, 3 tensors).  Thread
-// (run, c4) handles channels 4 c4 .. 4 c4 + 3 of runs of 8 consecutive
-// tokens; the run's dxt rows m .. m + 10 and x rows m - 3 .. m + 7 are loaded
-// at once (out-of-range rows read 0).  The tap gradients of the unit are
-// summed over the runs in run order.
+// Key pass: grid (units, H).
 // ---------------------------------------------------------------------------
 template <typename T, int D>
+__global__ void __launch_bounds__(kThreads, D >= 128 ? 1 : 2)
+bwd_key_rows_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
+                    const T* __restrict__ ain, const float* __restrict__ conv_w,
+                    const int32_t* __restrict__ cu, const float* __restrict__ dSg,
+                    const float* __restrict__ mz, float* __restrict__ dk, float* __restrict__ dv,
+                    float* __restrict__ da, float* __restrict__ dcp, float* __restrict__ edge) {
+  using C = CL<D>;
+  constexpr int NMB = C::NMB;
+  __shared__ f32x4_t f1[C::kFrag];  // t = dS vt: B[e][c] = dS[c][e]
+  __shared__ f32x4_t f2[C::kFrag];  // dvt = dS^T P: B[c][e] = dS[c][e]
+  __shared__ __attribute__((aligned(16))) float stg[4][C::kStage];
+  __shared__ __attribute__((aligned(16))) float later[4][2][3 * D];  // dkt, dvt
+  // gates of the unit's tokens, zero past the sequence end
+  __shared__ __attribute__((aligned(16))) float gt[kBwdUnit];
+  __shared__ float dzs[D];
+  constexpr bool kRegTaps = D >= 128;  // the operand layouts fill the LDS
+  __shared__ f32x4_t tk[kRegTaps ? 1 : D], tv[kRegTaps ? 1 : D];
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = blockIdx.y, unit = blockIdx.x;
+  int s, chunk;
+  if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
+  s = __builtin_amdgcn_readfirstlane(s);
+  chunk = __builtin_amdgcn_readfirstlane(chunk);
+  int64_t len, base_row;
+  seq_geometry(P, cu, s, h, &len, &base_row);
+  const int t0 = chunk * P.chunk;
+  const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
+  const uint32_t rows = (uint32_t)len * D;
+  const __amdgpu_buffer_rsrc_t rk = make_rsrc(kin + base_row * D, rows * sizeof(T));
+  const __amdgpu_buffer_rsrc_t rv = make_rsrc(vin + base_row * D, rows * sizeof(T));
+  const __amdgpu_buffer_rsrc_t rdk = make_rsrc(dk + base_row * D, rows * 4u);
+  const __amdgpu_buffer_rsrc_t rdv = make_rsrc(dv + base_row * D, rows * 4u);
+  // an absent da is not written (an empty range)
+  const __amdgpu_buffer_rsrc_t rda =
+      da ? make_rsrc(da + base_row, (uint32_t)t1 * 4u) : make_rsrc(dk, 0u);
+  const int q4 = quarter_tokens(t1 - t0);
+  const int w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
+  int b0 = w0 + (w1 > w0 ? (w1 - w0 - 1) / 16 * 16 : 0);  // the wave's last tile
+  Window<T, D> nk, nv;
+  nk.load(rk, b0 + 4 * g, n);
+  nv.load(rv, b0 + 4 * g, n);
+
+  const size_t sh = (size_t)s * P.heads + h;
+  const float* dS = dSg + sh * (D * D + D);
+  Frags<D> fa, fb;
+  fa.load_transposed(dS);
+  fb.load(dS);
+  using Taps = typename std::conditional<kRegTaps, RegTaps<D>, LdsTaps<D>>::type;
+  Taps wk, wv;
+  if constexpr (kRegTaps) {
+    wk.load(conv_w, P.heads, h, 1, P.W, n);
+    wv.load(conv_w, P.heads, h, 2, P.W, n);
+  } else {
+    stage_taps<D>(conv_w, P.heads, h, 1, P.W, tk);
+    stage_taps<D>(conv_w, P.heads, h, 2, P.W, tv);
+    wk = LdsTaps<D>{tk, n};
+    wv = LdsTaps<D>{tv, n};
+  }
+  if (tid < D) dzs[tid] = dS[D * D + tid];
+  const float M = mz[2 * sh], Z = mz[2 * sh + 1];
+  const float invZ = Z > 0.0f ? 1.0f / Z : 0.0f;
+  for (int j = tid; j < 4 * q4; j += kThreads)
+    gt[j] = j < t1 - t0 ? __expf(logit<T>(ain, base_row + t0 + j) - M) * invZ : 0.0f;
+  for (int x = lane; x < 6 * D; x += 64) (&later[wave][0][0])[x] = 0.0f;
+  fa.put(f1);
+  fb.put(f2);
+  float dwk[NMB][4], dwv[NMB][4];
+#pragma unroll
+  for (int b = 0; b < NMB; ++b)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) dwk[b][t] = dwv[b][t] = 0.0f;
+  __syncthreads();
+
+  for (; b0 >= w0 && w1 > w0; b0 -= 16) {
+    float pk[NMB][4], x[NMB][4];
+    __asm__ volatile("" ::: "memory");  // operands and taps are re-read from LDS
+    const Window<T, D> xk = nk, xv = nv;
+    const uint32_t off = row_off<float, D>(b0 + 4 * g, n);
+    xk.conv(wk, pk);
+    xv.conv(wv, x);
+    nk.load(rk, b0 - 16 + 4 * g, n);  // the tile before (before the slice: reads 0, unused)
+    nv.load(rv, b0 - 16 + 4 * g, n);
+    const f32x4_t gj = *reinterpret_cast<const f32x4_t*>(&gt[b0 - t0 + 4 * g]);
+    // t = dS vt + dz; dkt = g t phi'(kt); da = g (P . t)
+    {
+      f32x4_t acc[NMB];
+#pragma unroll
+      for (int b = 0; b < NMB; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+      contract_rows<D>(x, stg[wave], f1, lane, acc);
+      float dgl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int b = 0; b < NMB; ++b) {
+        const float dz = dzs[slot_chan<D>(b, n)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float p = phi_fast(pk[b][i]), t = acc[b][i] + dz;
+          pk[b][i] = p;
+          x[b][i] = gj[i] * t * fminf(p, 1.0f);  // phi'(u) = min(phi(u), 1)
+          dgl[i] = fmaf(p, t, dgl[i]);
+        }
+      }
+      float dg = 0.0f;  // lane n < 4 writes token 4 g + n
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float v = gj[i] * sum_row16(dgl[i]);
+        dg = n == i ? v : dg;
+      }
+      if (n < 4)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, dg), rda,
+                                              (uint32_t)(b0 + 4 * g + n) * 4u, 0, 0);
+    }
+    conv_back<T, D>(x, xk, wk, stg[wave], later[wave][0], rdk, off, lane, dwk);
+    // dvt = g dS^T P
+    {
+      f32x4_t acc[NMB];
+#pragma unroll
+      for (int b = 0; b < NMB; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+      contract_rows<D>(pk, stg[wave], f2, lane, acc);
+#pragma unroll
+      for (int b = 0; b < NMB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[b][i] = gj[i] * acc[b][i];
+    }
+    conv_back<T, D>(x, xv, wv, stg[wave], later[wave][1], rdv, off, lane, dwv);
+  }
+
+  wave_lds_sync();
+  store_edge<D>(later[wave][0], edge + edge_off<D>(P, 1, h, unit, wave), lane);
+  store_edge<D>(later[wave][1], edge + edge_off<D>(P, 2, h, unit, wave), lane);
+  const size_t ui = (size_t)h * P.units + unit;
+  __syncthreads();  // every wave is done with the operands
+  sum_taps<D>(dwk, reinterpret_cast<f32x4_t(*)[D]>(f1), dcp + (ui * 3 + 1) * D * 4);
+  sum_taps<D>(dwv, reinterpret_cast<f32x4_t(*)[D]>(f1), dcp + (ui * 3 + 2) * D * 4);
+}
+
+// ---------------------------------------------------------------------------
+// What the two passes leave: block (unit, h) of the first P.units adds the
+// missing products to dx of the three tokens before each wave's first token,
+//   dx_{p-3+j} += sum_{t <= j} w_t dxt_{p+j-t},  p > 0 the wave's first token,
+// the remaining blocks sum dgamma and the taps (bwd_params).
+// ---------------------------------------------------------------------------
+template <int D>
 __global__ void __launch_bounds__(kThreads)
-bwd_conv_stream_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ kin,
-                       const T* __restrict__ vin, const float* __restrict__ dxt_all,
-                       const float* __restrict__ conv_w, const int32_t* __restrict__ cu,
-                       float* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv,
-                       float* __restrict__ dcp, size_t act_elems) {
-  constexpr int CG = D / 4, RUNS = kThreads / CG, RL = 8;
-  __shared__ f32x4_t red[RUNS][D];
-  const int tid = threadIdx.x, c4 = tid % CG, run = tid / CG, c0 = 4 * c4;
-  const int h = blockIdx.y, unit = blockIdx.x, tensor = blockIdx.z;
+bwd_finish_kernel(Plan P, const int32_t* __restrict__ cu, const float* __restrict__ conv_w,
+                  const float* __restrict__ edge, const float* __restrict__ dgp,
+                  const float* __restrict__ dcp, float* __restrict__ dq, float* __restrict__ dk,
+                  float* __restrict__ dv, float* __restrict__ dgamma, float* __restrict__ dconv) {
+  const int h = blockIdx.y, tid = threadIdx.x;
+  if ((int)blockIdx.x >= P.units) {
+    bwd_params<D>(P, cu, dgp, dcp, dgamma, dconv, h, blockIdx.x - P.units);
+    return;
+  }
+  const int unit = blockIdx.x;
   int s, chunk;
   if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
   int64_t len, base_row;
   seq_geometry(P, cu, s, h, &len, &base_row);
   const int t0 = chunk * P.chunk;
   const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
-  const T* x = tensor == 0 ? qin : tensor == 1 ? kin : vin;
-  float* out = tensor == 0 ? dq : tensor == 1 ? dk : dv;
-  const uint32_t rows = (uint32_t)len * D;
-  const __amdgpu_buffer_rsrc_t rx = make_rsrc(x + base_row * D, rows * sizeof(T));
-  const __amdgpu_buffer_rsrc_t rd =
-      make_rsrc(dxt_all + (size_t)tensor * act_elems + base_row * D, rows * 4u);
-  const __amdgpu_buffer_rsrc_t ro = make_rsrc(out + base_row * D, (uint32_t)t1 * D * 4u);
-  float w4[4][4];
+  const int q4 = quarter_tokens(t1 - t0);
+  for (int x = tid; x < 3 * 4 * D; x += kThreads) {  // (tensor, wave, channel)
+    const int c = x % D, wave = (x / D) & 3, tensor = x / (4 * D);
+    const int p = t0 + wave * q4;
+    if (p == 0 || p >= t1) continue;
+    float w4[4], d[3];
+    load_taps4(conv_w, P.heads, h, tensor, D, P.W, c, w4);
+    const float* e = edge + edge_off<D>(P, tensor, h, unit, wave) + c;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) load_taps4(conv_w, P.heads, h, tensor, D, P.W, c0 + c, w4[c]);
-  float dc[4][4];
+    for (int j = 0; j < 3; ++j) d[j] = e[j * D];
+    float* out = (tensor == 0 ? dq : tensor == 1 ? dk : dv) + (base_row + p - 3) * D + c;
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+    for (int j = 0; j < 3; ++j) {
+      float acc = out[j * D];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) dc[c][t] = 0.0f;
-  for (int b = t0 + run * RL; b < t1; b += RUNS * RL) {
-    f32x4_t d[RL + 3], xx[RL + 3];
-#pragma unroll
-    for (int r = 0; r < RL + 3; ++r) {
-      d[r] = load4<float>(rd, eoff<D>(b + r, c0));
-      xx[r] = load4<T>(rx, eoff<D>(b - 3 + r, c0));
+      for (int t = 0; t <= j; ++t) acc = fmaf(w4[t], d[j - t], acc);
+      out[j * D] = acc;
     }
-#pragma unroll
-    for (int j = 0; j < RL; ++j) {
-      // tokens past t1: their dxt rows read 0 (past len) or belong to the
-      // next unit, and their stores fall outside the range; no tap sums
-      const bool live = b + j < t1;
-      float y[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        float acc = w4[c][3] * d[j][c];
-        acc = fmaf(w4[c][2], d[j + 1][c], acc);
-        acc = fmaf(w4[c][1], d[j + 2][c], acc);
-        y[c] = fmaf(w4[c][0], d[j + 3][c], acc);
-        const float dd = live ? d[j][c] : 0.0f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) dc[c][t] = fmaf(dd, xx[j + t][c], dc[c][t]);
-      }
-      store4(ro, eoff<D>(b + j, c0), y);
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 4; ++c) red[run][c0 + c] = (f32x4_t){dc[c][0], dc[c][1], dc[c][2], dc[c][3]};
-  __syncthreads();
-  if (tid < D) {
-    f32x4_t acc = red[0][tid];
-    for (int r = 1; r < RUNS; ++r) acc += red[r][tid];
-    *reinterpret_cast<f32x4_t*>(dcp + (((size_t)h * P.units + unit) * 3 + tensor) * D * 4 + tid * 4) = acc;
   }
 }
 
@@ -1548,69 +1238,58 @@ gbla_status run_backward(const Plan& p, const BwdLayout& L, const void* q, const
   float* dsp = reinterpret_cast<float*>(base + L.off_dsp);
   float* dS = reinterpret_cast<float*>(base + L.off_dS);
   float* dgp = reinterpret_cast<float*>(base + L.off_dgp);
-  float* dxt = reinterpret_cast<float*>(base + L.off_dxt);
   float* dcp = reinterpret_cast<float*>(base + L.off_dcp);
-  const size_t act_elems = (size_t)p.tokens * p.heads * D;
+  float* edge = reinterpret_cast<float*>(base + L.off_edge);
   const dim3 grid(p.units, p.heads);
-  // Matrix-core kernels for every head dim; 32-bit buffer offsets need every
-  // fp32 (sequence, head) slice below 2^31 bytes.
-  const bool small_slices = (int64_t)p.rows * D * 4 < (int64_t(1) << 31);
   constexpr int kElems = D * D + D;
   const dim3 cgrid((unsigned)((int64_t)p.nseq * p.heads), (kElems + kThreads - 1) / kThreads);
-  bool mfma = small_slices;
-  if (mfma) {
-    // d = 128: the query pass writes dnum into the third dxt slot (the key
-    // pass fills it only afterwards) and bwd_dsum_mfma_kernel sums dS from it
+  const int nparam = (D + 3 * D * p.W + 63) / 64;  // slices of bwd_params
+  const T *qq = (const T*)q, *kk = (const T*)k, *vv = (const T*)v, *aa = (const T*)a, *rr = (const T*)r;
+  if (rows_supported(p)) {
+    gbla_status e = launch_state_rows(p, k, v, a, conv_w, cu, dsp, false, st);
+    if (e != GBLA_OK) return e;
+    e = launch_combine_f32(p, cu, dsp, S, z, mz, st);
+    if (e != GBLA_OK) return e;
+    // d = 128: the query pass leaves dnum in dv, which the key pass fills only
+    // after bwd_dsum_rows_kernel has read it
     constexpr bool kDS = D <= 64;
-    float* dnum = dxt + 2 * act_elems;
-    hipLaunchKernelGGL((bwd_state_mfma_kernel<T, D>), grid, dim3(kThreads), 0, st, p,
-                       (const T*)k, (const T*)v, (const T*)a, conv_w, cu, dsp);
-    gbla_status e = launch_combine_f32(p, cu, dsp, S, z, mz, st);
-    if (e != GBLA_OK) return e;
     if (gamma)
-      hipLaunchKernelGGL((bwd_query_mfma_kernel<T, D, true, kDS>), grid, dim3(kThreads), 0, st, p,
-                         (const T*)q, (const T*)r, dy, conv_w, gamma, cu, (const float*)S,
-                         (const float*)z, dxt, dr, dsp, dgp, dnum);
+      hipLaunchKernelGGL((bwd_query_rows_kernel<T, D, true, kDS>), grid, dim3(kThreads), 0, st, p, qq,
+                         rr, dy, conv_w, gamma, cu, S, z, dq, dr, dsp, dgp, dcp, edge, dv);
     else
-      hipLaunchKernelGGL((bwd_query_mfma_kernel<T, D, false, kDS>), grid, dim3(kThreads), 0, st, p,
-                         (const T*)q, (const T*)r, dy, conv_w, gamma, cu, (const float*)S,
-                         (const float*)z, dxt, dr, dsp, dgp, dnum);
+      hipLaunchKernelGGL((bwd_query_rows_kernel<T, D, false, kDS>), grid, dim3(kThreads), 0, st, p, qq,
+                         rr, dy, conv_w, gamma, cu, S, z, dq, dr, dsp, dgp, dcp, edge, dv);
     if constexpr (!kDS)
-      hipLaunchKernelGGL((bwd_dsum_mfma_kernel<T, D>), grid, dim3(kThreads), 0, st, p,
-                         (const T*)q, (const float*)dnum, conv_w, cu, dsp);
+      hipLaunchKernelGGL((bwd_dsum_rows_kernel<T, D>), grid, dim3(kThreads), 0, st, p, qq,
+                         (const float*)dv, conv_w, cu, dsp);
     hipLaunchKernelGGL((bwd_dscombine_kernel<D>), cgrid, dim3(kThreads), 0, st, p, cu,
                        (const float*)dsp, dS);
-    hipLaunchKernelGGL((bwd_key_mfma_kernel<T, D>), grid, dim3(kThreads), 0, st, p,
-                       (const T*)k, (const T*)v, (const T*)a, conv_w, cu, (const float*)dS,
-                       (const float*)mz, dxt + act_elems, dxt + 2 * act_elems, da);
+    hipLaunchKernelGGL((bwd_key_rows_kernel<T, D>), grid, dim3(kThreads), 0, st, p, kk, vv, aa, conv_w,
+                       cu, (const float*)dS, (const float*)mz, dk, dv, da, dcp, edge);
+    hipLaunchKernelGGL((bwd_finish_kernel<D>), dim3(p.units + nparam, p.heads), dim3(kThreads), 0, st,
+                       p, cu, conv_w, (const float*)edge, (const float*)dgp, (const float*)dcp, dq, dk,
+                       dv, dgamma, dconv);
+    return hipGetLastError() == hipSuccess ? GBLA_OK : GBLA_ERR_HIP;
   }
-  if (!mfma) {
-    hipLaunchKernelGGL((bwd_state_kernel<T, D>), grid, dim3(kThreads), 0, st, p, (const T*)k,
-                       (const T*)v, (const T*)a, conv_w, cu, dsp);
-    gbla_status e = launch_combine_f32(p, cu, dsp, S, z, mz, st);
-    if (e != GBLA_OK) return e;
-    if (gamma)
-      hipLaunchKernelGGL((bwd_query_kernel<T, D, true>), grid, dim3(kThreads), 0, st, p,
-                         (const T*)q, (const T*)r, dy, conv_w, gamma, cu, S, z, dxt, dr, dsp, dgp);
-    else
-      hipLaunchKernelGGL((bwd_query_kernel<T, D, false>), grid, dim3(kThreads), 0, st, p,
-                         (const T*)q, (const T*)r, dy, conv_w, gamma, cu, S, z, dxt, dr, dsp, dgp);
-    hipLaunchKernelGGL((bwd_dscombine_kernel<D>), cgrid, dim3(kThreads), 0, st, p, cu,
-                       (const float*)dsp, dS);
-    hipLaunchKernelGGL((bwd_key_kernel<T, D>), grid, dim3(kThreads), 0, st, p, (const T*)k,
-                       (const T*)v, (const T*)a, conv_w, cu, (const float*)dS, (const float*)mz,
-                       dxt + act_elems, dxt + 2 * act_elems, da);
-  }
-  if (small_slices)
-    hipLaunchKernelGGL((bwd_conv_stream_kernel<T, D>), dim3(p.units, p.heads, 3), dim3(kThreads),
-                       0, st, p, (const T*)q, (const T*)k, (const T*)v, (const float*)dxt, conv_w,
-                       cu, dq, dk, dv, dcp, act_elems);
+  // slices of 2^31 bytes and more: vector kernels with 64-bit indexing
+  float* dxt = reinterpret_cast<float*>(base + L.off_dxt);
+  const size_t act_elems = (size_t)p.tokens * p.heads * D;
+  hipLaunchKernelGGL((bwd_state_kernel<T, D>), grid, dim3(kThreads), 0, st, p, kk, vv, aa, conv_w, cu, dsp);
+  gbla_status e = launch_combine_f32(p, cu, dsp, S, z, mz, st);
+  if (e != GBLA_OK) return e;
+  if (gamma)
+    hipLaunchKernelGGL((bwd_query_kernel<T, D, true>), grid, dim3(kThreads), 0, st, p, qq, rr, dy,
+                       conv_w, gamma, cu, S, z, dxt, dr, dsp, dgp);
   else
-    hipLaunchKernelGGL((bwd_conv_kernel<T, D>), dim3(p.units, p.heads, 3), dim3(kThreads), 0, st,
-                       p, (const T*)q, (const T*)k, (const T*)v, (const float*)dxt, conv_w, cu,
-                       dq, dk, dv, dcp, act_elems);
-  const int nout = D + 3 * D * p.W;
-  hipLaunchKernelGGL((bwd_param_kernel<D>), dim3(p.heads, (nout + 63) / 64), dim3(kThreads), 0, st, p, cu,
+    hipLaunchKernelGGL((bwd_query_kernel<T, D, false>), grid, dim3(kThreads), 0, st, p, qq, rr, dy,
+                       conv_w, gamma, cu, S, z, dxt, dr, dsp, dgp);
+  hipLaunchKernelGGL((bwd_dscombine_kernel<D>), cgrid, dim3(kThreads), 0, st, p, cu,
+                     (const float*)dsp, dS);
+  hipLaunchKernelGGL((bwd_key_kernel<T, D>), grid, dim3(kThreads), 0, st, p, kk, vv, aa, conv_w, cu,
+                     (const float*)dS, (const float*)mz, dxt + act_elems, dxt + 2 * act_elems, da);
+  hipLaunchKernelGGL((bwd_conv_kernel<T, D>), dim3(p.units, p.heads, 3), dim3(kThreads), 0, st, p, qq,
+                     kk, vv, (const float*)dxt, conv_w, cu, dq, dk, dv, dcp, act_elems);
+  hipLaunchKernelGGL((bwd_param_kernel<D>), dim3(p.heads, nparam), dim3(kThreads), 0, st, p, cu,
                      (const float*)dgp, (const float*)dcp, dgamma, dconv);
   return hipGetLastError() == hipSuccess ? GBLA_OK : GBLA_ERR_HIP;
 }

@@ -5,13 +5,25 @@
 #include "gbla_ext.h"
 
 namespace gbla {
+namespace {
+
+constexpr int kMinUnit = 64;  // the backward's shortest unit, one tile a wave
+
+}  // namespace
 
 gbla_status backward_plan(const Plan& p, Plan* out) {
-  // Units of 512 tokens, whatever the forward's: long enough to amortise each
-  // workgroup's set-up (A operands, the ordered wave sums), short enough for
-  // two workgroups per CU at n = 32768, H = 8 (measured against 256 and 1024).
+  // Units of at most 512 tokens: long enough to amortise each workgroup's
+  // set-up (A operands, the ordered wave sums), short enough for two workgroups
+  // per CU at n = 32768, H = 8.  Batches that would leave half of the CUs
+  // without one take shorter units, down to kMinUnit tokens (whole backward,
+  // units of 64 / 128 / 256 tokens: B = 4, n = 999, H = 4, d = 32 fp32 33 / 38 /
+  // 46 us; n = 512, H = 8, d = 64 44 / 54 / 73 us; where more workgroups than
+  // that are there the longer unit wins: B = 2, n = 4000, H = 8, d = 64 119 / 90
+  // / 86 us).
   Plan b = p;
+  const int64_t work = p.tokens * p.heads;
   b.chunk = 512;
+  while (b.chunk > kMinUnit && work < (int64_t)b.chunk * 128) b.chunk /= 2;
   int64_t units;
   if (p.ragged) {
     units = b.tokens / b.chunk + b.nseq;
@@ -95,6 +107,7 @@ BwdLayout make_bwd_layout(const Plan& p) {
   L.off_dsp = take(unit_recs * p.rec_floats * f);
   L.off_dS = take(pairs * (d * d + d) * f);
   L.off_dgp = take(unit_recs * d * f);
+  L.off_edge = take(unit_recs * 3 * 4 * 3 * d * f);
   L.off_dxt = take(3 * (size_t)p.tokens * p.heads * d * f);
   L.off_dcp = take(unit_recs * 3 * d * 4 * f);
   L.total_bytes = off;

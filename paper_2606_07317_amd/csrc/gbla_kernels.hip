@@ -10,6 +10,8 @@
 // Kernels:
 //   conv_kernel           the Conv1D alone (test hook): a tile of rows plus a
 //                         (W-1)-row halo is staged in LDS, fp32 out.
+//                         The next two kernels and readout_kernel serve slices of
+//                         2^31 bytes and more (64-bit indexing).
 //   state_partial_kernel  one workgroup per (head, chunk of tokens): conv of
 //                         k and v fused into the loads (a per-thread sliding
 //                         window), phi, gate weights exp(a - m_chunk), then
@@ -899,6 +901,8 @@ struct StateRun {
     gbla_status e;
     if (stream_supported(p)) {
       e = launch_state_stream(p, k, v, a, w, cu, partials, st);
+    } else if (p.dtype == GBLA_F32 && rows_supported(p)) {
+      e = launch_state_rows(p, k, v, a, w, cu, partials, true, st);
     } else {
       hipLaunchKernelGGL((state_partial_kernel<T, D>), dim3(p.units, p.heads), dim3(kThreads), 0,
                          st, p, (const T*)k, (const T*)v, (const T*)a, w, cu, partials);
@@ -931,6 +935,8 @@ struct ReadoutRun {
     const unsigned char* base = static_cast<const unsigned char*>(ws);
     if (stream_supported(p))
       return launch_readout_stream(p, q, r, w, gamma, cu, base + p.off_frags, out, st, ev);
+    if (p.dtype == GBLA_F32 && rows_supported(p))
+      return launch_readout_rows(p, q, r, w, gamma, cu, base + p.off_frags, out, st, ev);
     if (ev.any())
       hipExtLaunchKernelGGL((readout_kernel<T, D>), dim3(p.runits, p.heads), dim3(kThreads), 0, st,
                             ev.start, ev.stop, 0, p, (const T*)q, (const T*)r, w, gamma, cu,

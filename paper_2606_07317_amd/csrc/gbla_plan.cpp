@@ -19,11 +19,45 @@ int64_t next_pow2(int64_t x) {
   return p;
 }
 
+// Offsets and size of the workspace for `units` partial records per head.
+void set_workspace(Plan* q, int64_t units) {
+  const size_t part_bytes = (size_t)units * q->heads * q->rec_floats * sizeof(float);
+  q->off_frags = align_up(q->off_partials + part_bytes, 256);
+  q->total_bytes = align_up(q->off_frags + (size_t)q->nseq * q->heads * q->frag_bytes, 256);
+}
+
+// Split of the fp32 kernels, whose workgroups are smaller (four waves, two
+// workgroups per CU up to d = 64).  Small batches are cut finer: state units
+// of down to 64 tokens, readout tiles of down to 64 (whole forward, chunk 256 /
+// tile 512 against this rule: n = 256, H = 2, d = 32 19.4 against 15.1 us;
+// n = 1000, H = 4, d = 64 43.7 / 21.7; B = 2, n = 8191, H = 8, d = 64 66.8 /
+// 64.6).  At d = 128 a record is 66 KB and the units stay as they are (B = 8,
+// n = 2048, H = 8: 176 us, 201 with twice as many).  More records than the
+// fixed scratch of gbla_forward_noalloc holds are not taken for this, so that
+// the call accepts every shape that it does with the coarser split.
+void fp32_split(Plan* q) {
+  const int64_t work = q->tokens * q->heads;
+  while (q->rtile > 64 && work < (int64_t)q->rtile * 256) q->rtile /= 2;
+  if (q->d == 128) return;
+  int64_t chunk = next_pow2((work + 511) / 512);
+  if (chunk < 64) chunk = 64;
+  if (chunk >= q->chunk) return;
+  Plan t = *q;
+  set_workspace(&t, t.tokens / chunk + t.nseq);
+  if (t.total_bytes <= GBLA_NOALLOC_SCRATCH_BYTES) q->chunk = (int32_t)chunk;
+}
+
 }  // namespace
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
+
+bool rows_supported(const Plan& p) {
+  // 32-bit buffer offsets: every fp32 (sequence, head) slice below 2^31 bytes
+  return p.chunk <= kMaxChunk && p.chunk % 64 == 0 && p.rtile % 64 == 0 &&
+         (int64_t)p.rows * p.d * 4 < (int64_t(1) << 31);
+}
 
 gbla_status make_plan(const gbla_shape* s, bool ragged, Plan* p) {
   if (!s || !p) return GBLA_ERR_INVALID_ARGUMENT;
@@ -53,9 +87,14 @@ gbla_status make_plan(const gbla_shape* s, bool ragged, Plan* p) {
   const int64_t work = q.tokens * q.heads;
   int64_t chunk = next_pow2((work + 255) / 256);
   if (chunk < 256) chunk = 256;
-  if (chunk > 2048) chunk = 2048;
+  if (chunk > kMaxChunk) chunk = kMaxChunk;
   q.chunk = (int32_t)chunk;
   q.rtile = kReadoutTile;
+  q.rec_floats = (int32_t)align_up((size_t)q.d * q.d + q.d + 2, 64);
+  const size_t nmb = q.d / 16 + 1, nkb = q.d / 32;
+  const size_t lane_bytes = q.dtype == GBLA_BF16 ? 16 : 32;
+  q.frag_bytes = align_up(nmb * nkb * 64 * lane_bytes, 256);
+  if (q.dtype == GBLA_F32) fp32_split(&q);
 
   // Upper bounds valid for both layouts: sum_s max(1, ceil(len_s / u)) <=
   // tokens / u + N.  The partial records are sized with this bound so the
@@ -79,14 +118,8 @@ gbla_status make_plan(const gbla_shape* s, bool ragged, Plan* p) {
     q.runits = (int32_t)(rps * q.nseq);
   }
 
-  q.rec_floats = (int32_t)align_up((size_t)q.d * q.d + q.d + 2, 64);
-  const size_t nmb = q.d / 16 + 1, nkb = q.d / 32;
-  const size_t lane_bytes = q.dtype == GBLA_BF16 ? 16 : 32;
-  q.frag_bytes = align_up(nmb * nkb * 64 * lane_bytes, 256);
   q.off_partials = 0;
-  const size_t part_bytes = (size_t)units_cap * q.heads * q.rec_floats * sizeof(float);
-  q.off_frags = align_up(q.off_partials + part_bytes, 256);
-  q.total_bytes = align_up(q.off_frags + (size_t)q.nseq * q.heads * q.frag_bytes, 256);
+  set_workspace(&q, units_cap);
   *p = q;
   return GBLA_OK;
 }

@@ -10,6 +10,8 @@
 
 namespace gbla {
 
+constexpr int kMaxChunk = 2048;  // tokens of a state unit, at most
+
 // Everything a launch needs that depends only on the shape (never on the
 // contents of cu_seqlens), so that gbla_workspace_bytes and the entry points
 // always agree, and the split structure -- hence the summation order of the
@@ -105,5 +107,16 @@ gbla_status launch_state128(const Plan& p, const void* k, const void* v, const v
 gbla_status launch_readout_stream(const Plan& p, const void* q, const void* r, const float* conv_w,
                                   const float* gamma, const int32_t* cu, const unsigned char* frags,
                                   float* out, hipStream_t stream, KernelEvents ev = {});
+
+// fp32-product kernels (gbla_rows.hip): the fp32 forward, and the state that
+// the backward recomputes (either dtype; records as launch_state_stream's;
+// forward: with the fp32 forward's exponential).
+bool rows_supported(const Plan& p);
+gbla_status launch_state_rows(const Plan& p, const void* k, const void* v, const void* a,
+                              const float* conv_w, const int32_t* cu, float* partials,
+                              bool forward, hipStream_t stream);
+gbla_status launch_readout_rows(const Plan& p, const void* q, const void* r, const float* conv_w,
+                                const float* gamma, const int32_t* cu, const unsigned char* frags,
+                                float* out, hipStream_t stream, KernelEvents ev = {});
 
 }  // namespace gbla
