@@ -86,7 +86,8 @@ typedef struct {
   int32_t seqlen;     /* n (dense) or T = cu_seqlens[N_s] (ragged), >= 0          */
   int32_t head_dim;   /* d in {32, 64, 128}                                      */
   int32_t conv_width; /* W in [1, 4]                                             */
-  int32_t max_seqlen; /* ragged: an upper bound of the lengths (>= 0); dense: 0  */
+  int32_t max_seqlen; /* ragged: an upper bound of the lengths (>= 0); dense: 0.
+                         It only chooses kernels; a tight bound is faster       */
   int32_t dtype;      /* gbla_dtype of q, k, v, gate_logits and out_gate         */
   float eps;          /* RMSNorm epsilon, finite and >= 0                        */
   uint32_t flags;     /* OR of GBLA_NO_* switches; 0 is the full GBLA layer      */
@@ -185,7 +186,8 @@ gbla_status gbla_state(const gbla_shape* shape, const void* k, const void* v,
  * The readout and gated RMSNorm alone (o_i = phi(qt_i)^T S / phi(qt_i)^T z,
  * then y), reading the state that the last gbla_state call with the same
  * shape left in this workspace.  Stage hook for tests and timing; the
- * result equals gbla_forward's.
+ * result equals gbla_forward's (to rounding for batches of short sequences,
+ * which gbla_forward takes in one launch).
  */
 gbla_status gbla_readout(const gbla_shape* shape, const void* q, const void* out_gate,
                          const float* conv_w, const float* norm_w,

@@ -83,10 +83,14 @@ gbla_status forward_entry(const gbla_shape* shape, const void* q, const void* k,
   GBLA_TRY(check_ws(p, workspace, workspace_bytes));
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (ev.start && hipEventRecord(ev.start, st) != hipSuccess) return GBLA_ERR_HIP;
-  GBLA_TRY(gbla::launch_state(p, k, v, gate_logits, conv_w, cu_seqlens, workspace, nullptr,
-                              nullptr, nullptr, st));
   gbla::KernelEvents last;
   last.stop = ev.stop;
+  const gbla::KeyInputs keys = {k, v, gate_logits};
+  if (gbla::short_forward(p))
+    last.keys = &keys;
+  else
+    GBLA_TRY(gbla::launch_state(p, k, v, gate_logits, conv_w, cu_seqlens, workspace, nullptr,
+                                nullptr, nullptr, st));
   return gbla::launch_readout(p, q, out_gate, conv_w, norm_w, cu_seqlens, workspace, out, st,
                               last);
 }
@@ -286,9 +290,14 @@ gbla_status gbla_layer_forward(const gbla_layer_shape* shape, const void* x, con
   void *q = ws + L.off_q, *k = ws + L.off_k, *v = ws + L.off_v, *r = ws + L.off_r, *a = ws + L.off_a;
   GBLA_TRY(gbla::launch_project(L, x, conv_x, w_proj, cu_seqlens, ws + L.off_xt, q, k, v, r, a, st));
   void* cws = ws + L.off_core;
-  GBLA_TRY(gbla::launch_state(L.core, k, v, a, nullptr, cu_seqlens, cws, nullptr, nullptr,
-                              nullptr, st));
-  return gbla::launch_readout(L.core, q, r, nullptr, norm_w, cu_seqlens, cws, out, st);
+  gbla::KernelEvents last;
+  const gbla::KeyInputs keys = {k, v, a};
+  if (gbla::short_forward(L.core))
+    last.keys = &keys;
+  else
+    GBLA_TRY(gbla::launch_state(L.core, k, v, a, nullptr, cu_seqlens, cws, nullptr, nullptr,
+                                nullptr, st));
+  return gbla::launch_readout(L.core, q, r, nullptr, norm_w, cu_seqlens, cws, out, st, last);
 }
 
 const char* gbla_status_string(gbla_status status) {

@@ -933,6 +933,7 @@ struct ReadoutRun {
       return GBLA_OK;
     }
     const unsigned char* base = static_cast<const unsigned char*>(ws);
+    if (ev.keys) return launch_short_forward(p, q, *ev.keys, r, w, gamma, cu, out, st, ev);
     if (stream_supported(p))
       return launch_readout_stream(p, q, r, w, gamma, cu, base + p.off_frags, out, st, ev);
     if (p.dtype == GBLA_F32 && rows_supported(p))

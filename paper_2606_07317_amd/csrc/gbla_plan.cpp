@@ -59,6 +59,27 @@ bool rows_supported(const Plan& p) {
          (int64_t)p.rows * p.d * 4 < (int64_t(1) << 31);
 }
 
+// The one-launch forward gives each (sequence, head) one workgroup, so its time
+// is at least the longest sequence's (bf16 d = 64: 5 us + 0.037 us a token, half
+// of that at d = 32; fp32 about twice), while three launches spread long
+// sequences over the chip but take 14 to 25 us for any batch.  Whole forward,
+// one launch against three, H = 8, d = 64 bf16: B = 1 n = 256 15 / 24 us, B = 2
+// n = 512 24 / 26, B = 1 n = 1024 42 / 26; B = 16 n = 1024 56 / 41, B = 64
+// n = 1024 91 / 110, B = 32 n = 2048 111 / 108.  fp32 d = 64: n = 128 16 / 18,
+// n = 256 26 / 19, B = 16 n = 512 49 / 47, B = 32 n = 512 57 / 68, B = 32 n =
+// 1024 105 / 117; d = 32: n = 256 14 / 14, n = 512 23 / 15.  So: lengths up to the
+// first bound, or batches large enough that the longest sequence is a small
+// part of the chip's work.  The kernels are right for any length; max_seqlen
+// only chooses.
+bool short_forward(const Plan& p) {
+  if (!rows_supported(p) || p.d == 128) return false;
+  const bool bf16 = p.dtype == GBLA_BF16;
+  const int64_t longest = p.ragged ? p.max_seqlen : p.rows;
+  if ((int64_t)p.nseq * p.heads > kMaxGridX) return false;
+  if (longest <= (bf16 ? 512 : p.d == 64 ? 128 : 256)) return true;
+  return longest * (bf16 ? 300 : 256) <= p.tokens * p.heads;
+}
+
 gbla_status make_plan(const gbla_shape* s, bool ragged, Plan* p) {
   if (!s || !p) return GBLA_ERR_INVALID_ARGUMENT;
   if (s->batch < 1 || s->heads < 1 || s->seqlen < 0) return GBLA_ERR_INVALID_ARGUMENT;
@@ -78,6 +99,7 @@ gbla_status make_plan(const gbla_shape* s, bool ragged, Plan* p) {
   q.W = s->conv_width;
   q.dtype = s->dtype;
   q.ragged = ragged ? 1 : 0;
+  q.max_seqlen = ragged ? s->max_seqlen : 0;
   q.eps = s->eps;
   q.flags = s->flags;
   q.tokens = ragged ? (int64_t)s->seqlen : (int64_t)s->batch * s->seqlen;

@@ -24,6 +24,7 @@ struct Plan {
   int32_t W;           // conv width
   int32_t dtype;       // gbla_dtype
   int32_t ragged;      // 1 when cu_seqlens describes packed sequences
+  int32_t max_seqlen;  // ragged: the caller's bound of the lengths (for choices only)
   float eps;
   uint32_t flags;      // GBLA_NO_* switches
   int64_t tokens;      // sum of sequence lengths (B*n or T)
@@ -62,7 +63,15 @@ bool aligned(const void* p, size_t a);
 struct KernelEvents {
   hipEvent_t start = nullptr;
   hipEvent_t stop = nullptr;
+  // The key side of the forward when launch_readout is to run the whole pass
+  // in one launch (short_forward); NULL otherwise.
+  const struct KeyInputs* keys = nullptr;
   bool any() const { return start != nullptr || stop != nullptr; }
+};
+
+// Inputs of the state pass.
+struct KeyInputs {
+  const void *k, *v, *a;
 };
 
 // The forward pass behind gbla_forward, gbla_forward_timed and
@@ -115,6 +124,11 @@ bool rows_supported(const Plan& p);
 gbla_status launch_state_rows(const Plan& p, const void* k, const void* v, const void* a,
                               const float* conv_w, const int32_t* cu, float* partials,
                               bool forward, hipStream_t stream);
+// The whole forward in one launch, for batches of short sequences.
+bool short_forward(const Plan& p);
+gbla_status launch_short_forward(const Plan& p, const void* q, const KeyInputs& in, const void* r,
+                                 const float* conv_w, const float* gamma, const int32_t* cu,
+                                 float* out, hipStream_t stream, KernelEvents ev);
 gbla_status launch_readout_rows(const Plan& p, const void* q, const void* r, const float* conv_w,
                                 const float* gamma, const int32_t* cu, const unsigned char* frags,
                                 float* out, hipStream_t stream, KernelEvents ev = {});

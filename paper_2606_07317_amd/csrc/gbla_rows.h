@@ -271,11 +271,11 @@ __device__ __forceinline__ void token_product(const float (*x)[4], const float (
         acc[mb * NMB + nb] = mfma4(x[mb][i], y[nb][i], acc[mb * NMB + nb]);
 }
 
-// dst[c * D + e] = the four waves' token products, (w0 + w1) + (w2 + w3).
-// buf0, buf1: D^2 floats of LDS each, free to use.  Every thread calls.
+// buf0[c * D + e] = w0 + w1, buf1[c * D + e] = w2 + w3 of the four waves' token
+// products.  buf0, buf1: D^2 floats of LDS each, free to use.  Every thread
+// calls; the last step is a barrier.
 template <int D>
-__device__ __forceinline__ void sum_waves(const f32x4_t* acc, float* buf0, float* buf1,
-                                          float* __restrict__ dst) {
+__device__ __forceinline__ void put_waves(const f32x4_t* acc, float* buf0, float* buf1) {
   using C = CL<D>;
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -306,6 +306,12 @@ __device__ __forceinline__ void sum_waves(const f32x4_t* acc, float* buf0, float
     }
     __syncthreads();
   }
+}
+// dst[c * D + e] = (w0 + w1) + (w2 + w3).
+template <int D>
+__device__ __forceinline__ void sum_waves(const f32x4_t* acc, float* buf0, float* buf1,
+                                          float* __restrict__ dst) {
+  put_waves<D>(acc, buf0, buf1);
   for (int x = 4 * threadIdx.x; x < D * D; x += 4 * kThreads)
     *reinterpret_cast<f32x4_t*>(dst + x) = *reinterpret_cast<const f32x4_t*>(buf0 + x) +
                                            *reinterpret_cast<const f32x4_t*>(buf1 + x);

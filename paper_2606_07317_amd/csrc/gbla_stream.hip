@@ -493,7 +493,9 @@ readout_stream_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16_t* 
   seq_geometry(P, cu, s, h, &len, &base_row);
   const int64_t tt0 = (int64_t)tile * P.rtile;
   const int64_t tt1 = min(len, tt0 + (int64_t)P.rtile);
-  const int per_wave = P.rtile >> 2;
+  // a quarter of the tile's tokens a wave, in whole groups (short sequences
+  // would otherwise leave three waves idle)
+  const int per_wave = ((int)(tt1 - tt0) + 4 * C::kGroup - 1) / (4 * C::kGroup) * C::kGroup;
   const int r0 = (int)(tt0 + (int64_t)wave * per_wave);  // slice-relative
   const int r1 = (int)min(tt1, (int64_t)r0 + per_wave);
   const int ngroups = (r1 - r0 + C::kGroup - 1) / C::kGroup;  // < 1: the wave has no rows

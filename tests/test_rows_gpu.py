@@ -62,3 +62,61 @@ def test_fp32_forward_edges(G, dev, orc, d, width, heads):
                   cu_seqlens=t["cu_seqlens"], max_seqlen=t["max_seqlen"])
     torch.cuda.synchronize()
     close(y.cpu().numpy(), orc.forward_inputs(inp)["y"], 1e-5, "y")
+
+
+# One-launch forward: lengths about its tiles (16 tokens fp32, 32 bf16, four
+# waves), every length class of the longest-first order (over 4, 2, 1 times the
+# mean, the rest), empty sequences, more sequences than a workgroup has threads.
+SHORT_LENGTHS = {
+    "edges": [0, 1, 2, 3, 31, 32, 33, 63, 64, 65, 127, 128, 0],
+    "classes": [500, 1, 40, 90, 3, 300, 7, 100, 0, 5, 8, 60, 2, 4, 9, 20],
+    "many": [int(x) for x in (list(range(1, 41)) * 14)[:513]],
+}
+
+
+@pytest.mark.parametrize("flags", ["", "NO_GATE", "NO_CONV", "NO_NORM", "BLA"])
+@pytest.mark.parametrize("lens", list(SHORT_LENGTHS))
+@pytest.mark.parametrize("d,dtype,width", [(32, inputs.F32, 4), (64, inputs.F32, 2), (32, inputs.BF16, 3),
+                                           (64, inputs.BF16, 4)])
+def test_short_forward(G, dev, orc, d, dtype, width, lens, flags):
+    """The one-launch forward (max_seqlen given) against the oracle and against
+    the three launches that a loose max_seqlen takes."""
+    if flags and lens != "edges":
+        pytest.skip("the switches run on one set of lengths")
+    say("short forward", d, dtype, width, lens, flags)
+    lengths = SHORT_LENGTHS[lens]
+    if dtype == inputs.F32:  # fp32 takes one launch up to 128 (d = 64) or 256 tokens
+        lengths = [min(n, 128 if d == 64 else 256) for n in lengths]
+    inp = inputs.make_inputs(_case(d, dtype, width, 53, heads=2), lengths=lengths)
+    t = inputs.device_tensors(inp, dev)
+    fl = getattr(G, flags) if flags else 0
+    a = None if fl & G.NO_GATE else t["a"]
+    cw = None if fl & G.NO_CONV else t["conv_w"]
+    r, gm = (None, None) if fl & G.NO_NORM else (t["r"], t["gamma"])
+
+    def run(max_seqlen):
+        y = G.forward(t["q"], t["k"], t["v"], a, r, cw, gm, eps=inp.eps, cu_seqlens=t["cu_seqlens"],
+                      max_seqlen=max_seqlen, flags=fl)
+        torch.cuda.synchronize()
+        return y.cpu().numpy()
+
+    got = run(max(lengths))
+    tol = 1e-5 if dtype == inputs.F32 else 2e-2
+    ref = orc.forward_inputs(inp, gate=not fl & G.NO_GATE, conv=not fl & G.NO_CONV,
+                             norm=not fl & G.NO_NORM)["y"]
+    close(got, ref, tol, "y")
+    close(run(1 << 20), ref, tol, "y, three launches")
+    # an understated bound only chooses the kernels: the same bits
+    assert (run(1) == got).all()
+
+
+@pytest.mark.parametrize("d,dtype", [(64, inputs.BF16), (32, inputs.F32)])
+def test_short_forward_dense(G, dev, orc, d, dtype):
+    say("short forward, dense", d, dtype)
+    for n in (1, 33, 200):
+        inp = inputs.make_inputs(small("b8_n2048_d64", batch=3, heads=2, seqlen=n, head_dim=d, dtype=dtype,
+                                       seed=54))
+        t = inputs.device_tensors(inp, dev)
+        y = G.forward(t["q"], t["k"], t["v"], t["a"], t["r"], t["conv_w"], t["gamma"], eps=inp.eps)
+        torch.cuda.synchronize()
+        close(y.cpu().numpy(), orc.forward_inputs(inp)["y"], 1e-5 if dtype == inputs.F32 else 2e-2, "y")
