@@ -30,7 +30,7 @@
 #include "gbla_device.h"
 #include "gbla_ext.h"
 #include "gbla_plan.h"
-#include "gbla_rows.h"
+#include "gbla_split.h"
 
 namespace gbla {
 namespace {
@@ -42,6 +42,12 @@ __device__ __forceinline__ float act<float>(const float* p, int64_t i) { return 
 template <>
 __device__ __forceinline__ float act<uint16_t>(const uint16_t* p, int64_t i) {
   return __uint_as_float((uint32_t)p[i] << 16);
+}
+
+// Sum over the four lane groups (the lanes n, n + 16, n + 32, n + 48).
+__device__ __forceinline__ float sum_groups(float x) {
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
 }
 
 __device__ __forceinline__ float phi_f(float u) { return u > 0.0f ? u + 1.0f : expf(u); }
@@ -66,7 +72,7 @@ __device__ __forceinline__ float rsqrt_nr(float x) {
 }
 __device__ __forceinline__ float dphi_f(float u) { return u > 0.0f ? 1.0f : expf(u); }
 
-constexpr int kBwdUnit = 512;  // tokens of the channel-layout kernels' units, at most
+constexpr int kBwdUnit = 512;  // tokens of the split-product kernels' units, at most
 
 template <int D>
 struct BW {
@@ -265,7 +271,7 @@ bwd_query_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ rin,
         qt[cc] = acc;
         qh[cc] = phi_f(acc);
       }
-      wave_lds_sync();
+      wave_fence();
       // num and den (z dotted with Qh over the wave)
       float num[CPL], zd = 0.0f;
 #pragma unroll
@@ -326,7 +332,7 @@ bwd_query_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ rin,
         if (e < D) dn_b[slot][e] = dnum[cc];
       }
       if (lane == 0) dd_b[slot] = dden;
-      wave_lds_sync();
+      wave_fence();
       // dQh[c] = sum_e S[c][e] dnum[e] + z[c] dden (lane owns c)
 #pragma unroll
       for (int cc = 0; cc < CPL; ++cc) {
@@ -451,7 +457,7 @@ bwd_key_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
 
   for (int64_t j = t0 + wave; j < t1; j += C::kWaves) {
     const int64_t row = base_row + j;
-    wave_lds_sync();  // the previous token's reads of vb, pb are done
+    wave_fence();  // the previous token's reads of vb, pb are done
     float kt[CPL], pv[CPL];
 #pragma unroll
     for (int cc = 0; cc < CPL; ++cc) {
@@ -472,7 +478,7 @@ bwd_key_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
       kt[cc] = ka;
       pv[cc] = phi_f(ka);
     }
-    wave_lds_sync();
+    wave_fence();
     const float alog = ain ? act<T>(ain, row) : 0.0f;
     const float gj = M == -INFINITY ? 0.0f : expf(alog - M) * invZ;
     // t[c] = sum_e dS[c][e] vt[e] + dz[c]; dkt = g t phi'(kt); dg = P . t
@@ -625,146 +631,181 @@ bwd_param_kernel(Plan P, const int32_t* __restrict__ cu, const float* __restrict
 }
 
 // ===========================================================================
-// Channel-layout path (gbla_rows.h): every head dim, slices below 2^31 bytes.
+// Split-product path (gbla_split.h): every head dim, slices below 2^31 bytes.
 //
-// Every contraction runs on v_mfma_f32_16x16x4_f32: fp32 operands, exact
-// products, fp32 accumulation, so the results carry fp32 rounding only (the
-// gradients cancel strongly -- dQh = S dnum + z dden, t = dS vt + dz -- and
-// a two-way bf16 split of the operands would show through that cancellation).
+// The gradients cancel strongly (dQh = S dnum + z dden, t = dS vt + dz), so the
+// products carry fp32 operands to fp32 accuracy: a two-way bf16 split of the
+// operands would show through that cancellation, the three-way one does not.
 //
-// The conv's transpose is fused into the two passes.  A wave walks its
-// contiguous quarter of the unit from its last tile to its first, so the three
-// later tokens that a tile's dx needs are at hand: the next lane group's rows,
-// or, for the last group, the first rows of the tile done before (LDS).  At
-// the wave's own end those rows belong to another wave or unit: its last three
-// tokens' dx are stored without them, every wave leaves the gradients of its
+// The conv's transpose is fused into the two passes: a unit is walked from its
+// last tile to its first, so the three later tokens that a tile's dx needs are
+// at hand.  At the unit's end those belong to the next unit: its last three
+// tokens' dx are stored without them, every unit leaves the gradients of its
 // first three convolved tokens in an edge buffer, and bwd_finish_kernel adds
-// the missing products.  A separate conv pass over dqt, dkt, dvt in memory
-// cost 1,920 bytes a token and head at d = 64, 92 of 321 us at n = 32768.
+// the missing products.
 //
-// Measured (query + key + conv of the kernels that these replaced, against
-// query + dsum + key): n = 32768, H = 8, d = 64 bf16 280 -> 165 us; 57,511
-// packed tokens, H = 8, d = 128 bf16 1810 -> 1250 us.
+// Bound: the waves of a workgroup meet at each tile's barriers, so the tile's
+// LDS reads (every wave reads all channels' planes), products and vector work
+// follow one another with two waves on a SIMD.  Measured, state / query / key,
+// against the fp32-product kernels with a conv pass of their own that these
+// replaced (n = 32768, H = 8, d = 64 bf16: 52 / 107 / 71 + conv 92 us; 57,511
+// packed tokens, H = 8, d = 128: 405 / 681 + 330 for dS / 440 + conv 345): 33 /
+// 84 / 57 and 125 / 440 / 281 us.
 // ===========================================================================
 
-// Rows of the tile's dx: dx_m = sum_t w_t dxt_{m+3-t}, and the tap sums
-// dw_t += dxt_i x_{i-3+t}.  d: dxt of the tile (channel layout), x: its
-// windows; stage: the wave's LDS area; later: [3][D] floats
-// of LDS, dxt of the three tokens after the tile on entry, of its first three
-// tokens on return.  dx of token tile + 4 g + i is stored at out row off + i.
-template <typename T, int D, typename Taps>
-__device__ __forceinline__ void conv_back(const float (*d)[4], const Window<T, D>& x,
-                                          const Taps& taps, float* stage, float* later,
-                                          __amdgpu_buffer_rsrc_t out, uint32_t off, int lane,
-                                          float (*dw)[4]) {
-  using C = CL<D>;
-  const int n = lane & 15, g = lane >> 4;
-#pragma unroll
-  for (int k = 0; k < C::NV; ++k) {
-    wave_lds_sync();
-#pragma unroll
-    for (int i = 0; i < 3; ++i) put_vec<D>(stage + (4 * g + i) * C::kPitch + C::V * n, d, k, i);
-    wave_lds_sync();
-    const float* src = g < 3 ? stage + 4 * (g + 1) * C::kPitch : later + k * 16 * C::V;
-    const int pitch = g < 3 ? C::kPitch : D;
-    float nx[3][C::V];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) get_vec<D>(src + i * pitch + C::V * n, nx[i]);
-    wave_lds_sync();
-    if (g == 0) {
-#pragma unroll
-      for (int i = 0; i < 3; ++i) put_vec<D>(later + i * D + k * 16 * C::V + C::V * n, d, k, i);
-    }
-    float y[C::V][4];
-#pragma unroll
-    for (int j = 0; j < C::V; ++j) {
-      const int b = k * C::V + j;
-      const f32x4_t w = taps(b);
-      const float dd[7] = {d[b][0], d[b][1], d[b][2], d[b][3], nx[0][j], nx[1][j], nx[2][j]};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float acc = w[3] * dd[i];
-        acc = fmaf(w[2], dd[i + 1], acc);
-        acc = fmaf(w[1], dd[i + 2], acc);
-        y[j][i] = fmaf(w[0], dd[i + 3], acc);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) dw[b][t] = fmaf(dd[i], x.x[i + t].at(b), dw[b][t]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t o = off + (uint32_t)(i * D * 4 + k * 16 * C::V * 4);
-      if constexpr (C::V == 4) {
-        const f32x4_t v = {y[0][i], y[1][i], y[2][i], y[3][i]};
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), out, o, 0, 0);
-      } else {
-        const f32x2_t v = {y[0][i], y[1][i]};
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), out, o, 0, 0);
-      }
-    }
-  }
-}
-
-// Writes a unit's tap-gradient partial [D][4] from the lanes' sums (every
-// thread calls; red: 4 x D f32x4 of LDS).
-template <int D>
-__device__ __forceinline__ void sum_taps(const float (*dw)[4], f32x4_t (*red)[D], float* __restrict__ dst) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
-#pragma unroll
-  for (int b = 0; b < CL<D>::NMB; ++b) {
-    f32x4_t s;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) s[t] = sum_groups(dw[b][t]);
-    if (g == 0) red[wave][slot_chan<D>(b, n)] = s;
-  }
-  __syncthreads();
-  if (threadIdx.x < D) {
-    const int x = threadIdx.x;
-    *reinterpret_cast<f32x4_t*>(dst + 4 * x) = (red[0][x] + red[1][x]) + (red[2][x] + red[3][x]);
-  }
-  __syncthreads();
-}
-
-// Edge rows of the wave of a unit: dxt of the wave's first three tokens.
-template <int D>
-__device__ __forceinline__ size_t edge_off(const Plan& P, int tensor, int h, int unit, int wave) {
-  return ((((size_t)tensor * P.heads + h) * P.units + unit) * 4 + wave) * (3 * D);
-}
-template <int D>
-__device__ __forceinline__ void store_edge(const float* later, float* __restrict__ dst, int lane) {
-  for (int x = lane; x < 3 * D; x += 64) dst[x] = later[x];
-}
-
-// ---------------------------------------------------------------------------
-// Query pass: grid (units, H).
-// ---------------------------------------------------------------------------
-// kDS: the unit's dS partial is summed here (d <= 64).  At d = 128 its 256
-// accumulators leave too few registers for the rest (the compiler then moved
-// and spilled some 900 of them a tile: 1207 us against 677 for this and
-// bwd_dsum_rows_kernel together, 16 sequences of 57,511 tokens, H = 8), so this
-// kernel writes dnum (to dnum_out, in the layout of dy) for that one.
-template <typename T, int D, bool kNorm, bool kDS>
-__global__ void __launch_bounds__(kThreads, D >= 128 ? 1 : 2)
-bwd_query_rows_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ rin,
-                      const float* __restrict__ dy, const float* __restrict__ conv_w,
-                      const float* __restrict__ gamma, const int32_t* __restrict__ cu,
-                      const float* __restrict__ Sg, const float* __restrict__ zg,
-                      float* __restrict__ dq, float* __restrict__ dr, float* __restrict__ dsp,
-                      float* __restrict__ dgp, float* __restrict__ dcp, float* __restrict__ edge,
-                      float* __restrict__ dnum_out) {
-  using C = CL<D>;
-  constexpr int NMB = C::NMB;
-  __shared__ f32x4_t f1[C::kFrag];  // num: B[c][e] = S[c][e]; later the waves' sums
-  __shared__ f32x4_t f2[C::kFrag];  // dQh: B[e][c] = S'[c][e]
-  __shared__ __attribute__((aligned(16))) float stg[4][C::kStage];
-  __shared__ __attribute__((aligned(16))) float later[4][3 * D];
-  __shared__ f32x4_t tq[D];
-  __shared__ __attribute__((aligned(16))) float zs[D], gs[D], ms[D];  // by channel
+// State of a unit with fp32-accurate products: the record [S_p | z_p | m_p |
+// l_p].  Grid (units, H).
+template <typename T, int D>
+__global__ void __launch_bounds__(SP<D>::NT, 2)
+bwd_state_split_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
+                       const T* __restrict__ ain, const float* __restrict__ conv_w,
+                       const int32_t* __restrict__ cu, float* __restrict__ partials) {
+  using C = SP<D>;
+  constexpr int NW = C::NW, NT = C::NT;
+  // value planes of two steps, token 8 g + j at position 8 g + j
+  __shared__ __attribute__((aligned(16))) unsigned char pv[2][C::kOperand];
+  __shared__ __attribute__((aligned(16))) float wts[kBwdUnit];  // gate weights
+  __shared__ float red[NW];
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.y, unit = blockIdx.x;
   int s, chunk;
-  if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
+  if (!unit_of<NT>(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
+  s = __builtin_amdgcn_readfirstlane(s);
+  chunk = __builtin_amdgcn_readfirstlane(chunk);
+  int64_t len, base_row;
+  seq_geometry(P, cu, s, h, &len, &base_row);
+  const int t0 = chunk * P.chunk;
+  const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
+  const uint32_t bytes = (uint32_t)len * (uint32_t)(D * sizeof(T));
+  const __amdgpu_buffer_rsrc_t rk = make_rsrc(kin + base_row * D, bytes);
+  const __amdgpu_buffer_rsrc_t rv = make_rsrc(vin + base_row * D, bytes);
+  const int c = 16 * wave + n;
+  Column<T, D> nk, nv;
+  nk.load(rk, t0 + 8 * g, c);
+  nv.load(rv, t0 + 8 * g, c);
+  float wk[4], wv[4];
+  load_taps4(conv_w, P.heads, h, 1, D, P.W, c, wk);
+  load_taps4(conv_w, P.heads, h, 2, D, P.W, c, wv);
+  float ml = -INFINITY;
+  for (int j = tid; j < t1 - t0; j += NT) {
+    const float a = logit<T>(ain, base_row + t0 + j);
+    wts[j] = a;
+    ml = fmaxf(ml, a);
+  }
+  const float m = block_max<NT>(ml, red);
+  float lacc = 0.0f;
+  for (int j = tid; j < (t1 - t0 + 31) / 32 * 32; j += NT) {
+    float w = 0.0f;
+    if (j < t1 - t0) w = m == -INFINITY ? 0.0f : __expf(wts[j] - m);
+    wts[j] = j & 32 ? -w : w;  // every second tile negated
+    lacc += w;
+  }
+  __syncthreads();
+  f32x4_t acc[NW];
+#pragma unroll
+  for (int b = 0; b < NW; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+  float z = 0.0f;
+  int par = 0;
+  float sign = 1.0f;
+  for (int b0 = t0; b0 < t1; b0 += 32, par ^= 1, sign = -sign) {
+    float kt[8], vt[8];
+    nv.conv(wv, vt);
+    nk.conv(wk, kt);
+    nk.load(rk, b0 + 32 + 8 * g, c);  // past the slice they read 0; unused
+    nv.load(rv, b0 + 32 + 8 * g, c);
+    u32x4_t A[3];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      uint32_t x0, x1, x2;
+      split3(vt[2 * p], vt[2 * p + 1], x0, x1, x2);
+      A[0][p] = x0;
+      A[1][p] = x1;
+      A[2][p] = x2;
+    }
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+      *reinterpret_cast<u32x4_t*>(pv[par] + x * C::kPlane + plane_unit(c, g)) = A[x];
+    const f32x4_t wa = *reinterpret_cast<const f32x4_t*>(&wts[b0 - t0 + 8 * g]);
+    const f32x4_t wb = *reinterpret_cast<const f32x4_t*>(&wts[b0 - t0 + 8 * g + 4]);
+    float zt = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      kt[j] = (j < 4 ? wa[j & 3] : wb[j & 3]) * phi_fast(kt[j]);
+      zt += kt[j];
+    }
+    z = fmaf(sign, zt, z);  // a tile at a time, as all sums over a unit
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      uint32_t x0, x1, x2;
+      split3(kt[2 * p], kt[2 * p + 1], x0, x1, x2);
+      A[0][p] = x0;
+      A[1][p] = x1;
+      A[2][p] = x2;
+    }
+    __syncthreads();  // the planes are whole (and the step before's are read)
+#pragma unroll
+    for (int b = 0; b < NW; ++b) {
+      u32x4_t B[3];
+      row_operand<D>(pv[par], 16 * b + n, g, B);
+      const f32x4_t y = step_product(A, B);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[b][i] = fmaf(sign, y[i], acc[b][i]);
+    }
+  }
+  float* rec = partials + ((size_t)h * P.units + unit) * P.rec_floats;
+#pragma unroll
+  for (int b = 0; b < NW; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rec[(16 * wave + 4 * g + i) * D + 16 * b + n] = acc[b][i];
+  z = sum_groups(z);
+  if (g == 0) rec[D * D + c] = z;
+  lacc = wave_sum(lacc);
+  __syncthreads();  // red's maxima are read
+  if (lane == 0) red[wave] = lacc;
+  __syncthreads();
+  if (tid == 0) {
+    float l = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) l += red[w];
+    rec[D * D + D] = m;
+    rec[D * D + D + 1] = l;
+  }
+}
+
+// Edge rows of a unit: dxt of its first three tokens.
+template <int D>
+__device__ __forceinline__ size_t edge_off(const Plan& P, int tensor, int h, int unit) {
+  return (((size_t)tensor * P.heads + h) * P.units + unit) * (3 * D);
+}
+
+// ---------------------------------------------------------------------------
+// Query pass: grid (units, H).  Three barriers a tile: the planes of Qh and the
+// denominators' parts; the norm's sums; the planes of dnum.
+// ---------------------------------------------------------------------------
+template <typename T, int D, bool kNorm>
+__global__ void __launch_bounds__(SP<D>::NT, 2)
+bwd_query_split_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ rin,
+                       const float* __restrict__ dy, const float* __restrict__ conv_w,
+                       const float* __restrict__ gamma, const int32_t* __restrict__ cu,
+                       const float* __restrict__ Sg, const float* __restrict__ zg,
+                       float* __restrict__ dq, float* __restrict__ dr, float* __restrict__ dsp,
+                       float* __restrict__ dgp, float* __restrict__ dcp, float* __restrict__ edge) {
+  using C = SP<D>;
+  constexpr int NW = C::NW, NT = C::NT, KS = C::KS;
+  __shared__ __attribute__((aligned(16))) unsigned char pq[C::kOperand];  // Qh
+  __shared__ __attribute__((aligned(16))) unsigned char pd[C::kOperand];  // dnum
+  __shared__ __attribute__((aligned(16))) float part[4][NW][32];  // the waves' channel sums
+  __shared__ __attribute__((aligned(16))) float dist[NW][5][32];  // a wave's token values
+  __shared__ __attribute__((aligned(16))) float ms[D];
+  // at d = 128 two parts of one operand's columns leave the registers
+  constexpr bool kLdsCols = D >= 128;
+  __shared__ u32x4_t cols[kLdsCols ? 2 * KS * NT : 1];
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = blockIdx.y, unit = blockIdx.x;
+  int s, chunk;
+  if (!unit_of<NT>(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
   s = __builtin_amdgcn_readfirstlane(s);
   chunk = __builtin_amdgcn_readfirstlane(chunk);
   int64_t len, base_row;
@@ -780,292 +821,265 @@ bwd_query_rows_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ r
   const __amdgpu_buffer_rsrc_t rdq = make_rsrc(dq + base_row * D, rows * 4u);
   const __amdgpu_buffer_rsrc_t rdr =
       kNorm ? make_rsrc(dr + base_row * D, rows * 4u) : make_rsrc(dq, 0u);
-  const __amdgpu_buffer_rsrc_t rdn =
-      kDS ? make_rsrc(dq, 0u) : make_rsrc(dnum_out + base_row * D, rows * 4u);
-  // the wave's quarter of the unit, in whole tiles
-  const int q4 = quarter_tokens(t1 - t0);
-  const int w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
-  int b0 = w0 + (w1 > w0 ? (w1 - w0 - 1) / 16 * 16 : 0);  // the wave's last tile
-  Window<T, D> nq;
-  nq.load(rq, b0 + 4 * g, n);
+  const int c = 16 * wave + n;
+  int b0 = t0 + (t1 > t0 ? (t1 - t0 - 1) / 32 * 32 : 0);  // the last tile
+  Column<T, D> nq;
+  uint32_t nr[8], ndy[8];
+  nq.load(rq, b0 + 8 * g, c);
+  auto issue_rdy = [&](int tok) {
+    const uint32_t e = (uint32_t)(tok * D + c);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if constexpr (kNorm) nr[j] = load_elem<T>(rr, (e + (uint32_t)(j * D)) * (uint32_t)sizeof(T));
+      ndy[j] = load_elem<float>(rdy, (e + (uint32_t)(j * D)) * 4u);
+    }
+  };
+  issue_rdy(b0 + 8 * g);
 
   const size_t sh = (size_t)s * P.heads + h;
   const float* S = Sg + sh * D * D;
-  Frags<D> fa, fb;
-  fb.load_transposed(S);  // S[c][e .. e + 3]
-  fa.load(S);
-  stage_taps<D>(conv_w, P.heads, h, 0, P.W, tq);
-  if (tid < D) {
-    zs[tid] = zg[sh * D + tid];
-    gs[tid] = kNorm ? gamma[(size_t)h * D + tid] : 1.0f;
-  }
-  for (int x = lane; x < 3 * D; x += 64) later[wave][x] = 0.0f;
-  // dQh = S dnum + z dden is formed as S' dnum + z (dden + m . dnum) with
-  // S' = S - z m^T, m = (sum_c S[c][.]) / (sum_c z[c]) (the gate-weighted
+  const float* zrow = zg + sh * D;
+  float w4[4];
+  load_taps4(conv_w, P.heads, h, 0, D, P.W, c, w4);
+  const float z = zrow[c], gm = kNorm ? gamma[(size_t)h * D + c] : 1.0f;
+  // The wave's columns: f1 of num (X[k][e] = S[k][e]), f2 of dQh (X[k][c] =
+  // S'[c][k]).  dQh = S dnum + z dden is formed as S' dnum + z (dden + m . dnum)
+  // with S' = S - z m^T, m = (sum_c S[c][.]) / (sum_c z[c]) (the gate-weighted
   // mean value row): the same quantity, but without the cancellation between
   // the two terms when the value rows share a mean (then S dnum ~ z (m . dnum)
   // and o ~ m, and the no-norm dden + m . dnum is formed as
   // -((o - m) . dy) / den directly).
-  // Column sums of S from fb: a wave's vectors have the K blocks kq = wave +
-  // 4 j alone (d = 32: waves w and w + 2 share block w); sixteen lanes of a
-  // vector hold the block's columns c.
-  constexpr int kQ = NMB > 4 ? NMB / 4 : 1, kShare = NMB < 4 ? 4 / NMB : 1;
-  float* part = &stg[0][0];  // [kShare][D]
+  Columns<D> f1;
+  typename std::conditional<kLdsCols, ColumnsLds<D>, Columns<D>>::type f2;
+  if constexpr (kLdsCols) f2.lds = cols;
+  float m;
+  {
+    float x[KS][8], y[KS][8], cs = 0.0f, zs = 0.0f;
 #pragma unroll
-  for (int j = 0; j < kQ; ++j)
+    for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float cs = 0.0f;
+      for (int i = 0; i < 8; ++i) x[ks][i] = S[(size_t)(32 * ks + 8 * g + i) * D + c];
+      const f32x4_t y0 = *reinterpret_cast<const f32x4_t*>(S + (size_t)c * D + 32 * ks + 8 * g);
+      const f32x4_t y1 = *reinterpret_cast<const f32x4_t*>(S + (size_t)c * D + 32 * ks + 8 * g + 4);
 #pragma unroll
-      for (int u = j; u < Frags<D>::kPer; u += kQ) cs += fb.v[u][i];
-      cs = sum_row16(cs);
-      if (n == 0) part[(wave / NMB) * D + fb.k0(j) + i] = cs;
+      for (int i = 0; i < 4; ++i) {
+        y[ks][i] = y0[i];
+        y[ks][4 + i] = y1[i];
+      }
     }
-  __syncthreads();
-  if (tid < D) {
-    float cs = part[tid], zsum = 0.0f;
-    if constexpr (kShare == 2) cs += part[D + tid];
-    for (int c = 0; c < D; ++c) zsum += zs[c];
-    ms[tid] = zsum > 0.0f ? cs / zsum : 0.0f;
+    for (int k = lane; k < D; k += 64) zs += zrow[k];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) cs += x[ks][i];
+    cs = sum_groups(cs);
+    zs = wave_sum(zs);
+    m = zs > 0.0f ? cs / zs : 0.0f;
+    if (g == 0) ms[c] = m;
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) y[ks][i] = fmaf(-z, ms[32 * ks + 8 * g + i], y[ks][i]);
+      f1.set(ks, x[ks]);
+      f2.set(ks, y[ks]);
+    }
   }
-  __syncthreads();
+  f32x4_t acc[NW];  // dS rows 16 wave + 4 g + i, columns 16 b + n
 #pragma unroll
-  for (int u = 0; u < Frags<D>::kPer; ++u) {
-    const float z = zs[fb.col(u)];
-    const f32x4_t m = *reinterpret_cast<const f32x4_t*>(&ms[fb.k0(u)]);
+  for (int b = 0; b < NW; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+  float dzacc = 0.0f, dgacc = 0.0f, dw[4] = {0.0f, 0.0f, 0.0f, 0.0f}, prev[3] = {0.0f, 0.0f, 0.0f};
+  const int tok32 = lane & 31;  // the token of a lane in the channel sums
+  // the waves' sums of one quantity for the lane's token
+  auto total = [&](int q) {
+    float x = part[q][0][tok32];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) fb.v[u][i] = fmaf(-z, m[i], fb.v[u][i]);
-  }
-  fa.put(f1);
-  fb.put(f2);
-  f32x4_t acc3[kDS ? C::kBlocks : 1];
+    for (int w = 1; w < NW; ++w) x += part[q][w][tok32];
+    return x;
+  };
+  auto get8 = [&](int q, float* v) {
+    const f32x4_t a = *reinterpret_cast<const f32x4_t*>(&dist[wave][q][8 * g]);
+    const f32x4_t b = *reinterpret_cast<const f32x4_t*>(&dist[wave][q][8 * g + 4]);
 #pragma unroll
-  for (int k = 0; k < (kDS ? C::kBlocks : 1); ++k) acc3[k] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-  float dzacc[NMB], dgacc[NMB], dw[NMB][4];
-#pragma unroll
-  for (int b = 0; b < NMB; ++b) {
-    dzacc[b] = dgacc[b] = 0.0f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) dw[b][t] = 0.0f;
-  }
-  __syncthreads();
+    for (int j = 0; j < 4; ++j) {
+      v[j] = a[j];
+      v[4 + j] = b[j];
+    }
+  };
+  const int slot = 8 * g + (n >> 1);  // the token whose sum scatter_sum8 leaves here
+  auto put_part = [&](int q, const float* v) {
+    const float x = scatter_sum8(v, n);
+    if (!(n & 1)) part[q][wave][slot] = x;
+  };
 
-  for (; b0 >= w0 && w1 > w0; b0 -= 16) {
-    float qh[NMB][4], o[NMB][4], dn[NMB][4];
-    // operands and taps are re-read from LDS each tile, not held in registers
-    __asm__ volatile("" ::: "memory");
-    const Window<T, D> xq = nq;
-    const int tb = b0 + 4 * g;
-    Row<T, D> rw[4];
-    Row<float, D> dyw[4];
+  float sign = 1.0f;
+  for (; b0 >= t0 && t1 > t0; b0 -= 32, sign = -sign) {
+    const Column<T, D> xq = nq;
+    nq.load(rq, b0 - 32 + 8 * g, c);  // the tile before (before the slice: reads 0, unused)
+    float qh[8], o[8], v[8];
+    xq.conv(w4, qh);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      qh[j] = phi_fast(qh[j]);
+      v[j] = qh[j] * z;
+    }
+    put_part(0, v);
+    put_planes<D>(pq, c, g, qh);
+    __syncthreads();
+    // num = S^T Qh, den = z . Qh
+    const float inv = 1.0f / total(0);
+    if (lane < 32) dist[wave][0][tok32] = inv;
+    contract_planes<D>(pq, f1, lane, o);
+    float dn[8], dd = 0.0f;  // dd: dden of token tok32
+    float t1v[8], t2v[8];  // dr and dgamma's terms but for the factor oh
+    if constexpr (kNorm) {  // what the products do not enter, beside them
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float r = widen<T>(nr[j]), d = __uint_as_float(ndy[j]), sig = sigmoid_fast(r);
+        t1v[j] = d * (r * sig);
+        dn[j] = t1v[j] * gm;  // doh
+        t2v[j] = d * gm * sig * (1.0f + r * (1.0f - sig));
+      }
+      issue_rdy(b0 - 32 + 8 * g);
+    }
+    wave_fence();
+    get8(0, v);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j] *= v[j];
+    const uint32_t off = (uint32_t)((b0 + 8 * g) * D + c) * 4u;
     if constexpr (kNorm) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) rw[i].load(rr, row_off<T, D>(tb, n) + (uint32_t)(i * D * sizeof(T)));
-    }
+      for (int j = 0; j < 8; ++j) v[j] = o[j] * o[j];
+      put_part(1, v);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) dyw[i].load(rdy, row_off<float, D>(tb, n) + (uint32_t)(i * D * 4));
-    xq.conv(LdsTaps<D>{tq, n}, qh);
-    nq.load(rq, b0 - 16 + 4 * g, n);  // the tile before (before the slice: reads 0, unused)
-    float den[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int j = 0; j < 8; ++j) v[j] = dn[j] * o[j];
+      put_part(2, v);
+      __syncthreads();
+      // |o|^2 in the lower lanes, doh . o in the upper, then both in both
+      const float x = total(lane < 32 ? 1 : 2), y = __shfl_xor(x, 32);
+      const float s2 = lane < 32 ? x : y, s1 = lane < 32 ? y : x;
+      const float rs = rsqrt_nr(s2 * (1.0f / D) + P.eps);
+      // do . o = rs s1 (1 - rs^2 |o|^2 / d) = eps rs^3 s1 exactly (rs^-2 = |o|^2/d + eps):
+      // the RMSNorm leaves almost nothing along o, and summing do . o would
+      // return mostly the rounding of its terms.
+      dd = -P.eps * rs * rs * rs * s1 * inv;
+      dist[wave][lane < 32 ? 0 : 1][tok32] = lane < 32 ? rs : rs * inv;
+      dist[wave][lane < 32 ? 2 : 3][tok32] = lane < 32 ? rs * rs * rs * (1.0f / D) * s1 * inv : dd;
+      wave_fence();
+      get8(0, v);
+      float dgt = 0.0f;
 #pragma unroll
-    for (int b = 0; b < NMB; ++b) {
-      const float z = zs[slot_chan<D>(b, n)];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        qh[b][i] = phi_fast(qh[b][i]);
-        den[i] = fmaf(qh[b][i], z, den[i]);
+      for (int j = 0; j < 8; ++j) {
+        const float oh = v[j] * o[j];
+        dgt = fmaf(oh, t1v[j], dgt);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(oh * t2v[j]), rdr, off + (uint32_t)(j * D * 4), 0, 0);
       }
-    }
-    // num = S^T Qh, den = z . Qh
-    {
-      f32x4_t acc[NMB];
+      dgacc += dgt;
+      get8(1, v);
 #pragma unroll
-      for (int b = 0; b < NMB; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-      contract_rows<D>(qh, stg[wave], f1, lane, acc);
+      for (int j = 0; j < 8; ++j) dn[j] *= v[j];
+      get8(2, v);
 #pragma unroll
-      for (int b = 0; b < NMB; ++b)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[b][i] = acc[b][i];
-    }
-    float dden[4], dcen[4];  // dcen = dden + m . dnum
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float inv_den = 1.0f / sum_row16(den[i]);
-      float ss = 0.0f;
-#pragma unroll
-      for (int b = 0; b < NMB; ++b) {
-        o[b][i] *= inv_den;
-        ss = fmaf(o[b][i], o[b][i], ss);
+      for (int j = 0; j < 8; ++j) {
+        dn[j] = fmaf(-v[j], o[j], dn[j]);
+        v[j] = m * dn[j];
       }
-      if constexpr (kNorm) {
-        const float rs = rsqrt_nr(sum_row16(ss) * (1.0f / D) + P.eps);
-        float s1 = 0.0f, drv[NMB][4];
+      put_part(3, v);
+    } else {  // y = o: do = dy
 #pragma unroll
-        for (int b = 0; b < NMB; ++b) {
-          const float r = rw[i].at(b), d = dyw[i].at(b), gm = gs[slot_chan<D>(b, n)];
-          const float sig = sigmoid_fast(r), silu = r * sig;
-          const float dyoh = d * (o[b][i] * rs);
-          dn[b][i] = d * gm * silu;  // doh
-          dgacc[b] = fmaf(dyoh, silu, dgacc[b]);
-          drv[b][0] = dyoh * gm * sig * (1.0f + r * (1.0f - sig));
-          s1 = fmaf(dn[b][i], o[b][i], s1);
-        }
-        store_row<D>(rdr, row_off<float, D>(tb, n) + (uint32_t)(i * D * 4), drv, 0);
-        s1 = sum_row16(s1);
-        const float c3 = rs * rs * rs / D * s1;
-        // do . o = rs s1 (1 - rs^2 |o|^2 / d) = eps rs^3 s1 exactly (rs^-2 = |o|^2/d + eps):
-        // the RMSNorm leaves almost nothing along o, and summing do . o would
-        // return mostly the rounding of its terms.
-        dden[i] = -P.eps * rs * rs * rs * s1 * inv_den;
-        float md = 0.0f;
-#pragma unroll
-        for (int b = 0; b < NMB; ++b) {
-          dn[b][i] = (rs * dn[b][i] - c3 * o[b][i]) * inv_den;
-          md = fmaf(ms[slot_chan<D>(b, n)], dn[b][i], md);
-        }
-        dcen[i] = dden[i] + sum_row16(md);
-      } else {  // y = o: do = dy
-        float s2 = 0.0f, s2c = 0.0f;
-#pragma unroll
-        for (int b = 0; b < NMB; ++b) {
-          const float d = dyw[i].at(b);
-          dn[b][i] = d * inv_den;
-          s2 = fmaf(d, o[b][i], s2);
-          s2c = fmaf(d, o[b][i] - ms[slot_chan<D>(b, n)], s2c);
-        }
-        dden[i] = -sum_row16(s2) * inv_den;
-        dcen[i] = -sum_row16(s2c) * inv_den;
+      for (int j = 0; j < 8; ++j) {
+        const float d = __uint_as_float(ndy[j]);
+        dn[j] = d * v[j];
+        v[j] = d * o[j];
+        o[j] = d * (o[j] - m);
       }
+      issue_rdy(b0 - 32 + 8 * g);
+      put_part(1, v);
+      put_part(2, o);
+      __syncthreads();
+      const float x = -total(lane < 32 ? 1 : 2);
+      dist[wave][lane < 32 ? 3 : 4][tok32] = x * inv;
+      wave_fence();
     }
-    // dS += Qh dnum^T; dQh = S' dnum + z (dden + m . dnum)
-    if constexpr (kDS) {
-      token_product<D>(qh, dn, acc3);
-    } else {
+    get8(3, v);  // dden
+    float dzt = 0.0f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        store_row<D>(rdn, row_off<float, D>(tb, n) + (uint32_t)(i * D * 4), dn, i);
+    for (int j = 0; j < 8; ++j) dzt = fmaf(qh[j], v[j], dzt);
+    dzacc += dzt;
+    put_planes<D>(pd, c, g, dn);
+    __syncthreads();
+    // dQh = S' dnum + z (dden + m . dnum); dS += Qh dnum^T
+    contract_planes<D>(pd, f2, lane, o);
+    // dden + m . dnum, the second from the products that dnum itself enters: m is
+    // close to o, dnum nearly orthogonal to it, and m . dnum as a difference of
+    // the sums m . doh and m . o left 1.4 times the error in dq
+    if constexpr (kNorm) {
+      if (lane < 32) dist[wave][4][tok32] = dd + total(3);
+      wave_fence();
     }
-    {
-      f32x4_t acc[NMB];
+    get8(4, v);
+    // phi'(u) = 1 for u > 0 and e^u = phi(u) <= 1 otherwise: min(phi(u), 1)
 #pragma unroll
-      for (int b = 0; b < NMB; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-      contract_rows<D>(dn, stg[wave], f2, lane, acc);
+    for (int j = 0; j < 8; ++j) o[j] = fmaf(z, v[j], o[j]) * fminf(qh[j], 1.0f);
+    conv_back8<T, D>(o, xq, w4, prev, lane, rdq, off, dw);
+    u32x4_t A[3];
+    row_operand<D>(pq, c, g, A);
+    const uint32_t flip = sign < 0.0f ? 0x80008000u : 0u;
 #pragma unroll
-      for (int b = 0; b < NMB; ++b) {
-        const float z = zs[slot_chan<D>(b, n)];
+    for (int x = 0; x < 3; ++x)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          // phi'(u) = 1 for u > 0 and e^u = phi(u) <= 1 otherwise: min(phi(u), 1)
-          o[b][i] = fmaf(z, dcen[i], acc[b][i]) * fminf(qh[b][i], 1.0f);
-          dzacc[b] = fmaf(qh[b][i], dden[i], dzacc[b]);
-        }
-      }
+      for (int p = 0; p < 4; ++p) A[x][p] ^= flip;
+#pragma unroll
+    for (int b = 0; b < NW; ++b) {
+      u32x4_t B[3];
+      row_operand<D>(pd, 16 * b + n, g, B);
+      const f32x4_t y = step_product(A, B);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[b][i] = fmaf(sign, y[i], acc[b][i]);
     }
-    conv_back<T, D>(o, xq, LdsTaps<D>{tq, n}, stg[wave], later[wave], rdq, row_off<float, D>(tb, n), lane, dw);
   }
 
-  wave_lds_sync();
-  store_edge<D>(later[wave], edge + edge_off<D>(P, 0, h, unit, wave), lane);
   const size_t ui = (size_t)h * P.units + unit;
   float* rec = dsp + ui * P.rec_floats;
-  __syncthreads();  // every wave is done with the operands
-  static_assert(2 * sizeof(f1) >= 2 * D * D * sizeof(float), "f1, f2 hold the waves' sums");
-  if constexpr (kDS) {
-    sum_waves<D>(acc3, reinterpret_cast<float*>(f1), reinterpret_cast<float*>(f2), rec);
-    __syncthreads();
+#pragma unroll
+  for (int b = 0; b < NW; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rec[(16 * wave + 4 * g + i) * D + 16 * b + n] = acc[b][i];
+  dzacc = sum_groups(dzacc);
+  dgacc = sum_groups(dgacc);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) dw[t] = sum_groups(dw[t]);
+  if (g == 0) {
+    rec[D * D + c] = dzacc;
+    dgp[ui * D + c] = dgacc;
+    *reinterpret_cast<f32x4_t*>(dcp + (ui * 3 + 0) * D * 4 + 4 * c) = (f32x4_t){dw[0], dw[1], dw[2], dw[3]};
+    float* e = edge + edge_off<D>(P, 0, h, unit) + c;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) e[i * D] = prev[i];
   }
-  sum_channels<D>(dzacc, reinterpret_cast<float(*)[D]>(f1), rec + D * D);
-  sum_channels<D>(dgacc, reinterpret_cast<float(*)[D]>(f1), dgp + ui * D);
-  sum_taps<D>(dw, reinterpret_cast<f32x4_t(*)[D]>(f1), dcp + (ui * 3 + 0) * D * 4);
 }
 
 // ---------------------------------------------------------------------------
-// dS of a unit from the query pass's dnum (d = 128): dS_p = sum_i Qh_i dnum_i^T
-// with Qh formed as the query pass forms it.  Writes the S part of the unit's
-// record; the query pass wrote its dz part.
+// Key pass: grid (units, H).  Two barriers a tile.
 // ---------------------------------------------------------------------------
 template <typename T, int D>
-__global__ void __launch_bounds__(kThreads, D >= 128 ? 1 : 2)
-bwd_dsum_rows_kernel(Plan P, const T* __restrict__ qin, const float* __restrict__ dnum,
-                     const float* __restrict__ conv_w, const int32_t* __restrict__ cu,
-                     float* __restrict__ dsp) {
-  using C = CL<D>;
-  constexpr int NMB = C::NMB;
-  __shared__ __attribute__((aligned(16))) float buf[2 * D * D];  // the waves' sums
-  __shared__ f32x4_t tq[D];
+__global__ void __launch_bounds__(SP<D>::NT, 2)
+bwd_key_split_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
+                     const T* __restrict__ ain, const float* __restrict__ conv_w,
+                     const int32_t* __restrict__ cu, const float* __restrict__ dSg,
+                     const float* __restrict__ mz, float* __restrict__ dk, float* __restrict__ dv,
+                     float* __restrict__ da, float* __restrict__ dcp, float* __restrict__ edge) {
+  using C = SP<D>;
+  constexpr int NW = C::NW, NT = C::NT, KS = C::KS;
+  __shared__ __attribute__((aligned(16))) unsigned char pv[C::kOperand];  // vt
+  __shared__ __attribute__((aligned(16))) unsigned char pk[C::kOperand];  // P = phi(kt)
+  __shared__ __attribute__((aligned(16))) float gt[kBwdUnit];  // gates, zero past the sequence end
+  __shared__ float part[NW][32];
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.y, unit = blockIdx.x;
   int s, chunk;
-  if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
-  s = __builtin_amdgcn_readfirstlane(s);
-  chunk = __builtin_amdgcn_readfirstlane(chunk);
-  int64_t len, base_row;
-  seq_geometry(P, cu, s, h, &len, &base_row);
-  const int t0 = chunk * P.chunk;
-  const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
-  const uint32_t rows = (uint32_t)len * D;
-  const __amdgpu_buffer_rsrc_t rq = make_rsrc(qin + base_row * D, rows * sizeof(T));
-  // dnum past the unit's end reads 0
-  const __amdgpu_buffer_rsrc_t rdn = make_rsrc(dnum + base_row * D, (uint32_t)t1 * (uint32_t)(D * 4));
-  const int q4 = quarter_tokens(t1 - t0);
-  const int w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
-  Window<T, D> nq;
-  Row<float, D> nd[4];
-  auto issue = [&](int b0) {
-    nq.load(rq, b0 + 4 * g, n);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) nd[i].load(rdn, row_off<float, D>(b0 + 4 * g, n) + (uint32_t)(i * D * 4));
-  };
-  issue(w0);
-  stage_taps<D>(conv_w, P.heads, h, 0, P.W, tq);
-  f32x4_t acc[C::kBlocks];
-#pragma unroll
-  for (int k = 0; k < C::kBlocks; ++k) acc[k] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-  __syncthreads();
-  for (int b0 = w0; b0 < w1; b0 += 16) {
-    float qh[NMB][4], dn[NMB][4];
-    __asm__ volatile("" ::: "memory");  // taps are re-read from LDS, not held
-    nq.conv(LdsTaps<D>{tq, n}, qh);
-#pragma unroll
-    for (int b = 0; b < NMB; ++b)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        qh[b][i] = phi_fast(qh[b][i]);
-        dn[b][i] = nd[i].at(b);
-      }
-    issue(b0 + 16);
-    token_product<D>(qh, dn, acc);
-  }
-  sum_waves<D>(acc, buf, buf + D * D, dsp + ((size_t)h * P.units + unit) * P.rec_floats);
-}
-
-// ---------------------------------------------------------------------------
-// Key pass: grid (units, H).
-// ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ void __launch_bounds__(kThreads, D >= 128 ? 1 : 2)
-bwd_key_rows_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
-                    const T* __restrict__ ain, const float* __restrict__ conv_w,
-                    const int32_t* __restrict__ cu, const float* __restrict__ dSg,
-                    const float* __restrict__ mz, float* __restrict__ dk, float* __restrict__ dv,
-                    float* __restrict__ da, float* __restrict__ dcp, float* __restrict__ edge) {
-  using C = CL<D>;
-  constexpr int NMB = C::NMB;
-  __shared__ f32x4_t f1[C::kFrag];  // t = dS vt: B[e][c] = dS[c][e]
-  __shared__ f32x4_t f2[C::kFrag];  // dvt = dS^T P: B[c][e] = dS[c][e]
-  __shared__ __attribute__((aligned(16))) float stg[4][C::kStage];
-  __shared__ __attribute__((aligned(16))) float later[4][2][3 * D];  // dkt, dvt
-  // gates of the unit's tokens, zero past the sequence end
-  __shared__ __attribute__((aligned(16))) float gt[kBwdUnit];
-  __shared__ float dzs[D];
-  constexpr bool kRegTaps = D >= 128;  // the operand layouts fill the LDS
-  __shared__ f32x4_t tk[kRegTaps ? 1 : D], tv[kRegTaps ? 1 : D];
-  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int h = blockIdx.y, unit = blockIdx.x;
-  int s, chunk;
-  if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
+  if (!unit_of<NT>(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
   s = __builtin_amdgcn_readfirstlane(s);
   chunk = __builtin_amdgcn_readfirstlane(chunk);
   int64_t len, base_row;
@@ -1080,110 +1094,115 @@ bwd_key_rows_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin
   // an absent da is not written (an empty range)
   const __amdgpu_buffer_rsrc_t rda =
       da ? make_rsrc(da + base_row, (uint32_t)t1 * 4u) : make_rsrc(dk, 0u);
-  const int q4 = quarter_tokens(t1 - t0);
-  const int w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
-  int b0 = w0 + (w1 > w0 ? (w1 - w0 - 1) / 16 * 16 : 0);  // the wave's last tile
-  Window<T, D> nk, nv;
-  nk.load(rk, b0 + 4 * g, n);
-  nv.load(rv, b0 + 4 * g, n);
-
+  const int c = 16 * wave + n;
+  int b0 = t0 + (t1 > t0 ? (t1 - t0 - 1) / 32 * 32 : 0);  // the last tile
+  Column<T, D> nk, nv;
+  nk.load(rk, b0 + 8 * g, c);
+  nv.load(rv, b0 + 8 * g, c);
   const size_t sh = (size_t)s * P.heads + h;
   const float* dS = dSg + sh * (D * D + D);
-  Frags<D> fa, fb;
-  fa.load_transposed(dS);
-  fb.load(dS);
-  using Taps = typename std::conditional<kRegTaps, RegTaps<D>, LdsTaps<D>>::type;
-  Taps wk, wv;
-  if constexpr (kRegTaps) {
-    wk.load(conv_w, P.heads, h, 1, P.W, n);
-    wv.load(conv_w, P.heads, h, 2, P.W, n);
-  } else {
-    stage_taps<D>(conv_w, P.heads, h, 1, P.W, tk);
-    stage_taps<D>(conv_w, P.heads, h, 2, P.W, tv);
-    wk = LdsTaps<D>{tk, n};
-    wv = LdsTaps<D>{tv, n};
-  }
-  if (tid < D) dzs[tid] = dS[D * D + tid];
-  const float M = mz[2 * sh], Z = mz[2 * sh + 1];
-  const float invZ = Z > 0.0f ? 1.0f / Z : 0.0f;
-  for (int j = tid; j < 4 * q4; j += kThreads)
-    gt[j] = j < t1 - t0 ? __expf(logit<T>(ain, base_row + t0 + j) - M) * invZ : 0.0f;
-  for (int x = lane; x < 6 * D; x += 64) (&later[wave][0][0])[x] = 0.0f;
-  fa.put(f1);
-  fb.put(f2);
-  float dwk[NMB][4], dwv[NMB][4];
+  float wk[4], wv[4];
+  load_taps4(conv_w, P.heads, h, 1, D, P.W, c, wk);
+  load_taps4(conv_w, P.heads, h, 2, D, P.W, c, wv);
+  const float dz = dS[D * D + c];
+  Columns<D> f1, f2;  // t: X[e][c] = dS[c][e]; dvt: X[c][e] = dS[c][e]
+  {
+    float x[KS][8], y[KS][8];
 #pragma unroll
-  for (int b = 0; b < NMB; ++b)
+    for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) dwk[b][t] = dwv[b][t] = 0.0f;
-  __syncthreads();
-
-  for (; b0 >= w0 && w1 > w0; b0 -= 16) {
-    float pk[NMB][4], x[NMB][4];
-    __asm__ volatile("" ::: "memory");  // operands and taps are re-read from LDS
-    const Window<T, D> xk = nk, xv = nv;
-    const uint32_t off = row_off<float, D>(b0 + 4 * g, n);
-    xk.conv(wk, pk);
-    xv.conv(wv, x);
-    nk.load(rk, b0 - 16 + 4 * g, n);  // the tile before (before the slice: reads 0, unused)
-    nv.load(rv, b0 - 16 + 4 * g, n);
-    const f32x4_t gj = *reinterpret_cast<const f32x4_t*>(&gt[b0 - t0 + 4 * g]);
-    // t = dS vt + dz; dkt = g t phi'(kt); da = g (P . t)
-    {
-      f32x4_t acc[NMB];
-#pragma unroll
-      for (int b = 0; b < NMB; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-      contract_rows<D>(x, stg[wave], f1, lane, acc);
-      float dgl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int b = 0; b < NMB; ++b) {
-        const float dz = dzs[slot_chan<D>(b, n)];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float p = phi_fast(pk[b][i]), t = acc[b][i] + dz;
-          pk[b][i] = p;
-          x[b][i] = gj[i] * t * fminf(p, 1.0f);  // phi'(u) = min(phi(u), 1)
-          dgl[i] = fmaf(p, t, dgl[i]);
-        }
-      }
-      float dg = 0.0f;  // lane n < 4 writes token 4 g + n
+      for (int i = 0; i < 8; ++i) x[ks][i] = dS[(size_t)(32 * ks + 8 * g + i) * D + c];
+      const f32x4_t y0 = *reinterpret_cast<const f32x4_t*>(dS + (size_t)c * D + 32 * ks + 8 * g);
+      const f32x4_t y1 = *reinterpret_cast<const f32x4_t*>(dS + (size_t)c * D + 32 * ks + 8 * g + 4);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float v = gj[i] * sum_row16(dgl[i]);
-        dg = n == i ? v : dg;
+        y[ks][i] = y0[i];
+        y[ks][4 + i] = y1[i];
       }
-      if (n < 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, dg), rda,
-                                              (uint32_t)(b0 + 4 * g + n) * 4u, 0, 0);
     }
-    conv_back<T, D>(x, xk, wk, stg[wave], later[wave][0], rdk, off, lane, dwk);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      f1.set(ks, y[ks]);
+      f2.set(ks, x[ks]);
+    }
+  }
+  const float M = mz[2 * sh], Z = mz[2 * sh + 1];
+  const float invZ = Z > 0.0f ? 1.0f / Z : 0.0f;
+  for (int j = tid; j < (t1 - t0 + 31) / 32 * 32; j += NT)
+    gt[j] = j < t1 - t0 ? __expf(logit<T>(ain, base_row + t0 + j) - M) * invZ : 0.0f;
+  float dwk[4] = {0.0f, 0.0f, 0.0f, 0.0f}, dwv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  float pvk[3] = {0.0f, 0.0f, 0.0f}, pvv[3] = {0.0f, 0.0f, 0.0f};
+  int turn = 0;  // the wave that writes the tile's da
+
+  for (; b0 >= t0 && t1 > t0; b0 -= 32) {
+    const Column<T, D> xk = nk, xv = nv;
+    nk.load(rk, b0 - 32 + 8 * g, c);  // the tile before (before the slice: reads 0, unused)
+    nv.load(rv, b0 - 32 + 8 * g, c);
+    float p[8], t[8];
+    xv.conv(wv, t);
+    put_planes<D>(pv, c, g, t);
+    xk.conv(wk, p);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = phi_fast(p[j]);
+    put_planes<D>(pk, c, g, p);
+    __syncthreads();  // the planes (and, the first time, the gates)
+    const f32x4_t ga = *reinterpret_cast<const f32x4_t*>(&gt[b0 - t0 + 8 * g]);
+    const f32x4_t gb = *reinterpret_cast<const f32x4_t*>(&gt[b0 - t0 + 8 * g + 4]);
+    const float gj[8] = {ga[0], ga[1], ga[2], ga[3], gb[0], gb[1], gb[2], gb[3]};
+    const uint32_t off = (uint32_t)((b0 + 8 * g) * D + c) * 4u;
+    // t = dS vt + dz; dkt = g t phi'(kt); da = g (P . t)
+    contract_planes<D>(pv, f1, lane, t);
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      t[j] += dz;
+      v[j] = p[j] * t[j];
+    }
+    const float dg = scatter_sum8(v, n);
+    if (!(n & 1)) part[wave][8 * g + (n >> 1)] = dg;
     // dvt = g dS^T P
-    {
-      f32x4_t acc[NMB];
+    contract_planes<D>(pk, f2, lane, v);
 #pragma unroll
-      for (int b = 0; b < NMB; ++b) acc[b] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
-      contract_rows<D>(pk, stg[wave], f2, lane, acc);
-#pragma unroll
-      for (int b = 0; b < NMB; ++b)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[b][i] = gj[i] * acc[b][i];
+    for (int j = 0; j < 8; ++j) {
+      t[j] = gj[j] * t[j] * fminf(p[j], 1.0f);  // phi'(u) = min(phi(u), 1)
+      v[j] *= gj[j];
     }
-    conv_back<T, D>(x, xv, wv, stg[wave], later[wave][1], rdv, off, lane, dwv);
+    __syncthreads();  // the planes are read, the sums of da whole
+    if (wave == turn && lane < 32) {
+      float x = part[0][lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) x += part[w][lane];
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(gt[b0 - t0 + lane] * x), rda,
+                                            (uint32_t)(b0 + lane) * 4u, 0, 0);
+    }
+    turn = turn + 1 == NW ? 0 : turn + 1;
+    conv_back8<T, D>(t, xk, wk, pvk, lane, rdk, off, dwk);
+    conv_back8<T, D>(v, xv, wv, pvv, lane, rdv, off, dwv);
   }
 
-  wave_lds_sync();
-  store_edge<D>(later[wave][0], edge + edge_off<D>(P, 1, h, unit, wave), lane);
-  store_edge<D>(later[wave][1], edge + edge_off<D>(P, 2, h, unit, wave), lane);
   const size_t ui = (size_t)h * P.units + unit;
-  __syncthreads();  // every wave is done with the operands
-  sum_taps<D>(dwk, reinterpret_cast<f32x4_t(*)[D]>(f1), dcp + (ui * 3 + 1) * D * 4);
-  sum_taps<D>(dwv, reinterpret_cast<f32x4_t(*)[D]>(f1), dcp + (ui * 3 + 2) * D * 4);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    dwk[t] = sum_groups(dwk[t]);
+    dwv[t] = sum_groups(dwv[t]);
+  }
+  if (g == 0) {
+    *reinterpret_cast<f32x4_t*>(dcp + (ui * 3 + 1) * D * 4 + 4 * c) = (f32x4_t){dwk[0], dwk[1], dwk[2], dwk[3]};
+    *reinterpret_cast<f32x4_t*>(dcp + (ui * 3 + 2) * D * 4 + 4 * c) = (f32x4_t){dwv[0], dwv[1], dwv[2], dwv[3]};
+    float* ek = edge + edge_off<D>(P, 1, h, unit) + c;
+    float* ev = edge + edge_off<D>(P, 2, h, unit) + c;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      ek[i * D] = pvk[i];
+      ev[i * D] = pvv[i];
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
 // What the two passes leave: block (unit, h) of the first P.units adds the
-// missing products to dx of the three tokens before each wave's first token,
-//   dx_{p-3+j} += sum_{t <= j} w_t dxt_{p+j-t},  p > 0 the wave's first token,
+// missing products to dx of the three tokens before the unit's first token,
+//   dx_{p-3+j} += sum_{t <= j} w_t dxt_{p+j-t},  p > 0 the unit's first token,
 // the remaining blocks sum dgamma and the taps (bwd_params).
 // ---------------------------------------------------------------------------
 template <int D>
@@ -1202,16 +1221,13 @@ bwd_finish_kernel(Plan P, const int32_t* __restrict__ cu, const float* __restric
   if (!unit_of(P, cu, P.chunk, P.chunks_per_seq, unit, &s, &chunk)) return;
   int64_t len, base_row;
   seq_geometry(P, cu, s, h, &len, &base_row);
-  const int t0 = chunk * P.chunk;
-  const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
-  const int q4 = quarter_tokens(t1 - t0);
-  for (int x = tid; x < 3 * 4 * D; x += kThreads) {  // (tensor, wave, channel)
-    const int c = x % D, wave = (x / D) & 3, tensor = x / (4 * D);
-    const int p = t0 + wave * q4;
-    if (p == 0 || p >= t1) continue;
+  const int p = chunk * P.chunk;
+  if (p == 0) return;
+  for (int x = tid; x < 3 * D; x += kThreads) {  // (tensor, channel)
+    const int c = x % D, tensor = x / D;
     float w4[4], d[3];
     load_taps4(conv_w, P.heads, h, tensor, D, P.W, c, w4);
-    const float* e = edge + edge_off<D>(P, tensor, h, unit, wave) + c;
+    const float* e = edge + edge_off<D>(P, tensor, h, unit) + c;
 #pragma unroll
     for (int j = 0; j < 3; ++j) d[j] = e[j * D];
     float* out = (tensor == 0 ? dq : tensor == 1 ? dk : dv) + (base_row + p - 3) * D + c;
@@ -1246,26 +1262,20 @@ gbla_status run_backward(const Plan& p, const BwdLayout& L, const void* q, const
   const int nparam = (D + 3 * D * p.W + 63) / 64;  // slices of bwd_params
   const T *qq = (const T*)q, *kk = (const T*)k, *vv = (const T*)v, *aa = (const T*)a, *rr = (const T*)r;
   if (rows_supported(p)) {
-    gbla_status e = launch_state_rows(p, k, v, a, conv_w, cu, dsp, false, st);
+    const dim3 block(SP<D>::NT);
+    hipLaunchKernelGGL((bwd_state_split_kernel<T, D>), grid, block, 0, st, p, kk, vv, aa, conv_w, cu, dsp);
+    gbla_status e = launch_combine_f32(p, cu, dsp, S, z, mz, st);
     if (e != GBLA_OK) return e;
-    e = launch_combine_f32(p, cu, dsp, S, z, mz, st);
-    if (e != GBLA_OK) return e;
-    // d = 128: the query pass leaves dnum in dv, which the key pass fills only
-    // after bwd_dsum_rows_kernel has read it
-    constexpr bool kDS = D <= 64;
     if (gamma)
-      hipLaunchKernelGGL((bwd_query_rows_kernel<T, D, true, kDS>), grid, dim3(kThreads), 0, st, p, qq,
-                         rr, dy, conv_w, gamma, cu, S, z, dq, dr, dsp, dgp, dcp, edge, dv);
+      hipLaunchKernelGGL((bwd_query_split_kernel<T, D, true>), grid, block, 0, st, p, qq, rr, dy, conv_w,
+                         gamma, cu, S, z, dq, dr, dsp, dgp, dcp, edge);
     else
-      hipLaunchKernelGGL((bwd_query_rows_kernel<T, D, false, kDS>), grid, dim3(kThreads), 0, st, p, qq,
-                         rr, dy, conv_w, gamma, cu, S, z, dq, dr, dsp, dgp, dcp, edge, dv);
-    if constexpr (!kDS)
-      hipLaunchKernelGGL((bwd_dsum_rows_kernel<T, D>), grid, dim3(kThreads), 0, st, p, qq,
-                         (const float*)dv, conv_w, cu, dsp);
+      hipLaunchKernelGGL((bwd_query_split_kernel<T, D, false>), grid, block, 0, st, p, qq, rr, dy, conv_w,
+                         gamma, cu, S, z, dq, dr, dsp, dgp, dcp, edge);
     hipLaunchKernelGGL((bwd_dscombine_kernel<D>), cgrid, dim3(kThreads), 0, st, p, cu,
                        (const float*)dsp, dS);
-    hipLaunchKernelGGL((bwd_key_rows_kernel<T, D>), grid, dim3(kThreads), 0, st, p, kk, vv, aa, conv_w,
-                       cu, (const float*)dS, (const float*)mz, dk, dv, da, dcp, edge);
+    hipLaunchKernelGGL((bwd_key_split_kernel<T, D>), grid, block, 0, st, p, kk, vv, aa, conv_w, cu,
+                       (const float*)dS, (const float*)mz, dk, dv, da, dcp, edge);
     hipLaunchKernelGGL((bwd_finish_kernel<D>), dim3(p.units + nparam, p.heads), dim3(kThreads), 0, st,
                        p, cu, conv_w, (const float*)edge, (const float*)dgp, (const float*)dcp, dq, dk,
                        dv, dgamma, dconv);

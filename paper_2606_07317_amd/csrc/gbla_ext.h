@@ -20,8 +20,8 @@ struct BwdLayout {
                     // per-unit dS, dz partials
   size_t off_dS;    // [N, H, d*d + d] dS, dz
   size_t off_dgp;   // [H, units, d] per-unit dgamma partials
-  size_t off_edge;  // [3, H, units, 4, 3, d] gradients of the first three
-                    // convolved tokens of each wave's part of a unit (q, k, v)
+  size_t off_edge;  // [3, H, units, 3, d] gradients of the first three
+                    // convolved tokens of each unit (q, k, v)
   size_t off_dxt;   // [3, tokens * H * d] gradients of the convolved q, k, v
                     // (read and written for slices of 2^31 bytes and more only)
   size_t off_dcp;   // [H, units, 3, d, 4] per-unit tap-gradient partials

@@ -107,7 +107,7 @@ BwdLayout make_bwd_layout(const Plan& p) {
   L.off_dsp = take(unit_recs * p.rec_floats * f);
   L.off_dS = take(pairs * (d * d + d) * f);
   L.off_dgp = take(unit_recs * d * f);
-  L.off_edge = take(unit_recs * 3 * 4 * 3 * d * f);
+  L.off_edge = take(unit_recs * 3 * 3 * d * f);
   L.off_dxt = take(3 * (size_t)p.tokens * p.heads * d * f);
   L.off_dcp = take(unit_recs * 3 * d * 4 * f);
   L.total_bytes = off;

@@ -869,14 +869,16 @@ struct ConvRun {
 
 // One element per thread while the grid stays small, four or sixteen once
 // there are many (sequence, head) pairs (fewer workgroups, each with more
-// loads in flight).  The result does not depend on the choice.
+// loads in flight).  fp32 (the backward's 512-token units, so more partials a
+// pair) keeps one element longer: 128 pairs of d = 128, 57,511 tokens 31 us
+// against 48 with four.  The result does not depend on the choice.
 template <typename T, int D>
 gbla_status run_combine(const Plan& p, const int32_t* cu, const float* partials, float* S,
                         float* z, unsigned char* frags, float* mz, hipStream_t st) {
   constexpr int kElems = D * D + D;
   const int64_t pairs = (int64_t)p.nseq * p.heads;
   const int slices1 = (kElems + kThreads - 1) / kThreads;
-  if (pairs * slices1 <= 4096) {
+  if (pairs * slices1 <= (sizeof(T) == 4 ? 16384 : 4096)) {
     hipLaunchKernelGGL((combine_kernel<T, D, 1>), dim3(pairs, slices1), dim3(kThreads), 0, st, p,
                        cu, partials, S, z, frags, mz);
   } else if (pairs * ((kElems + 4 * kThreads - 1) / (4 * kThreads)) <= 4096) {
@@ -902,7 +904,7 @@ struct StateRun {
     if (stream_supported(p)) {
       e = launch_state_stream(p, k, v, a, w, cu, partials, st);
     } else if (p.dtype == GBLA_F32 && rows_supported(p)) {
-      e = launch_state_rows(p, k, v, a, w, cu, partials, true, st);
+      e = launch_state_rows(p, k, v, a, w, cu, partials, st);
     } else {
       hipLaunchKernelGGL((state_partial_kernel<T, D>), dim3(p.units, p.heads), dim3(kThreads), 0,
                          st, p, (const T*)k, (const T*)v, (const T*)a, w, cu, partials);

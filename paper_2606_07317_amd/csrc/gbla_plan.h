@@ -117,13 +117,12 @@ gbla_status launch_readout_stream(const Plan& p, const void* q, const void* r, c
                                   const float* gamma, const int32_t* cu, const unsigned char* frags,
                                   float* out, hipStream_t stream, KernelEvents ev = {});
 
-// fp32-product kernels (gbla_rows.hip): the fp32 forward, and the state that
-// the backward recomputes (either dtype; records as launch_state_stream's;
-// forward: with the fp32 forward's exponential).
+// fp32-product kernels (gbla_rows.hip): the fp32 forward (records as
+// launch_state_stream's).
 bool rows_supported(const Plan& p);
 gbla_status launch_state_rows(const Plan& p, const void* k, const void* v, const void* a,
                               const float* conv_w, const int32_t* cu, float* partials,
-                              bool forward, hipStream_t stream);
+                              hipStream_t stream);
 // The whole forward in one launch, for batches of short sequences.
 bool short_forward(const Plan& p);
 gbla_status launch_short_forward(const Plan& p, const void* q, const KeyInputs& in, const void* r,

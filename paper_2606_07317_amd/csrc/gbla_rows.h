@@ -1,6 +1,6 @@
-// gbla_rows.h -- device helpers of the fp32-product kernels (the fp32 forward
-// and the backward): rows of a tensor held channel-major in registers, so that
-// every product runs on v_mfma_f32_16x16x4_f32 with fp32 operands.
+// gbla_rows.h -- device helpers of the fp32 forward and of the one-launch
+// forward: rows of a tensor held channel-major in registers, so that every
+// product of the fp32 kernels runs on v_mfma_f32_16x16x4_f32 with fp32 operands.
 //
 // Channel layout.  A wave works on a tile of 16 consecutive tokens.  Lane (n,
 // g) = (lane & 15, lane >> 4) holds the D/16 channels slot_chan(b, n), b < D/16, of
@@ -10,9 +10,9 @@
 //     registers with no cross-lane traffic.  A layout with one token per lane
 //     needed two DPP moves per tap and channel: 12 vector instructions per
 //     element against 6.
-//   - Per-channel sums over tokens (z, dz, dgamma, the tap gradients) take one
-//     accumulator per channel slot: D/16 a lane instead of D/4.
-//   - Token sums (S, dS) take the values as MFMA operands directly: in K step
+//   - Per-channel sums over tokens (z) take one accumulator per channel slot:
+//     D/16 a lane instead of D/4.
+//   - Token sums (S) take the values as MFMA operands directly: in K step
 //     i, lane group g supplies token 4 g + i.
 //   - Channel sums need one token per lane: the tile goes through the wave's
 //     own LDS stage (contract_rows), whose product comes out in the channel
@@ -206,20 +206,6 @@ struct Frags {
     const int idx = threadIdx.x + u * kThreads;
     return slot_chan<D>((idx >> 6) / CL<D>::NMB, idx & 15);
   }
-  // X[k][c] = m[c * D + k] of a row-major matrix in memory.  All loads are
-  // issued before any is used.
-  __device__ __forceinline__ void load_transposed(const float* __restrict__ m) {
-#pragma unroll
-    for (int u = 0; u < kPer; ++u)
-      v[u] = *reinterpret_cast<const f32x4_t*>(m + (size_t)col(u) * D + k0(u));
-  }
-  // X[k][c] = m[k * D + c]
-  __device__ __forceinline__ void load(const float* __restrict__ m) {
-#pragma unroll
-    for (int u = 0; u < kPer; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[u][i] = m[(size_t)(k0(u) + i) * D + col(u)];
-  }
   __device__ __forceinline__ void put(f32x4_t* frag) const {
 #pragma unroll
     for (int u = 0; u < kPer; ++u) frag[threadIdx.x + u * kThreads] = v[u];
@@ -336,26 +322,12 @@ __device__ __forceinline__ void sum_channels(const float* v, float (*red)[D], fl
   __syncthreads();
 }
 
-// Taps of a lane's channel slot b: read from LDS where they are used, or held
-// in registers (where LDS is full).
+// Taps of a lane's channel slot b, read from LDS where they are used.
 template <int D>
 struct LdsTaps {
   const f32x4_t* t;  // slot order: slot 16 b + n holds channel slot_chan(b, n)
   int n;
   __device__ __forceinline__ f32x4_t operator()(int b) const { return t[16 * b + n]; }
-};
-template <int D>
-struct RegTaps {
-  f32x4_t w[CL<D>::NMB];
-  __device__ __forceinline__ f32x4_t operator()(int b) const { return w[b]; }
-  __device__ __forceinline__ void load(const float* conv_w, int H, int h, int tensor, int W, int n) {
-#pragma unroll
-    for (int b = 0; b < CL<D>::NMB; ++b) {
-      float w4[4];
-      load_taps4(conv_w, H, h, tensor, D, W, slot_chan<D>(b, n), w4);
-      w[b] = (f32x4_t){w4[0], w4[1], w4[2], w4[3]};
-    }
-  }
 };
 
 // Taps of one tensor into LDS in LdsTaps' order.

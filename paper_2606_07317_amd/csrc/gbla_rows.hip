@@ -1,6 +1,6 @@
-// gbla_rows.hip -- the state reduction and the readout with fp32 products
-// (channel layout, gbla_rows.h): the whole fp32 forward, and the state that
-// the backward recomputes.  Slices below 2^31 bytes.
+// gbla_rows.hip -- the fp32 forward (state reduction and readout with fp32
+// products) and the one-launch forward of short sequences, in the channel
+// layout of gbla_rows.h.  Slices below 2^31 bytes.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -19,13 +19,10 @@ __device__ __forceinline__ float gate(float x) {
   if constexpr (kFull) return expf(x);
   else return __expf(x);
 }
-// phi(u) = elu(u) + 1 without a branch, as the forward's other kernels have it
-// (kFwd) or the backward's.
-template <bool kFwd, bool kFull>
+// phi(u) = elu(u) + 1 without a branch.
+template <bool kFull>
 __device__ __forceinline__ float phi(float u) {
-  if constexpr (kFwd) return fmaxf(u, 0.0f) + gate<kFull>(fminf(u, 0.0f));
-  const float e = gate<kFull>(u);
-  return u > 0.0f ? u + 1.0f : e;
+  return fmaxf(u, 0.0f) + gate<kFull>(fminf(u, 0.0f));
 }
 
 template <typename T>
@@ -43,15 +40,13 @@ __device__ __forceinline__ float load_logit(__amdgpu_buffer_rsrc_t r, int tok) {
 //   S_p = sum_j w_j phi(kt_j) vt_j^T, z_p = sum_j w_j phi(kt_j).
 // Each wave takes a contiguous quarter of the unit's tokens, 16 at a time, and
 // keeps its own D x D sum, so the waves never meet inside the loop; the
-// quarters are added as (w0 + w1) + (w2 + w3).  Measured against the kernels
-// that this replaced: fp32 forward, B = 2, n = 8191, H = 8, d = 64 52 -> 29 us;
-// the backward's bf16 state at n = 32768, H = 8, d = 64 52 -> 39 us, on 57,511
-// packed tokens, H = 8, d = 128 407 -> 275 us (256 products a tile are 107 us).
+// quarters are added as (w0 + w1) + (w2 + w3).  Measured against the kernel
+// that this replaced: B = 2, n = 8191, H = 8, d = 64 52 -> 29 us.
 // ---------------------------------------------------------------------------
-template <typename T, int D, bool kFwd>
+template <int D>
 __global__ void __launch_bounds__(kThreads, D >= 128 ? 1 : 2)
-state_rows_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
-                  const T* __restrict__ ain, const float* __restrict__ conv_w,
+state_rows_kernel(Plan P, const float* __restrict__ kin, const float* __restrict__ vin,
+                  const float* __restrict__ ain, const float* __restrict__ conv_w,
                   const int32_t* __restrict__ cu, float* __restrict__ partials) {
   using C = CL<D>;
   constexpr int NMB = C::NMB;
@@ -71,17 +66,17 @@ state_rows_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
   seq_geometry(P, cu, s, h, &len, &base_row);
   const int t0 = chunk * P.chunk;
   const int t1 = (int)min(len, (int64_t)t0 + P.chunk);
-  const uint32_t bytes = (uint32_t)len * (uint32_t)(D * sizeof(T));
+  const uint32_t bytes = (uint32_t)len * (uint32_t)(D * 4);
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(kin + base_row * D, bytes);
   const __amdgpu_buffer_rsrc_t rv = make_rsrc(vin + base_row * D, bytes);
   // no gate logits: an empty range, so every logit reads as 0
   const __amdgpu_buffer_rsrc_t ra =
-      ain ? make_rsrc(ain + base_row, (uint32_t)len * (uint32_t)sizeof(T)) : make_rsrc(kin, 0u);
+      ain ? make_rsrc(ain + base_row, (uint32_t)len * 4u) : make_rsrc(kin, 0u);
 
   // the wave's quarter of the unit, in whole tiles
   const int q4 = quarter_tokens(t1 - t0);
   const int w0 = t0 + wave * q4, w1 = min(t1, w0 + q4);
-  Window<T, D> nk, nv;
+  Window<float, D> nk, nv;
   nk.load(rk, w0 + 4 * g, n);
   nv.load(rv, w0 + 4 * g, n);
   stage_taps<D>(conv_w, P.heads, h, 1, P.W, tk);
@@ -90,7 +85,7 @@ state_rows_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
   // gate weights of the unit, zero past its end
   float ml = -INFINITY;
   for (int j = t0 + tid; j < t1; j += kThreads) {
-    const float a = load_logit<T>(ra, j);
+    const float a = load_logit<float>(ra, j);
     wts[j - t0] = a;
     ml = fmaxf(ml, a);
   }
@@ -98,7 +93,7 @@ state_rows_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
   float lacc = 0.0f;
   for (int j = tid; j < 4 * q4; j += kThreads) {
     float w = 0.0f;
-    if (j < t1 - t0) w = m == -INFINITY ? 0.0f : gate<kFwd>(wts[j] - m);
+    if (j < t1 - t0) w = m == -INFINITY ? 0.0f : gate<true>(wts[j] - m);
     wts[j] = w;
     lacc += w;
   }
@@ -124,7 +119,7 @@ state_rows_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vin,
     for (int b = 0; b < NMB; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        kt[b][i] = w[i] * phi<kFwd, kFwd>(kt[b][i]);
+        kt[b][i] = w[i] * phi<true>(kt[b][i]);
         z[b] += kt[b][i];
       }
     token_product<D>(kt, vt, acc);
@@ -220,7 +215,7 @@ readout_rows_kernel(Plan P, const float* __restrict__ qin, const float* __restri
       const float z = zs[16 * b + n];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        x[b][i] = phi<true, true>(x[b][i]);
+        x[b][i] = phi<true>(x[b][i]);
         den[i] = fmaf(x[b][i], z, den[i]);
       }
     }
@@ -338,7 +333,7 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
                      const int32_t* __restrict__ cu, float* __restrict__ out) {
   using C = CL<D>;
   constexpr int NMB = C::NMB;
-  constexpr bool kFwd = sizeof(T) == 4;
+  constexpr bool kFull = sizeof(T) == 4;
   // the waves' sums, then the operands B[c][e] = S[c][e]
   __shared__ __attribute__((aligned(16))) float buf[2 * D * D];
   __shared__ __attribute__((aligned(16))) float stg[4][C::kStage];
@@ -397,13 +392,13 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
       nv.conv(LdsTaps<D>{tv, n}, vt);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        w[i] = b0 + 4 * g + i < len && m != -INFINITY ? gate<kFwd>(na[i] - m) : 0.0f;
+        w[i] = b0 + 4 * g + i < len && m != -INFINITY ? gate<kFull>(na[i] - m) : 0.0f;
       issue_kv(b0 + 16 + 4 * g);  // past the sequence they read 0; unused
 #pragma unroll
       for (int b = 0; b < NMB; ++b)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          kt[b][i] = w[i] * phi<true, kFwd>(kt[b][i]);
+          kt[b][i] = w[i] * phi<kFull>(kt[b][i]);
           z[b] += kt[b][i];
         }
       token_product<D>(kt, vt, acc);
@@ -451,7 +446,7 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
       const float z = zs[slot_chan<D>(b, n)];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        x[b][i] = phi<true, kFwd>(x[b][i]);
+        x[b][i] = phi<kFull>(x[b][i]);
         den[i] = fmaf(x[b][i], z, den[i]);
       }
     }
@@ -482,7 +477,7 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
         for (int b = 0; b < NMB; ++b) {
           const float r = rv4[b][i];
           x[b][i] = x[b][i] * scale * gs[slot_chan<D>(b, n)] *
-                    (r * __builtin_amdgcn_rcpf(1.0f + gate<kFwd>(-r)));
+                    (r * __builtin_amdgcn_rcpf(1.0f + gate<kFull>(-r)));
         }
       }
       store_row<D>(ro, off + (uint32_t)(i * D * 4), x, i);
@@ -587,7 +582,7 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
           float a = t4[0] * xk[j].at(b);
 #pragma unroll
           for (int t = 1; t < 4; ++t) a = fmaf(t4[t], xk[j + t].at(b), a);
-          kw[j] = w[j] * phi<true, false>(a);
+          kw[j] = w[j] * phi<false>(a);
           z[b] += kw[j];
         }
 #pragma unroll
@@ -677,7 +672,7 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
         float a = t4[0] * xq[j].at(b);
 #pragma unroll
         for (int t = 1; t < 4; ++t) a = fmaf(t4[t], xq[j + t].at(b), a);
-        x[b][j] = phi<true, false>(a);
+        x[b][j] = phi<false>(a);
         den[j] = fmaf(x[b][j], z, den[j]);
       }
     }
@@ -735,28 +730,20 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
   }
 }
 
-template <typename T, bool kFwd>
-gbla_status run_state(const Plan& p, const void* k, const void* v, const void* a,
-                      const float* conv_w, const int32_t* cu, float* partials, hipStream_t st) {
+}  // namespace
+
+gbla_status launch_state_rows(const Plan& p, const void* k, const void* v, const void* a,
+                              const float* conv_w, const int32_t* cu, float* partials,
+                              hipStream_t st) {
   const dim3 grid(p.units, p.heads);
-#define GBLA_STATE_ROWS(DD)                                                                       \
-  hipLaunchKernelGGL((state_rows_kernel<T, DD, kFwd>), grid, dim3(kThreads), 0, st, p, (const T*)k, \
-                     (const T*)v, (const T*)a, conv_w, cu, partials)
+#define GBLA_STATE_ROWS(DD)                                                                     \
+  hipLaunchKernelGGL((state_rows_kernel<DD>), grid, dim3(kThreads), 0, st, p, (const float*)k,  \
+                     (const float*)v, (const float*)a, conv_w, cu, partials)
   if (p.d == 128) GBLA_STATE_ROWS(128);
   else if (p.d == 64) GBLA_STATE_ROWS(64);
   else GBLA_STATE_ROWS(32);
 #undef GBLA_STATE_ROWS
   return hipGetLastError() == hipSuccess ? GBLA_OK : GBLA_ERR_HIP;
-}
-
-}  // namespace
-
-gbla_status launch_state_rows(const Plan& p, const void* k, const void* v, const void* a,
-                              const float* conv_w, const int32_t* cu, float* partials,
-                              bool forward, hipStream_t st) {
-  if (p.dtype == GBLA_BF16) return run_state<uint16_t, false>(p, k, v, a, conv_w, cu, partials, st);
-  if (forward) return run_state<float, true>(p, k, v, a, conv_w, cu, partials, st);
-  return run_state<float, false>(p, k, v, a, conv_w, cu, partials, st);
 }
 
 gbla_status launch_readout_rows(const Plan& p, const void* q, const void* r, const float* conv_w,
