@@ -1,8 +1,9 @@
 // gbla_layer.hip -- the projections of the full GBLA layer (Section 2.1):
 //     Xt = Conv1D(X),  [Q | K | V | R | a] = Xt Wp^T
 //
-// conv_x_kernel  streams X once: causal depthwise conv in fp32, Xt rounded
-//                to bf16 into the workspace (a bf16 layer stores it so).
+// conv_gate_kernel  streams X once: causal depthwise conv in fp32, Xt rounded
+//                to bf16 into the workspace (a bf16 layer stores it so), and
+//                the gate logits from it.
 // proj_kernel    P = Xt Wp^T on v_mfma_f32_32x32x16_bf16 (fp32 accumulation):
 //                a workgroup of 4 waves (2 x 2, 128 x 128 each, one per
 //                SIMD, accumulators in AGPRs) computes a 256-token x
@@ -125,73 +126,172 @@ __device__ __forceinline__ int seq_end(const LayerPlan& P, const int32_t* cu, in
 }
 
 // ---------------------------------------------------------------------------
-// conv_x_kernel: Xt = Conv1D(X) in fp32, rounded to bf16, into the
-// workspace.  grid (d_model / 128, tokens / 256): thread (run, chunk) takes
-// eight channels of 16 consecutive tokens from the 19 rows covering their
-// windows (the three rows before the run come from the previous run's
-// tokens, or read as zero before the sequence start).
+// conv_gate_kernel: Xt = Conv1D(X) in fp32, rounded to bf16, into the workspace,
+// and from it the first 32 gate logits a = Xt w_g^T (rows of Wp past the 4 H d
+// features), in one pass over X: a gate pass of its own read Xt again (0.54 GB
+// and 135 us at B = 8, L = 32768, d_model = 1024).
+//
+// grid (tokens / TM): a workgroup takes TM tokens and goes through the model
+// channels 128 at a time.  Thread (run, chunk) convolves eight channels of TM /
+// 16 consecutive tokens (their windows' rows come from memory, mostly L1; the
+// next step's rows are loaded while the current ones are worked on), writes
+// them to Xt, whole lines, and to an LDS slab (256-byte token rows, 16-byte
+// chunks XOR-swizzled by the row); the gate rows' channels are staged beside it.
+// On v_mfma_f32_32x32x16_bf16, gate rows as the first operand, wave w then
+// multiplies the 32 tokens w % (TM / 32), with TM < 128 a part of the slab's
+// channels (the parts are added at the end).  Bound by HBM (one read, one
+// write): TM = 128 has the fewest halo rows and tap loads per token, shorter
+// tiles fill the chip where there are few tokens.  Measured, d_model = 1024,
+// against the two passes: 262144 tokens 224 us (4.8 TB/s; 357 before; TM = 64:
+// 250, TM = 32: 370), 16384 tokens 27 us (31 before; TM = 64: 31); 7700 tokens,
+// d_model = 256: 10.6 us (17 before).  TM = 128 needs more than the 168
+// registers of three waves a SIMD (spilled: 560 us).
 // ---------------------------------------------------------------------------
-constexpr int kConvRun = 16;
-
-__global__ void __launch_bounds__(kThreads)
-conv_x_kernel(LayerPlan P, const uint16_t* __restrict__ x, const float* __restrict__ conv_x,
-              const int32_t* __restrict__ cu, uint16_t* __restrict__ xt) {
-  const int tid = threadIdx.x, chunk = tid & 15, run = tid >> 4;
-  const int c0 = blockIdx.x * 128 + 8 * chunk;
-  const int t0 = blockIdx.y * (16 * kConvRun) + run * kConvRun;
-  const int K = P.d_model, M = P.tokens;
-  if (t0 >= M || c0 >= K) return;  // no barrier follows
+template <int TM>
+__global__ void __launch_bounds__(kThreads, TM == 128 ? 2 : 3)
+conv_gate_kernel(LayerPlan P, const uint16_t* __restrict__ x, const float* __restrict__ conv_x,
+                 const int32_t* __restrict__ cu, const uint16_t* __restrict__ wp,
+                 uint16_t* __restrict__ xt, uint16_t* __restrict__ a) {
+  constexpr int RUN = TM / 16, kTiles = TM / 32, kParts = 4 / kTiles, kPer = 8 / kParts;
+  __shared__ __attribute__((aligned(16))) unsigned char slab[TM * 256];
+  __shared__ __attribute__((aligned(16))) unsigned char wslab[32 * 256];
+  __shared__ float sums[kParts > 1 ? 4 * 16 * 64 : 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, half = lane >> 5;
+  const int chunk = tid & 15, run = tid >> 4;
+  const int K = P.d_model, M = P.tokens, H = P.heads;
+  const int tb = blockIdx.x * TM, t0 = tb + run * RUN;
+  const int64_t grow0 = (int64_t)4 * H * P.d;  // first gate row of Wp
+  // rows past the last token (gate, channel) read zeros and are not written
   const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, (uint32_t)((int64_t)M * K * 2));
-  // taps: one 16-byte load per channel at W = 4, else one load per tap (an
-  // out-of-range offset, read as zero, for the taps before the first)
+  const __amdgpu_buffer_rsrc_t rt = make_rsrc(xt, (uint32_t)((int64_t)M * K * 2));
+  const __amdgpu_buffer_rsrc_t rg = make_rsrc(wp + grow0 * K, (uint32_t)((int64_t)H * K * 2));
   const __amdgpu_buffer_rsrc_t rw = make_rsrc(conv_x, (uint32_t)(K * P.W * 4));
-  float w[8][4];
+
+  u32x4_t raw[RUN + 3], wg[2];
+  auto load = [&](int k0) {
+    const int c0 = k0 + 8 * chunk;
+    const bool in = c0 < K;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const uint32_t row = (uint32_t)((c0 + j) * P.W) * 4u;
-    if (P.W == 4) {
-      const u32x4_t t4 = __builtin_amdgcn_raw_buffer_load_b128(rw, row, 0, 0);
+    for (int u = 0; u < RUN + 3; ++u)
+      raw[u] = bload(rx, in ? (uint32_t)(((int64_t)(t0 - 3 + u) * K + c0) * 2) : kOutOfRange);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) w[j][t] = __uint_as_float(t4[t]);
-    } else {
+    for (int j = 0; j < 2; ++j)
+      wg[j] = bload(rg, in ? ((uint32_t)(run + 16 * j) * (uint32_t)K + (uint32_t)c0) * 2u : kOutOfRange);
+  };
+  load(0);
+  // rows of each token's window inside its sequence: min(3, tokens before it)
+  int back[RUN];
+  bool whole = true;
+  {
+    const int m0 = min(t0, M - 1);
+    int start = seq_start(P, cu, m0), next = P.ragged ? seq_end(P, cu, m0) : start + P.rows;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int ti = t - (4 - P.W);
-        w[j][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, ti >= 0 ? row + 4u * ti : kOutOfRange, 0, 0));
+    for (int i = 0; i < RUN; ++i) {
+      const int m = min(t0 + i, M - 1);
+      if (m >= next) {  // a new sequence starts inside the run
+        start = seq_start(P, cu, m);
+        next = P.ragged ? seq_end(P, cu, m) : start + P.rows;
       }
+      back[i] = m - start;
+      whole = whole && back[i] >= 3;
     }
   }
-  u32x4_t raw[kConvRun + 3];
+  const bool all_whole = __all(whole);
+
+  f32x16_t acc = {};
+  const int wtile = wave % kTiles, wpart = wave / kTiles;
+  const int srow = 32 * wtile + l32;
+  // d_model is a multiple of 64: the last step may be half empty
+  const int nk = (K + 127) / 128;
+  for (int s = 0; s < nk; ++s) {
+    const int c0 = 128 * s + 8 * chunk;
+    // taps: one 16-byte load per channel at W = 4, else one load per tap (an
+    // out-of-range offset, read as zero, for the taps before the first)
+    float w[8][4];
 #pragma unroll
-  for (int u = 0; u < kConvRun + 3; ++u)
-    raw[u] = bload(rx, (uint32_t)(((int64_t)(t0 - 3 + u) * K + c0) * 2));
-  int start = seq_start(P, cu, t0), next = P.ragged ? seq_end(P, cu, t0) : start + P.rows;
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t row = (uint32_t)((c0 + j) * P.W) * 4u;
+      if (P.W == 4) {
+        const u32x4_t t4 = __builtin_amdgcn_raw_buffer_load_b128(rw, row, 0, 0);
 #pragma unroll
-  for (int i = 0; i < kConvRun; ++i) {
-    const int m = t0 + i;
-    if (m >= M) break;
-    if (m >= next) {  // a new sequence starts inside the run
-      start = seq_start(P, cu, m);
-      next = P.ragged ? seq_end(P, cu, m) : start + P.rows;
-    }
-    const int back = m - start;
-    float acc[8];
+        for (int t = 0; t < 4; ++t) w[j][t] = __uint_as_float(t4[t]);
+      } else {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (3 - t > back) continue;  // row before the sequence start
-      const u32x4_t v = raw[i + t];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        acc[2 * q] = fmaf(w[2 * q][t], bf16_lo(v[q]), acc[2 * q]);
-        acc[2 * q + 1] = fmaf(w[2 * q + 1][t], bf16_hi(v[q]), acc[2 * q + 1]);
+        for (int t = 0; t < 4; ++t) {
+          const int ti = t - (4 - P.W);
+          w[j][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, ti >= 0 ? row + 4u * ti : kOutOfRange, 0, 0));
+        }
       }
     }
-    u32x4_t o;
+    u32x4_t o[RUN];
+    auto conv = [&](auto checked) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = pack_bf16x2(acc[2 * q], acc[2 * q + 1]);
-    *reinterpret_cast<u32x4_t*>(xt + (size_t)m * K + c0) = o;
+      for (int i = 0; i < RUN; ++i) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          u32x4_t r = raw[i + t];
+          if (decltype(checked)::value && 3 - t > back[i]) continue;  // row before the sequence start
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            v[2 * q] = fmaf(w[2 * q][t], bf16_lo(r[q]), v[2 * q]);
+            v[2 * q + 1] = fmaf(w[2 * q + 1][t], bf16_hi(r[q]), v[2 * q + 1]);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[i][q] = pack_bf16x2(v[2 * q], v[2 * q + 1]);
+      }
+    };
+    if (all_whole) conv(std::false_type{}); else conv(std::true_type{});
+    if (s > 0) __syncthreads();  // every wave done reading the slabs
+#pragma unroll
+    for (int i = 0; i < RUN; ++i) {
+      const int row = run * RUN + i;
+      __builtin_amdgcn_raw_buffer_store_b128(o[i], rt, c0 < K ? (uint32_t)(((int64_t)(t0 + i) * K + c0) * 2) : kOutOfRange, 0, 0);
+      *reinterpret_cast<u32x4_t*>(&slab[row * 256 + ((chunk ^ (row & 15)) << 4)]) = o[i];
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int row = run + 16 * j;
+      *reinterpret_cast<u32x4_t*>(&wslab[row * 256 + ((chunk ^ (row & 15)) << 4)]) = wg[j];
+    }
+    load(128 * (s + 1));  // past the channels: zeros, unused
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int ch = 2 * (kPer * wpart + u) + half;
+      const u32x4_t wa = *reinterpret_cast<const u32x4_t*>(&wslab[l32 * 256 + ((ch ^ (l32 & 15)) << 4)]);
+      const u32x4_t xa = *reinterpret_cast<const u32x4_t*>(&slab[srow * 256 + ((ch ^ (srow & 15)) << 4)]);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wa),
+                                                    __builtin_bit_cast(bf16x8_t, xa), acc, 0, 0, 0);
+    }
+  }
+  if constexpr (kParts > 1) {  // add the channel parts, part 0 first
+#pragma unroll
+    for (int rr = 0; rr < 16; ++rr) sums[(wave * 16 + rr) * 64 + lane] = acc[rr];
+    __syncthreads();
+    if (wpart > 0) return;
+#pragma unroll
+    for (int rr = 0; rr < 16; ++rr)
+#pragma unroll
+      for (int pt = 1; pt < kParts; ++pt) acc[rr] += sums[((pt * kTiles + wtile) * 16 + rr) * 64 + lane];
+  }
+  const int m = tb + srow;
+  if (m < M) {
+    int64_t arow = m;  // row of (gate 0, token m) in a
+    if (!P.ragged) {
+      const int b = m / P.rows;
+      arow = (int64_t)b * H * P.rows + (m - b * P.rows);
+    }
+    const int64_t hstride = P.ragged ? (int64_t)M : (int64_t)P.rows;
+#pragma unroll
+    for (int rr = 0; rr < 16; ++rr) {
+      const int gi = 8 * (rr >> 2) + 4 * half + (rr & 3);
+      if (gi < H) a[arow + gi * hstride] = (uint16_t)pack_bf16x2(acc[rr], 0.0f);
+    }
   }
 }
 
@@ -589,8 +689,9 @@ proj_kernel(LayerPlan P, const uint16_t* __restrict__ xt, const uint16_t* __rest
 }
 
 // ---------------------------------------------------------------------------
-// gate_kernel: the gate logits a = Xt w_g^T (the last H rows of Wp), rounded
-// to bf16, in the [B, H, L] / [H, T] layout.  H outputs per token make this a
+// gate_kernel: the gate logits from the 33rd on (conv_gate_kernel forms the
+// first 32), a = Xt w_g^T (the last H rows of Wp), rounded to bf16, in the [B,
+// H, L] / [H, T] layout.  H outputs per token make this a
 // pass over Xt rather than a GEMM tile: in the projection kernel they would
 // fill a 256-feature tile for 16 features.  A workgroup takes 128 tokens; per
 // step of 128 model channels its threads load the 128 x 256-byte slab with
@@ -647,7 +748,7 @@ gate_kernel(LayerPlan P, const uint16_t* __restrict__ xt, const uint16_t* __rest
   // d_model is a multiple of 64: the last step may be half empty, its
   // channels past d_model read as zeros (out-of-range offsets)
   const int nk = (K + 127) / 128;
-  for (int g0 = 0; g0 < H; g0 += 32) {
+  for (int g0 = 32; g0 < H; g0 += 32) {
     f32x16_t acc = {};
     u32x4_t x[10];
     load(0, g0, x);
@@ -696,8 +797,12 @@ gbla_status launch_project(const LayerPlan& p, const void* x, const float* conv_
   if (p.tokens == 0) return GBLA_OK;
   const int64_t tiles = (int64_t)((4 * p.heads * p.d + kBN - 1) / kBN) * ((p.tokens + kBM - 1) / kBM);
   if (tiles > 2147483647LL) return GBLA_ERR_UNSUPPORTED;  // the grid's x extent; nothing enqueued
-  hipLaunchKernelGGL(conv_x_kernel, dim3((p.d_model + 127) / 128, (p.tokens + 16 * kConvRun - 1) / (16 * kConvRun)),
-                     dim3(kThreads), 0, st, p, (const uint16_t*)x, conv_x, cu, (uint16_t*)xt);
+  // the largest token tile that still gives the chip two workgroups per CU (at
+  // one per CU, 16384 tokens, TM = 64 takes 31 us and TM = 32 27)
+  const int tm = p.tokens >= 128 * 512 ? 128 : p.tokens >= 64 * 512 ? 64 : 32;
+  auto* const conv = tm == 128 ? conv_gate_kernel<128> : tm == 64 ? conv_gate_kernel<64> : conv_gate_kernel<32>;
+  hipLaunchKernelGGL(conv, dim3((unsigned)((p.tokens + (int64_t)tm - 1) / tm)), dim3(kThreads), 0, st, p,
+                     (const uint16_t*)x, conv_x, cu, (const uint16_t*)w_proj, (uint16_t*)xt, (uint16_t*)a);
   // one workgroup per CU (256 on MI355X), each owning every 256th tile; a
   // multiple of 8 keeps tile L on XCD L % 8
   const dim3 grid((unsigned)(tiles < kProjGrid ? tiles : kProjGrid));
@@ -709,7 +814,8 @@ gbla_status launch_project(const LayerPlan& p, const void* x, const float* conv_
   hipLaunchKernelGGL(defer ? proj_kernel<true> : proj_kernel<false>, grid, dim3(kProjThreads), 0, st, p,
                      (const uint16_t*)xt, (const uint16_t*)w_proj, (uint16_t*)q, (uint16_t*)k,
                      (uint16_t*)v, (uint16_t*)r);
-  hipLaunchKernelGGL(gate_kernel, dim3((unsigned)((p.tokens + kGateTokens - 1) / kGateTokens)), dim3(kThreads), 0,
+  if (p.heads > 32)
+    hipLaunchKernelGGL(gate_kernel, dim3((unsigned)((p.tokens + kGateTokens - 1) / kGateTokens)), dim3(kThreads), 0,
                      st, p, (const uint16_t*)xt, (const uint16_t*)w_proj, (uint16_t*)a);
   return hipGetLastError() == hipSuccess ? GBLA_OK : GBLA_ERR_HIP;
 }

@@ -6,7 +6,7 @@
 // g) = (lane & 15, lane >> 4) holds the D/16 channels slot_chan(b, n), b < D/16, of
 // the four consecutive tokens 4 g + i, i < 4.
 //   - The conv window of its tokens is the lane's own seven rows (three of
-//     them loaded again from L1), so the conv and its transpose slide through
+//     them loaded again from L1), so the conv slides through
 //     registers with no cross-lane traffic.  A layout with one token per lane
 //     needed two DPP moves per tap and channel: 12 vector instructions per
 //     element against 6.

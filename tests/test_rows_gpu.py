@@ -1,12 +1,14 @@
-"""The fp32-product kernels (channel layout) at the edges of their tiles: 16
-tokens a wave and tile, four waves a unit, units of 64 to 512 tokens chosen by
-the batch's size.  Forward (fp32) and backward (both dtypes) against the fp64
-oracles, with the tolerances of test_parity_gpu.py and test_backward_gpu.py.
+"""The channel-layout kernels at the edges of their tiles: 16 tokens a wave in
+the fp32 forward, 32 in the backward's split products, units of 64 to 512 tokens
+chosen by the batch's size; the one-launch forward; the layer's conv and gate
+pass.  Against the fp64 oracles, with the tolerances of test_parity_gpu.py,
+test_backward_gpu.py and test_layer_gpu.py.
 """
 import pytest
 import torch
 
 from paper_2606_07317_amd import inputs
+from tests import test_layer_gpu
 from tests.test_backward_gpu import NAMES, TOL, close_scaled, run_backward
 from tests.test_parity_gpu import close, say, small
 
@@ -120,3 +122,23 @@ def test_short_forward_dense(G, dev, orc, d, dtype):
         y = G.forward(t["q"], t["k"], t["v"], t["a"], t["r"], t["conv_w"], t["gamma"], eps=inp.eps)
         torch.cuda.synchronize()
         close(y.cpu().numpy(), orc.forward_inputs(inp)["y"], 1e-5 if dtype == inputs.F32 else 2e-2, "y")
+
+
+# The layer's conv and gate logits in one pass: token tiles of 64 (32768 to
+# 65535 tokens; test_layer_gpu.py has tiles of 32 and 128), sequences ending in
+# and on a tile's runs, a half-empty last channel step, and gates past the 32nd,
+# which a kernel of their own forms.
+LAYER_CASES = {
+    "tile64": dict(lens=[1, 32767, 3, 0, 60, 129, 2, 5], d_model=192, heads=2, head_dim=32, conv_width=3),
+    "tile64_full_width": dict(lens=[32764, 4, 1], d_model=256, heads=1, head_dim=64, conv_width=4),
+    "gates40": dict(lens=[33, 95, 7], d_model=64, heads=40, head_dim=32, conv_width=4),
+}
+
+
+@pytest.mark.parametrize("name", list(LAYER_CASES))
+def test_layer_conv_gate(G, dev, monkeypatch, name):
+    kw = dict(LAYER_CASES[name])
+    lens = kw.pop("lens")
+    w = inputs.LayerWorkload("conv gate " + name, batch=len(lens), seqlen=0, seed=55, ragged=True, **kw)
+    monkeypatch.setitem(test_layer_gpu.CASES, name, (w, lens))
+    test_layer_gpu.test_layer_project_parity(G, dev, name)
