@@ -689,6 +689,100 @@ proj_kernel(LayerPlan P, const uint16_t* __restrict__ xt, const uint16_t* __rest
 }
 
 // ---------------------------------------------------------------------------
+// proj_small_kernel: the same products on 128 x 128 tiles, one per workgroup,
+// where proj_kernel's 256 x 256 tiles would leave CUs idle.  Four waves (2 x 2)
+// of 64 x 64; K steps of 64 channels through two LDS stages in registers one
+// step ahead, one barrier a step.  The tile goes out through LDS: 16 bytes a
+// lane, whole lines (H d is a multiple of 32, so a tile has no feature past the
+// last and 8 features lie in one head).  The products of an element run in
+// proj_kernel's order, so the bits are the same.
+// ---------------------------------------------------------------------------
+constexpr int kSmallTile = 128;
+
+__global__ void __launch_bounds__(kThreads, 2)
+proj_small_kernel(LayerPlan P, const uint16_t* __restrict__ xt, const uint16_t* __restrict__ wp,
+                  uint16_t* __restrict__ q, uint16_t* __restrict__ k, uint16_t* __restrict__ v,
+                  uint16_t* __restrict__ r) {
+  constexpr int kTile = kSmallTile * kRowBytes;  // one operand's stage: 128 rows of 64 channels
+  __shared__ __attribute__((aligned(16))) unsigned char lds[4 * kTile];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
+  const int Hd = P.heads * P.d, K = P.d_model, M = P.tokens, N = 4 * Hd;
+  const int tiles_n = N / kSmallTile;
+  const int n0 = (int)(blockIdx.x % tiles_n) * kSmallTile, m0 = (int)(blockIdx.x / tiles_n) * kSmallTile;
+  // rows past the last token read zeros and are not written
+  const __amdgpu_buffer_rsrc_t rx = make_rsrc(xt, (uint32_t)((int64_t)M * K * 2));
+  const __amdgpu_buffer_rsrc_t rw = make_rsrc(wp, (uint32_t)((int64_t)N * K * 2));
+  const int lrow = tid >> 3, lch = tid & 7;
+  u32x4_t gx[4], gw[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      gx[j] = bload(rx, ((uint32_t)(m0 + lrow + 32 * j) * (uint32_t)K + (uint32_t)(k0 + 8 * lch)) * 2u);
+      gw[j] = bload(rw, ((uint32_t)(n0 + lrow + 32 * j) * (uint32_t)K + (uint32_t)(k0 + 8 * lch)) * 2u);
+    }
+  };
+  f32x16_t acc[2][2] = {};
+  const int nk = K / 64;
+  load(0);
+  for (int s = 0; s < nk; ++s) {
+    unsigned char* const st = lds + (s & 1) * 2 * kTile;  // last read two steps ago, a barrier between
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      *reinterpret_cast<u32x4_t*>(st + tile_off(lrow + 32 * j, lch)) = gx[j];
+      *reinterpret_cast<u32x4_t*>(st + kTile + tile_off(lrow + 32 * j, lch)) = gw[j];
+    }
+    if (s + 1 < nk) load(64 * (s + 1));
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      u32x4_t fa[2], fb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        fa[i] = *reinterpret_cast<const u32x4_t*>(st + tile_off(64 * wm + 32 * i + l32, 2 * ks + half));
+        fb[i] = *reinterpret_cast<const u32x4_t*>(st + kTile + tile_off(64 * wn + 32 * i + l32, 2 * ks + half));
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fb[j]),
+                                                              __builtin_bit_cast(bf16x8_t, fa[i]), acc[i][j], 0, 0, 0);
+    }
+  }
+  __syncthreads();  // every wave done reading the stages
+  // 128 token rows of 256 bytes, 16-byte chunks XOR-swizzled by the token
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        const int row = 64 * wm + 32 * i + l32, ch = (8 * wn + 4 * j + gq) ^ (row & 15);
+        *reinterpret_cast<u32x2_t*>(lds + row * 256 + ch * 16 + 8 * half) =
+            u32x2_t{pack_bf16x2(acc[i][j][4 * gq], acc[i][j][4 * gq + 1]),
+                    pack_bf16x2(acc[i][j][4 * gq + 2], acc[i][j][4 * gq + 3])};
+      }
+  __syncthreads();
+  const int ch = tid & 15, nf = n0 + 8 * ch, blk = nf / Hd, h = (nf % Hd) / P.d, e = nf % P.d;
+  uint16_t* const dst = blk == 0 ? q : blk == 1 ? k : blk == 2 ? v : r;
+  const int64_t hstride = P.ragged ? (int64_t)M : (int64_t)P.rows;  // rows between heads
+#pragma unroll
+  for (int ps = 0; ps < 8; ++ps) {
+    const int row = (tid >> 4) + 16 * ps, m = m0 + row;
+    if (m >= M) continue;
+    int64_t trow = m;
+    if (!P.ragged) {
+      const int b = m / P.rows;
+      trow = (int64_t)b * P.heads * P.rows + (m - b * P.rows);
+    }
+    *reinterpret_cast<u32x4_t*>(dst + (trow + h * hstride) * P.d + e) =
+        *reinterpret_cast<const u32x4_t*>(lds + row * 256 + ((ch ^ (row & 15)) * 16));
+  }
+}
+
+// ---------------------------------------------------------------------------
 // gate_kernel: the gate logits from the 33rd on (conv_gate_kernel forms the
 // first 32), a = Xt w_g^T (the last H rows of Wp), rounded to bf16, in the [B,
 // H, L] / [H, T] layout.  H outputs per token make this a
@@ -811,9 +905,21 @@ gbla_status launch_project(const LayerPlan& p, const void* x, const float* conv_
   const bool defer = p.d_model % 1024 == 0 && (p.heads * p.d) % 256 == 0 &&
                      (p.ragged || p.rows % kBM == 0) &&
                      (int64_t)p.tokens * p.heads * p.d * 2 < (int64_t(1) << 31);
-  hipLaunchKernelGGL(defer ? proj_kernel<true> : proj_kernel<false>, grid, dim3(kProjThreads), 0, st, p,
-                     (const uint16_t*)xt, (const uint16_t*)w_proj, (uint16_t*)q, (uint16_t*)k,
-                     (uint16_t*)v, (uint16_t*)r);
+  // Small tiles while the large ones leave CUs idle, and further where those
+  // write their output without the deferred stores.  Conv, gates and
+  // projections, large / small, tiles of 256: d_model = 1024, H = 16: 32 tiles
+  // 43 / 33 us, 128 51 / 47, 240 57 / 67, 512 90 / 118; d_model = 256, H = 4: 8
+  // tiles 22 / 13, 124 28 / 23, 252 38 / 35, 472 60 / 56; d_model = 512, H = 8:
+  // 376 tiles 66 / 58.
+  const int64_t small = (int64_t)(4 * p.heads * p.d / kSmallTile) * ((p.tokens + kSmallTile - 1) / kSmallTile);
+  if (tiles <= (defer ? 128 : 512)) {
+    hipLaunchKernelGGL(proj_small_kernel, dim3((unsigned)small), dim3(kThreads), 0, st, p, (const uint16_t*)xt,
+                       (const uint16_t*)w_proj, (uint16_t*)q, (uint16_t*)k, (uint16_t*)v, (uint16_t*)r);
+  } else {
+    hipLaunchKernelGGL(defer ? proj_kernel<true> : proj_kernel<false>, grid, dim3(kProjThreads), 0, st, p,
+                       (const uint16_t*)xt, (const uint16_t*)w_proj, (uint16_t*)q, (uint16_t*)k,
+                       (uint16_t*)v, (uint16_t*)r);
+  }
   if (p.heads > 32)
     hipLaunchKernelGGL(gate_kernel, dim3((unsigned)((p.tokens + kGateTokens - 1) / kGateTokens)), dim3(kThreads), 0,
                      st, p, (const uint16_t*)xt, (const uint16_t*)w_proj, (uint16_t*)a);

@@ -132,6 +132,12 @@ LAYER_CASES = {
     "tile64": dict(lens=[1, 32767, 3, 0, 60, 129, 2, 5], d_model=192, heads=2, head_dim=32, conv_width=3),
     "tile64_full_width": dict(lens=[32764, 4, 1], d_model=256, heads=1, head_dim=64, conv_width=4),
     "gates40": dict(lens=[33, 95, 7], d_model=64, heads=40, head_dim=32, conv_width=4),
+    # projections on 128 x 128 tiles: one full tile and one feature tile, one K
+    # step; a last tile of one token; and, past them, deferred stores over 32 K
+    # steps (17 x 16 tiles of 256)
+    "small_tile": dict(lens=[100, 28], d_model=64, heads=1, head_dim=32, conv_width=2),
+    "small_tile_rest": dict(lens=[257], d_model=320, heads=3, head_dim=128, conv_width=4),
+    "deferred_long": dict(lens=[4099, 2], d_model=2048, heads=8, head_dim=128, conv_width=3),
 }
 
 
