@@ -867,28 +867,30 @@ struct ConvRun {
   }
 };
 
-// One element per thread while the grid stays small, four or sixteen once
+// bf16: one element per thread while the grid stays small, four or sixteen once
 // there are many (sequence, head) pairs (fewer workgroups, each with more
-// loads in flight).  fp32 (the backward's 512-token units, so more partials a
-// pair) keeps one element longer: 128 pairs of d = 128, 57,511 tokens 31 us
-// against 48 with four.  The result does not depend on the choice.
+// loads in flight and whole fragment slots to write).  fp32 (the backward's
+// 512-token units, so more partials a pair): always one; 128 pairs of d = 128,
+// 57,511 tokens 31 us against 48 with four; 512 pairs, 177,929 tokens 123 us
+// against 244 with sixteen.  The result does not depend on the choice.
 template <typename T, int D>
 gbla_status run_combine(const Plan& p, const int32_t* cu, const float* partials, float* S,
                         float* z, unsigned char* frags, float* mz, hipStream_t st) {
   constexpr int kElems = D * D + D;
   const int64_t pairs = (int64_t)p.nseq * p.heads;
   const int slices1 = (kElems + kThreads - 1) / kThreads;
-  if (pairs * slices1 <= (sizeof(T) == 4 ? 16384 : 4096)) {
+  if (sizeof(T) == 4 || pairs * slices1 <= 4096) {
     hipLaunchKernelGGL((combine_kernel<T, D, 1>), dim3(pairs, slices1), dim3(kThreads), 0, st, p,
                        cu, partials, S, z, frags, mz);
-  } else if (pairs * ((kElems + 4 * kThreads - 1) / (4 * kThreads)) <= 4096) {
+  } else if constexpr (sizeof(T) == 2) {
     const int slices4 = (kElems + 4 * kThreads - 1) / (4 * kThreads);
-    hipLaunchKernelGGL((combine_kernel<T, D, 4>), dim3(pairs, slices4), dim3(kThreads), 0, st, p,
-                       cu, partials, S, z, frags, mz);
-  } else {
     const int slices16 = (kElems + 16 * kThreads - 1) / (16 * kThreads);
-    hipLaunchKernelGGL((combine_kernel<T, D, 16>), dim3(pairs, slices16), dim3(kThreads), 0, st, p,
-                       cu, partials, S, z, frags, mz);
+    if (pairs * slices4 <= 4096)
+      hipLaunchKernelGGL((combine_kernel<T, D, 4>), dim3(pairs, slices4), dim3(kThreads), 0, st, p,
+                         cu, partials, S, z, frags, mz);
+    else
+      hipLaunchKernelGGL((combine_kernel<T, D, 16>), dim3(pairs, slices16), dim3(kThreads), 0, st, p,
+                         cu, partials, S, z, frags, mz);
   }
   return last_launch_status();
 }
