@@ -426,12 +426,12 @@ def main():
     readout_call_ms = statistics.mean(a.elapsed_time(b) for a, b in calls)
     ach = algorithmic_bytes(inp, "readout", keep_gate, keep_norm) / (readout_ms * 1e-3) / 1e9
     fwd_gbps = algorithmic_bytes(inp, "forward", keep_gate, keep_norm) / (ms_per_step * 1e-3) / 1e9
-    # the kernel that ran: the streaming readout for bf16 slices under 2^31
-    # bytes of fp32 output, the generic one otherwise
+    # the kernel that ran: the streaming readout (bf16) or the channel-layout
+    # one (fp32) for slices under 2^31 bytes of fp32 output, the generic one
+    # otherwise
     slice_rows = inp.tokens if w.ragged else w.seqlen
-    readout_kernel = ("readout_stream_kernel"
-                      if w.dtype == "bf16" and slice_rows * w.head_dim * 4 < (1 << 31)
-                      else "readout_kernel")
+    readout_kernel = ("readout_kernel" if slice_rows * w.head_dim * 4 >= (1 << 31)
+                      else "readout_stream_kernel" if w.dtype == "bf16" else "readout_rows_kernel")
 
     res = {
         "metric": METRIC if w.name == inputs.THROUGHPUT_WORKLOAD else "GBLA fwd tokens/sec on " + w.name,
