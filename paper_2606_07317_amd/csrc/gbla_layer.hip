@@ -13,6 +13,8 @@
 //                scattered to the head-major layout the attention kernels
 //                read ([B, H, n, d] / [B, H, n]), written under the next
 //                tile's products where the shape allows.
+// proj_small_kernel  the same products on 128 x 128 tiles, for small batches.
+// gate_kernel    gate logits past the 32nd, from Xt.
 // The conv is a separate pass rather than part of the tile staging: redone
 // for every feature tile, its vector work would compete with the products
 // (measured: 0.36 against 0.54 PFLOP/s for the GEMM), while the pass itself
@@ -691,8 +693,9 @@ proj_kernel(LayerPlan P, const uint16_t* __restrict__ xt, const uint16_t* __rest
 // ---------------------------------------------------------------------------
 // proj_small_kernel: the same products on 128 x 128 tiles, one per workgroup,
 // where proj_kernel's 256 x 256 tiles would leave CUs idle.  Four waves (2 x 2)
-// of 64 x 64; K steps of 64 channels through two LDS stages in registers one
-// step ahead, one barrier a step.  The tile goes out through LDS: 16 bytes a
+// of 64 x 64; K steps of 64 channels, loaded into registers one step ahead,
+// through two LDS stages, one barrier a step.  Bound by the loads' latency and L2
+// (two workgroups a CU); times beside the rule in launch_project.  The tile goes out through LDS: 16 bytes a
 // lane, whole lines (H d is a multiple of 32, so a tile has no feature past the
 // last and 8 features lie in one head).  The products of an element run in
 // proj_kernel's order, so the bits are the same.
