@@ -491,7 +491,10 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
 // unlike the fp32 one, runs beside the vector unit).  As in the other bf16
 // kernels the gated keys, phi(qt) and the readout's S are rounded to bf16 and
 // the values enter without rounding error (here as bf16 + bf16 residue); z stays
-// in fp32.  256 packed sequences, T = 39,470 (5 to 1,019 tokens), H = 8, d = 64:
+// in fp32.  S is normalised by the sum of the gates before it is rounded, as the
+// combine does, so that both forms round the same values: rounded as summed, the
+// output was 4.2e-4 (2-norm) from the three launches' on these sequences, as far
+// as either is from the exact result.  256 packed sequences, T = 39,470 (5 to 1,019 tokens), H = 8, d = 64:
 // 75 us against 164 us for the three launches, whose partial records and
 // operands (70 MB) and one workgroup per CU this avoids; 243 MB of inputs and
 // outputs are 48 us of plain copy.  117 us in sequence order (long_first), 216
@@ -565,6 +568,7 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
     float z[NMB];
 #pragma unroll
     for (int b = 0; b < NMB; ++b) z[b] = 0.0f;
+    float lacc = 0.0f;
     for (int b0 = w0; b0 < w1; b0 += 128) {
       __asm__ volatile("" ::: "memory");  // taps are re-read from LDS, not held
       if (b0 > w0) issue_kv(b0 + 8 * g);
@@ -572,6 +576,8 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         w[j] = b0 + 8 * g + j < len && m != -INFINITY ? __expf(na[j] - m) : 0.0f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) lacc += w[j];
       u32x4_t A[NMB];
 #pragma unroll
       for (int b = 0; b < NMB; ++b) {
@@ -621,6 +627,8 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
       const float zsum = sum_groups(z[b]);
       if (g == 0) red[wave][slot_chan<D>(b, n)] = zsum;
     }
+    lacc = sum_groups(lacc);
+    if (lane == 0) red4[wave] = lacc;
   }
   // the readout's first rows, in flight over the sums
   Row<T, D>(&xq)[11] = xk;
@@ -635,7 +643,9 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
   };
   if (w0 < w1) issue_qr(w0 + 8 * g);
   __syncthreads();
-  if (tid < D) zs[tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+  const float l = (red4[0] + red4[1]) + (red4[2] + red4[3]);
+  const float inv_l = l > 0.0f ? 1.0f / l : 0.0f;
+  if (tid < D) zs[tid] = ((red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid])) * inv_l;
   // B operands of S: vector (nb * KS + ks) * 64 + lane holds S[32 ks + 8 g + i]
   // [slot_chan(nb, n)], i < 8
   constexpr int kPer = (kOps + kThreads - 1) / kThreads;
@@ -646,7 +656,7 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
     const int l = idx & 63, x0 = (32 * ((idx >> 6) % KS) + 8 * (l >> 4)) * D + slot_chan<D>((idx >> 6) / KS, l & 15);
     float v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = buf[x0 + i * D] + buf[D * D + x0 + i * D];
+    for (int i = 0; i < 8; ++i) v[i] = (buf[x0 + i * D] + buf[D * D + x0 + i * D]) * inv_l;
 #pragma unroll
     for (int p = 0; p < 4; ++p) f[u][p] = pack_bf16x2(v[2 * p], v[2 * p + 1]);
   }

@@ -112,6 +112,24 @@ def test_short_forward(G, dev, orc, d, dtype, width, lens, flags):
     assert (run(1) == got).all()
 
 
+def test_short_forward_rounds_as_three_launches(G, dev):
+    """Both forms of the bf16 forward at d = 64 round the same gated keys and the
+    same normalised S (sequences of one state unit; at d = 32 the state kernel's
+    gate maxima are per wave), so they differ where sums an ulp apart round to
+    neighbouring values: a share of about 2^-14, each by 2^-8, so 2^-8 / 2^7 =
+    3e-5 of the output.  Roundings of their own of S would be 4e-4 apart."""
+    say("short forward, rounding")
+    lengths = [0, 1, 2, 31, 33, 64, 65, 127, 128, 200, 255, 256, 90, 100, 7]
+    inp = inputs.make_inputs(_case(64, inputs.BF16, 4, 56, heads=2), lengths=lengths)
+    t = inputs.device_tensors(inp, dev)
+    y = [G.forward(t["q"], t["k"], t["v"], t["a"], t["r"], t["conv_w"], t["gamma"], eps=inp.eps,
+                   cu_seqlens=t["cu_seqlens"], max_seqlen=m).double() for m in (max(lengths), 1 << 20)]
+    torch.cuda.synchronize()
+    rel = float((y[0] - y[1]).norm() / y[1].norm())
+    say("  one launch against three: rel %.2g" % rel)
+    assert 0 < rel < 1e-4  # 0 would mean that one form gave both
+
+
 @pytest.mark.parametrize("d,dtype", [(64, inputs.BF16), (32, inputs.F32)])
 def test_short_forward_dense(G, dev, orc, d, dtype):
     say("short forward, dense", d, dtype)
