@@ -65,10 +65,12 @@ __device__ __forceinline__ float phi_fast(float u) {
 __device__ __forceinline__ float sigmoid_fast(float x) {
   return __builtin_amdgcn_rcpf(1.0f + __expf(-x));
 }
-// x^(-1/2): the hardware's (1 ulp) with one Newton step.
+// x^(-1/2): the hardware's (1 ulp) with one Newton step, which has no value at
+// 0 and infinity (a square sum that overflowed): there the hardware's inf and 0.
 __device__ __forceinline__ float rsqrt_nr(float x) {
   const float r = __builtin_amdgcn_rsqf(x);
-  return fmaf(0.5f * r, fmaf(-x * r, r, 1.0f), r);
+  const float e = fmaf(-x * r, r, 1.0f);
+  return e == e ? fmaf(0.5f * r, e, r) : r;
 }
 __device__ __forceinline__ float dphi_f(float u) { return u > 0.0f ? 1.0f : expf(u); }
 

@@ -54,6 +54,21 @@ def test_backward_edges(G, dev, d, dtype, width, heads):
         close_scaled(got[n], ref[n], TOL[dtype], n)
 
 
+@pytest.mark.parametrize("d,dtype", [(32, inputs.F32), (64, inputs.BF16), (128, inputs.F32)])
+def test_backward_square_overflow(G, dev, d, dtype):
+    """Outputs whose squares overflow fp32 have the norm factor 0, and so have all
+    the gradients."""
+    say("backward, |o|^2 overflows", d, dtype)
+    inp = inputs.make_inputs(_case(d, dtype, 4, 57, heads=2), lengths=[40, 3, 130])
+    t = inputs.device_tensors(inp, dev)
+    dy = torch.from_numpy(inputs.make_cotangent(inp)).to(dev)
+    got = G.backward(t["q"], t["k"], t["v"] * 1e25, t["a"], t["r"], t["conv_w"], t["gamma"], dy, eps=inp.eps,
+                     cu_seqlens=t["cu_seqlens"], max_seqlen=t["max_seqlen"])
+    torch.cuda.synchronize()
+    for n in NAMES:
+        assert bool((got[n] == 0).all()), n
+
+
 @pytest.mark.parametrize("heads", [1, 24])
 @pytest.mark.parametrize("d,width", [(32, 4), (64, 3), (128, 4)])
 def test_fp32_forward_edges(G, dev, orc, d, width, heads):
