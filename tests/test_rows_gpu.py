@@ -69,6 +69,29 @@ def test_backward_square_overflow(G, dev, d, dtype):
         assert bool((got[n] == 0).all()), n
 
 
+@pytest.mark.parametrize("dtype", [inputs.F32, inputs.BF16])
+def test_infinite_sums_stay_infinite(G, dev, dtype):
+    """A state sum that is infinite in one unit is infinite, not NaN, over several:
+    an infinite value leaves the other channels of the norm's output zero, an
+    infinite key (z infinite: dnum = dy / den = 0) the other tokens' dv zero."""
+    say("infinite sums", dtype)
+    inp = inputs.make_inputs(_case(64, dtype, 4, 58, heads=1), lengths=[2600])  # several units, forward and backward
+    t = inputs.device_tensors(inp, dev)
+    conv_w = t["conv_w"].abs()  # every infinite term of one sign
+    rest = dict(eps=inp.eps, cu_seqlens=t["cu_seqlens"], max_seqlen=t["max_seqlen"])
+    v = t["v"].clone()
+    v[0, 5, 3] = float("inf")
+    y = G.forward(t["q"], t["k"], v, t["a"], t["r"], conv_w, t["gamma"], **rest)
+    dy = torch.from_numpy(inputs.make_cotangent(inp)).to(dev)
+    k = t["k"].clone()
+    k[0, 5, 3] = float("inf")
+    g = G.backward(t["q"], k, t["v"], t["a"], None, conv_w, None, dy, flags=G.NO_NORM, **rest)
+    torch.cuda.synchronize()
+    other = [c for c in range(64) if c != 3]
+    assert bool(y[0, :, 3].isnan().all()) and bool((y[0][:, other] == 0).all())
+    assert bool((g["dv"][0, 16:] == 0).all())
+
+
 @pytest.mark.parametrize("heads", [1, 24])
 @pytest.mark.parametrize("d,width", [(32, 4), (64, 3), (128, 4)])
 def test_fp32_forward_edges(G, dev, orc, d, width, heads):
