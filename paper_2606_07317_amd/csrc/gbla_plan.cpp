@@ -70,22 +70,36 @@ bool rows_supported(const Plan& p) {
 // The one-launch forward gives each (sequence, head) one workgroup, so its time
 // is at least the longest sequence's (bf16 d = 64: 5 us + 0.037 us a token, half
 // of that at d = 32; fp32 about twice), while three launches spread long
-// sequences over the chip but take 14 to 25 us for any batch.  Whole forward,
-// one launch against three, H = 8, d = 64 bf16: B = 1 n = 256 15 / 24 us, B = 2
-// n = 512 24 / 26, B = 1 n = 1024 42 / 26; B = 16 n = 1024 56 / 41, B = 64
-// n = 1024 91 / 110, B = 32 n = 2048 111 / 108.  fp32 d = 64: n = 128 16 / 18,
-// n = 256 26 / 19, B = 16 n = 512 49 / 47, B = 32 n = 512 57 / 68, B = 32 n =
-// 1024 105 / 117; d = 32: n = 256 14 / 14, n = 512 23 / 15.  So: lengths up to the
-// first bound, or batches large enough that the longest sequence is a small
-// part of the chip's work.  The kernels are right for any length; max_seqlen
-// only chooses.
+// sequences over the chip but take 14 to 25 us for any batch.  So: lengths up to
+// a first bound, or batches of so many pairs that the longest sequence is a small
+// part of the chip's work.  Whole forward in us, one launch / three:
+//   first bound, H = 8: bf16 d = 64 B = 1 n = 256 15 / 24, B = 2 n = 512 24 / 26,
+//   B = 1 n = 1024 42 / 26; fp32 d = 64 n = 128 16 / 18, n = 256 26 / 19; d = 32
+//   n = 256 14 / 14, n = 512 23 / 15.
+//   bf16 d = 64: 256 pairs n = 1024 56 / 41; 304 n = 1024 66 / 79, n = 2048 138 /
+//   143, n = 3000 202 / 199; 384 n = 3000 214 / 229, n = 4096 281 / 292, n = 8192
+//   567 / 537; 512 n = 8192 664 / 710.
+//   bf16 d = 32: 304 n = 1400 49 / 53, n = 2048 68 / 63; 352 n = 2048 80 / 82; 384
+//   n = 4096 155 / 157, n = 8192 301 / 272; 512 n = 8192 340 / 356.
+//   fp32 d = 64: 128 pairs n = 512 49 / 47; 256 n = 1024 107 / 130, n = 2048 203 /
+//   230, n = 4096 391 / 344; d = 32: 256 n = 2048 98 / 90, n = 4096 192 / 163.
+// A wave sums a quarter of its sequence into one fp32 accumulator, so the error
+// of the sums grows with the length, which that of the three launches'
+// compensated units does not: against 64 bits, fp32 d = 32, 1.67e-7 / 1.55e-7 at
+// n = 2048, 2.5e-7 / 1.8e-7 at 8192, 3.3e-7 / 1.9e-7 at 16384.  So at most 2048
+// tokens (a unit's) in fp32; in bf16, where roundings of the operands are 4.5e-4,
+// 8192, which keeps a wave's sum to a unit's tokens.  max_seqlen only chooses.
 bool short_forward(const Plan& p) {
   if (!rows_supported(p) || p.d == 128) return false;
   const bool bf16 = p.dtype == GBLA_BF16;
   const int64_t longest = p.ragged ? p.max_seqlen : p.rows;
   if ((int64_t)p.nseq * p.heads > kMaxGridX) return false;
   if (longest <= (bf16 ? 512 : p.d == 64 ? 128 : 256)) return true;
-  return longest * (bf16 ? 300 : 256) <= p.tokens * p.heads;
+  if (longest > (bf16 ? 4 * kMaxChunk : kMaxChunk)) return false;
+  int64_t pairs = 256;
+  if (bf16) pairs = p.d == 32 && longest > 1536 ? 352 : 300;
+  if (longest > kMaxChunk) pairs += (longest - kMaxChunk) / 32;
+  return longest * pairs <= p.tokens * p.heads;
 }
 
 gbla_status make_plan(const gbla_shape* s, bool ragged, Plan* p) {

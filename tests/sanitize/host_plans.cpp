@@ -124,9 +124,38 @@ void drive_layer(int32_t B, int32_t L, int32_t dm, int32_t H, int32_t d, int32_t
   }
 }
 
+// Whether the forward of B sequences of n tokens takes one launch (dense), or
+// does with max_seqlen = n over B * n packed tokens (ragged).
+bool one_launch(bool ragged, int32_t B, int32_t H, int32_t n, int32_t d, int32_t dtype) {
+  const gbla_shape s = shape(B, H, ragged ? B * n : n, d, 4, ragged ? n : 0, dtype);
+  gbla::Plan p;
+  REQUIRE(gbla::make_plan(&s, ragged, &p) == GBLA_OK);
+  return gbla::short_forward(p);
+}
+
+void choices() {
+  for (int r = 0; r < 2; ++r) {
+    // short sequences, whatever their number
+    REQUIRE(one_launch(r, 1, 1, 512, 64, GBLA_BF16) && one_launch(r, 3, 2, 1, 32, GBLA_BF16));
+    REQUIRE(one_launch(r, 2, 2, 128, 64, GBLA_F32) && one_launch(r, 2, 2, 256, 32, GBLA_F32));
+    REQUIRE(!one_launch(r, 1, 1, 513, 64, GBLA_BF16) && !one_launch(r, 2, 2, 129, 64, GBLA_F32));
+    REQUIRE(!one_launch(r, 2, 2, 64, 128, GBLA_BF16) && !one_launch(r, 2, 2, 64, 128, GBLA_F32));
+    // longer ones where the pairs are many
+    REQUIRE(one_launch(r, 75, 4, 2048, 64, GBLA_BF16) && !one_launch(r, 74, 4, 2048, 64, GBLA_BF16));
+    REQUIRE(one_launch(r, 75, 4, 1536, 32, GBLA_BF16) && !one_launch(r, 75, 4, 1537, 32, GBLA_BF16));
+    REQUIRE(one_launch(r, 64, 4, 2048, 64, GBLA_F32) && !one_launch(r, 63, 4, 2048, 64, GBLA_F32));
+    // and no sums over more tokens than the precision allows
+    for (int32_t d = 32; d <= 64; d += 32) {
+      REQUIRE(one_launch(r, 600, 4, 8192, d, GBLA_BF16) && !one_launch(r, 600, 4, 8193, d, GBLA_BF16));
+      REQUIRE(one_launch(r, 600, 4, 2048, d, GBLA_F32) && !one_launch(r, 600, 4, 2049, d, GBLA_F32));
+    }
+  }
+}
+
 }  // namespace
 
 int main() {
+  choices();
   const int32_t dims[3] = {32, 64, 128};
   for (int32_t d : dims) {
     for (int32_t W = 1; W <= 4; ++W) drive(shape(1, 8, 32768, d, W));

@@ -4,6 +4,7 @@ chosen by the batch's size; the one-launch forward; the layer's conv and gate
 pass.  Against the fp64 oracles, with the tolerances of test_parity_gpu.py,
 test_backward_gpu.py and test_layer_gpu.py.
 """
+import numpy as np
 import pytest
 import torch
 
@@ -178,6 +179,28 @@ def test_short_forward_dense(G, dev, orc, d, dtype):
         y = G.forward(t["q"], t["k"], t["v"], t["a"], t["r"], t["conv_w"], t["gamma"], eps=inp.eps)
         torch.cuda.synchronize()
         close(y.cpu().numpy(), orc.forward_inputs(inp)["y"], 1e-5 if dtype == inputs.F32 else 2e-2, "y")
+
+
+@pytest.mark.parametrize("d,dtype,n,tol", [
+    (32, inputs.F32, 2048, 2.0e-7), (64, inputs.F32, 2048, 2.0e-7), (32, inputs.BF16, 8192, 7e-4),
+    (64, inputs.BF16, 8192, 5e-4), (32, inputs.F32, 16384, 2.3e-7), (64, inputs.F32, 16384, 2.3e-7)])
+def test_error_does_not_grow_with_length(G, dev, orc, d, dtype, n, tol):
+    """Many pairs of long sequences: the longest that one launch takes, and those
+    past it.  Measured, 2-norm of the error over that of the result: fp32 1.67e-7
+    at n = 2048, 1.9e-7 at 16384 (uncompensated sums over the sequence: 3.2e-7 and
+    2.6e-7); bf16 6.3e-4 (d = 32) and 4.5e-4, the rounding of S."""
+    say("long sequences, many pairs", d, dtype, n)
+    inp = inputs.make_inputs(small("b8_n2048_d64", batch=1, heads=8, seqlen=n, head_dim=d, dtype=dtype, seed=59))
+    ref = orc.forward_inputs(inp)["y"][0]
+    t = inputs.device_tensors(inp, dev)
+    B = 70 if dtype == inputs.BF16 else 33  # 560 or 264 pairs, all sequences alike
+    q, k, v, a, r = (t[x].expand(B, *t[x].shape[1:]).contiguous() for x in ("q", "k", "v", "a", "r"))
+    y = G.forward(q, k, v, a, r, t["conv_w"], t["gamma"], eps=inp.eps)
+    torch.cuda.synchronize()
+    for b in (0, B - 1):
+        err = np.linalg.norm(y[b].cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+        say("  rel %.3g" % err)
+        assert err < tol
 
 
 # The layer's conv and gate logits in one pass: token tiles of 64 (32768 to
