@@ -908,14 +908,20 @@ gbla_status launch_project(const LayerPlan& p, const void* x, const float* conv_
   const bool defer = p.d_model % 1024 == 0 && (p.heads * p.d) % 256 == 0 &&
                      (p.ragged || p.rows % kBM == 0) &&
                      (int64_t)p.tokens * p.heads * p.d * 2 < (int64_t(1) << 31);
-  // Small tiles while the large ones leave CUs idle, and further where those
-  // write their output without the deferred stores.  Conv, gates and
-  // projections, large / small, tiles of 256: d_model = 1024, H = 16: 32 tiles
-  // 43 / 33 us, 128 51 / 47, 240 57 / 67, 512 90 / 118; d_model = 256, H = 4: 8
-  // tiles 22 / 13, 124 28 / 23, 252 38 / 35, 472 60 / 56; d_model = 512, H = 8:
-  // 376 tiles 66 / 58.
+  // Small tiles while the large ones leave CUs idle, and, where those write their
+  // output without the deferred stores, in their first two rounds of 256.  A
+  // round of small tiles does the work of 128 large ones.  With many K steps two
+  // of them take longer than a round of large tiles, so there the small ones are
+  // for a last round that is at most half full; with few, the large tiles' stores
+  // decide and the small ones win almost anywhere.  Whole layer, small over
+  // large, at 128 / 208 / 256 / 320 / 512 tiles of 256: d_model = 256 0.84 / 0.98
+  // / 0.89 / 0.85 / 0.88, 512 0.89 / 1.04 / 0.97 / 0.89 / 0.96, 768 0.91 / 1.07 /
+  // 1.01 / 0.92 / 1.02 (with H d = 768 204 tiles 1.03, 408 and 504 0.92), 1024
+  // 0.92 / 1.09 / 1.02 / 0.93 / 1.06, 1536 0.92 / 1.11 / 1.09 / 0.96 / 1.12, 4096
+  // 0.96 / 1.23 / 1.16 / 0.99 / 1.18 (H d = 256; with 1024 the same to 0.05);
+  // deferred, d_model = 1024, 128 tiles 0.92, 144 1.04, 208 1.13.
   const int64_t small = (int64_t)(4 * p.heads * p.d / kSmallTile) * ((p.tokens + kSmallTile - 1) / kSmallTile);
-  if (tiles <= (defer ? 128 : 512)) {
+  if (tiles <= (defer ? 128 : 512) && (p.d_model <= 768 || (tiles - 1) % 256 < 128)) {
     hipLaunchKernelGGL(proj_small_kernel, dim3((unsigned)small), dim3(kThreads), 0, st, p, (const uint16_t*)xt,
                        (const uint16_t*)w_proj, (uint16_t*)q, (uint16_t*)k, (uint16_t*)v, (uint16_t*)r);
   } else {
