@@ -609,7 +609,10 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
           hi[p] = pack_bf16x2(vt[2 * p], vt[2 * p + 1]);
-          lo[p] = pack_bf16x2(vt[2 * p] - bf16_lo(hi[p]), vt[2 * p + 1] - bf16_hi(hi[p]));
+          // no residue is below -2^120; that of an infinite value is NaN, which
+          // fmaxf replaces: its products stay infinite
+          lo[p] = pack_bf16x2(fmaxf(vt[2 * p] - bf16_lo(hi[p]), -0x1p120f),
+                              fmaxf(vt[2 * p + 1] - bf16_hi(hi[p]), -0x1p120f));
         }
 #pragma unroll
         for (int mb = 0; mb < NMB; ++mb) {

@@ -70,6 +70,25 @@ def test_backward_square_overflow(G, dev, d, dtype):
         assert bool((got[n] == 0).all()), n
 
 
+def norm_of_infinite(y):
+    """The output where channel 3 of o is infinite: the norm factor is 0."""
+    other = [c for c in range(y.shape[-1]) if c != 3]
+    assert bool(y[:, 3].isnan().all()) and bool((y[:, other] == 0).all())
+
+
+@pytest.mark.parametrize("d,dtype", [(32, inputs.F32), (64, inputs.F32), (32, inputs.BF16), (64, inputs.BF16)])
+def test_short_forward_infinite_value(G, dev, d, dtype):
+    say("short forward, infinite value", d, dtype)
+    inp = inputs.make_inputs(_case(d, dtype, 4, 60, heads=1), lengths=[40, 100])
+    t = inputs.device_tensors(inp, dev)
+    t["v"][0, 45, 3] = float("inf")
+    y = G.forward(t["q"], t["k"], t["v"], t["a"], t["r"], t["conv_w"].abs(), t["gamma"], eps=inp.eps,
+                  cu_seqlens=t["cu_seqlens"], max_seqlen=100)
+    torch.cuda.synchronize()
+    assert bool(y[0, :40].isfinite().all())
+    norm_of_infinite(y[0, 40:])
+
+
 @pytest.mark.parametrize("dtype", [inputs.F32, inputs.BF16])
 def test_infinite_sums_stay_infinite(G, dev, dtype):
     """A state sum that is infinite in one unit is infinite, not NaN, over several:
@@ -88,8 +107,7 @@ def test_infinite_sums_stay_infinite(G, dev, dtype):
     k[0, 5, 3] = float("inf")
     g = G.backward(t["q"], k, t["v"], t["a"], None, conv_w, None, dy, flags=G.NO_NORM, **rest)
     torch.cuda.synchronize()
-    other = [c for c in range(64) if c != 3]
-    assert bool(y[0, :, 3].isnan().all()) and bool((y[0][:, other] == 0).all())
+    norm_of_infinite(y[0])
     assert bool((g["dv"][0, 16:] == 0).all())
 
 
