@@ -150,6 +150,18 @@ void choices() {
       REQUIRE(one_launch(r, 600, 4, 2048, d, GBLA_F32) && !one_launch(r, 600, 4, 2049, d, GBLA_F32));
     }
   }
+  // state units of the fp32 forward and units of the backward, by tokens x heads
+  // (2691 x 24: records of 128-token units past the fixed scratch)
+  const struct { int32_t T, H, fwd, bwd; } units[] = {
+      {2691, 1, 64, 64},       {2691, 13, 128, 256},    {2691, 24, 256, 256},    {2691, 25, 256, 512},    {16383, 1, 64, 64},
+      {16384, 1, 64, 128},     {65535, 1, 128, 256},    {65536, 1, 128, 512},    {16579, 5, 256, 512},
+      {16579, 10, 512, 512},   {16579, 20, 1024, 512},  {16579, 34, 2048, 512},  {1 << 20, 8, 2048, 512}};
+  for (const auto& u : units) {
+    const gbla_shape s = shape(13, u.H, u.T, 64, 4, u.T, GBLA_F32);
+    gbla::Plan p, b;
+    REQUIRE(gbla::make_plan(&s, true, &p) == GBLA_OK && gbla::backward_plan(p, &b) == GBLA_OK);
+    REQUIRE(p.chunk == u.fwd && b.chunk == u.bwd);
+  }
 }
 
 }  // namespace

@@ -1,7 +1,7 @@
 """The channel-layout kernels at the edges of their tiles: 16 tokens a wave in
-the fp32 forward, 32 in the backward's split products, units of 64 to 512 tokens
-chosen by the batch's size; the one-launch forward; the layer's conv and gate
-pass.  Against the fp64 oracles, with the tolerances of test_parity_gpu.py,
+the fp32 forward, 32 in the backward's split products, units of 64 to 512 (the
+backward) or 2048 tokens (the forward) chosen by the batch's size; the one-launch
+forward; the layer's conv and gate pass.  Against the fp64 oracles, with the tolerances of test_parity_gpu.py,
 test_backward_gpu.py and test_layer_gpu.py.
 """
 import numpy as np
@@ -41,11 +41,34 @@ def _case(d, dtype, width, seed, **kw):
     return small("ragged64_d128", head_dim=d, dtype=dtype, conv_width=width, seed=seed, **kw)
 
 
-# heads = 1: units of 64 tokens; heads = 24: units of 512 (fp32 forward: 128)
-@pytest.mark.parametrize("heads", [1, 24])
+def backward_unit(work):
+    """Tokens of the backward's units for `work` tokens x heads."""
+    unit = 512
+    while unit > 64 and work < unit * 128:
+        unit //= 2
+    return unit
+
+
+def fp32_state_unit(lengths, heads, d):
+    """Tokens of the fp32 forward's state units: about 256 workgroups' share, up to
+    d = 64 about 512 workgroups' where the records fit the fixed scratch (d = 64:
+    16,896 bytes a record, 20,480 of operands a pair; d = 32: 4352, 6144)."""
+    pow2 = lambda x: 1 << max(0, (x - 1).bit_length())
+    work = sum(lengths) * heads
+    coarse = min(max(256, pow2((work + 255) // 256)), 2048)
+    fine = max(64, pow2((work + 511) // 512))
+    if d == 128 or fine >= coarse:
+        return coarse
+    rec, ops = {64: (16896, 20480), 32: (4352, 6144)}[d]
+    size = heads * ((sum(lengths) // fine + len(lengths)) * rec + len(lengths) * ops)
+    return fine if size <= 16 << 20 else coarse
+
+
+@pytest.mark.parametrize("heads,unit", [(1, 64), (25, 512)])
 @pytest.mark.parametrize("d,dtype,width", DIMS)
-def test_backward_edges(G, dev, d, dtype, width, heads):
+def test_backward_edges(G, dev, d, dtype, width, heads, unit):
     from oracle import gbla_backward
+    assert backward_unit(sum(EDGES) * heads) == unit
     say("backward edges", d, dtype, width, heads)
     inp = inputs.make_inputs(_case(d, dtype, width, 51, heads=heads), lengths=EDGES)
     dy = inputs.make_cotangent(inp)
@@ -111,16 +134,33 @@ def test_infinite_sums_stay_infinite(G, dev, dtype):
     assert bool((g["dv"][0, 16:] == 0).all())
 
 
-@pytest.mark.parametrize("heads", [1, 24])
-@pytest.mark.parametrize("d,width", [(32, 4), (64, 3), (128, 4)])
-def test_fp32_forward_edges(G, dev, orc, d, width, heads):
-    say("fp32 forward edges", d, width, heads)
-    inp = inputs.make_inputs(_case(d, inputs.F32, width, 52, heads=heads), lengths=EDGES)
+def check_fp32_forward(G, dev, orc, d, width, heads, lengths, seed):
+    inp = inputs.make_inputs(_case(d, inputs.F32, width, seed, heads=heads), lengths=lengths)
     t = inputs.device_tensors(inp, dev)
     y = G.forward(t["q"], t["k"], t["v"], t["a"], t["r"], t["conv_w"], t["gamma"], eps=inp.eps,
                   cu_seqlens=t["cu_seqlens"], max_seqlen=t["max_seqlen"])
     torch.cuda.synchronize()
     close(y.cpu().numpy(), orc.forward_inputs(inp)["y"], 1e-5, "y")
+
+
+@pytest.mark.parametrize("d,width,heads,unit", [(32, 4, 1, 64), (32, 4, 13, 128), (64, 3, 1, 64), (64, 3, 13, 128),
+                                                (128, 4, 1, 256), (128, 4, 24, 256)])
+def test_fp32_forward_edges(G, dev, orc, d, width, heads, unit):
+    say("fp32 forward edges", d, width, heads)
+    assert fp32_state_unit(EDGES, heads, d) == unit
+    check_fp32_forward(G, dev, orc, d, width, heads, EDGES, 52)
+
+
+# lengths about the longer units
+UNIT_EDGES = [2047, 2048, 2049, 2051, 4099, 1, 1023, 1025, 511, 513, 255, 257, 700]
+
+
+@pytest.mark.parametrize("d,width,heads,unit", [(32, 4, 5, 256), (64, 3, 5, 256), (64, 4, 10, 512), (32, 2, 20, 1024),
+                                                (32, 4, 34, 2048), (64, 4, 34, 2048)])
+def test_fp32_forward_long_units(G, dev, orc, d, width, heads, unit):
+    say("fp32 forward, units of", unit, d, width)
+    assert fp32_state_unit(UNIT_EDGES, heads, d) == unit
+    check_fp32_forward(G, dev, orc, d, width, heads, UNIT_EDGES, 61)
 
 
 # One-launch forward: lengths about its tiles (16 tokens fp32, 32 bf16, four
@@ -133,40 +173,55 @@ SHORT_LENGTHS = {
 }
 
 
-@pytest.mark.parametrize("flags", ["", "NO_GATE", "NO_CONV", "NO_NORM", "BLA"])
+SHORT_DIMS = [(32, inputs.F32, 4), (64, inputs.F32, 2), (32, inputs.BF16, 3), (64, inputs.BF16, 4)]
+
+
+def check_forms(G, dev, orc, d, dtype, width, lengths, bounds, flags=0):
+    """The forward with each max_seqlen of `bounds` against the oracle; the bits
+    differ where one takes one launch and the other three."""
+    inp = inputs.make_inputs(_case(d, dtype, width, 53, heads=2), lengths=lengths)
+    t = inputs.device_tensors(inp, dev)
+    a = None if flags & G.NO_GATE else t["a"]
+    cw = None if flags & G.NO_CONV else t["conv_w"]
+    r, gm = (None, None) if flags & G.NO_NORM else (t["r"], t["gamma"])
+    tol = 1e-5 if dtype == inputs.F32 else 2e-2
+    ref = orc.forward_inputs(inp, gate=not flags & G.NO_GATE, conv=not flags & G.NO_CONV,
+                             norm=not flags & G.NO_NORM)["y"]
+    ys = []
+    for m in bounds:
+        y = G.forward(t["q"], t["k"], t["v"], a, r, cw, gm, eps=inp.eps, cu_seqlens=t["cu_seqlens"], max_seqlen=m,
+                      flags=flags)
+        torch.cuda.synchronize()
+        ys.append(y.cpu().numpy())
+        close(ys[-1], ref, tol, "y, max_seqlen %d" % m)
+    assert (ys[0] != ys[1]).any(), "one form gave both"
+
+
 @pytest.mark.parametrize("lens", list(SHORT_LENGTHS))
-@pytest.mark.parametrize("d,dtype,width", [(32, inputs.F32, 4), (64, inputs.F32, 2), (32, inputs.BF16, 3),
-                                           (64, inputs.BF16, 4)])
-def test_short_forward(G, dev, orc, d, dtype, width, lens, flags):
-    """The one-launch forward (max_seqlen given) against the oracle and against
-    the three launches that a loose max_seqlen takes."""
-    if flags and lens != "edges":
-        pytest.skip("the switches run on one set of lengths")
-    say("short forward", d, dtype, width, lens, flags)
+@pytest.mark.parametrize("d,dtype,width", SHORT_DIMS)
+def test_short_forward(G, dev, orc, d, dtype, width, lens):
+    """The one-launch forward (max_seqlen given) and the three launches that a
+    loose max_seqlen takes."""
+    say("short forward", d, dtype, width, lens)
     lengths = SHORT_LENGTHS[lens]
     if dtype == inputs.F32:  # fp32 takes one launch up to 128 (d = 64) or 256 tokens
         lengths = [min(n, 128 if d == 64 else 256) for n in lengths]
-    inp = inputs.make_inputs(_case(d, dtype, width, 53, heads=2), lengths=lengths)
-    t = inputs.device_tensors(inp, dev)
-    fl = getattr(G, flags) if flags else 0
-    a = None if fl & G.NO_GATE else t["a"]
-    cw = None if fl & G.NO_CONV else t["conv_w"]
-    r, gm = (None, None) if fl & G.NO_NORM else (t["r"], t["gamma"])
+    check_forms(G, dev, orc, d, dtype, width, lengths, (max(lengths), 1 << 20))
 
-    def run(max_seqlen):
-        y = G.forward(t["q"], t["k"], t["v"], a, r, cw, gm, eps=inp.eps, cu_seqlens=t["cu_seqlens"],
-                      max_seqlen=max_seqlen, flags=fl)
-        torch.cuda.synchronize()
-        return y.cpu().numpy()
 
-    got = run(max(lengths))
-    tol = 1e-5 if dtype == inputs.F32 else 2e-2
-    ref = orc.forward_inputs(inp, gate=not fl & G.NO_GATE, conv=not fl & G.NO_CONV,
-                             norm=not fl & G.NO_NORM)["y"]
-    close(got, ref, tol, "y")
-    close(run(1 << 20), ref, tol, "y, three launches")
-    # an understated bound only chooses the kernels: the same bits
-    assert (run(1) == got).all()
+@pytest.mark.parametrize("flags", ["NO_GATE", "NO_CONV", "NO_NORM", "BLA"])
+@pytest.mark.parametrize("d,dtype,width", SHORT_DIMS)
+def test_short_forward_switches(G, dev, orc, d, dtype, width, flags):
+    say("short forward", d, dtype, width, flags)
+    check_forms(G, dev, orc, d, dtype, width, SHORT_LENGTHS["edges"], (128, 1 << 20), getattr(G, flags))
+
+
+@pytest.mark.parametrize("d,dtype,width", SHORT_DIMS)
+def test_understated_bound_only_chooses(G, dev, orc, d, dtype, width):
+    """Sequences for which the true max_seqlen takes three launches (more than 512
+    tokens, few pairs) come out the same, to rounding, in one."""
+    say("understated max_seqlen", d, dtype, width)
+    check_forms(G, dev, orc, d, dtype, width, [1100, 3, 600, 0, 40], (1, 1100))
 
 
 def test_short_forward_rounds_as_three_launches(G, dev):
