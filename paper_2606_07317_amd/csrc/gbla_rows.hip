@@ -11,7 +11,6 @@
 namespace gbla {
 namespace {
 
-
 // kFull: the library's expf (the fp32 forward); otherwise the hardware
 // exponential, a few ulp.
 template <bool kFull>
@@ -320,20 +319,19 @@ __device__ __forceinline__ void short_unit(const Plan& P, const int32_t* cu, int
 }
 
 // ---------------------------------------------------------------------------
-// The whole forward of short sequences in one launch: grid (N * H).  A workgroup
+// The whole fp32 forward of short sequences in one launch: grid (N * H).  A workgroup
 // reduces its (sequence, head) to [S; z] as the state kernel does, keeps it in
 // LDS as the readout's operands and reads the sequence out as the readout
 // kernel does.  The gates are not normalised (the factor cancels in o).
 // ---------------------------------------------------------------------------
-template <typename T, int D, bool kNorm>
+template <int D, bool kNorm>
 __global__ void __launch_bounds__(kThreads, 2)
-short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ kin,
-                     const T* __restrict__ vin, const T* __restrict__ ain, const T* __restrict__ rin,
+short_forward_kernel(Plan P, const float* __restrict__ qin, const float* __restrict__ kin,
+                     const float* __restrict__ vin, const float* __restrict__ ain, const float* __restrict__ rin,
                      const float* __restrict__ conv_w, const float* __restrict__ gamma,
                      const int32_t* __restrict__ cu, float* __restrict__ out) {
   using C = CL<D>;
   constexpr int NMB = C::NMB;
-  constexpr bool kFull = sizeof(T) == 4;
   // the waves' sums, then the operands B[c][e] = S[c][e]
   __shared__ __attribute__((aligned(16))) float buf[2 * D * D];
   __shared__ __attribute__((aligned(16))) float stg[4][C::kStage];
@@ -350,7 +348,7 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
   seq_geometry(P, cu, s, h, &len64, &base_row);
   const int len = (int)len64;
   if (len <= 0) return;
-  const uint32_t bytes = (uint32_t)len * (uint32_t)(D * sizeof(T));
+  const uint32_t bytes = (uint32_t)len * (uint32_t)(D * 4);
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(kin + base_row * D, bytes);
   const __amdgpu_buffer_rsrc_t rv = make_rsrc(vin + base_row * D, bytes);
   const __amdgpu_buffer_rsrc_t rq = make_rsrc(qin + base_row * D, bytes);
@@ -358,16 +356,16 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
   const __amdgpu_buffer_rsrc_t ro = make_rsrc(out + base_row * D, (uint32_t)len * (uint32_t)(D * 4));
   // no gate logits: an empty range, so every logit reads as 0
   const __amdgpu_buffer_rsrc_t ra =
-      ain ? make_rsrc(ain + base_row, (uint32_t)len * (uint32_t)sizeof(T)) : make_rsrc(kin, 0u);
+      ain ? make_rsrc(ain + base_row, (uint32_t)len * 4u) : make_rsrc(kin, 0u);
   const int q4 = quarter_tokens(len);
   const int w0 = wave * q4, w1 = min(len, w0 + q4);
-  Window<T, D> nk, nv;
+  Window<float, D> nk, nv;
   float na[4];
   auto issue_kv = [&](int tok) {
     nk.load(rk, tok, n);
     nv.load(rv, tok, n);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) na[i] = load_logit<T>(ra, tok + i);
+    for (int i = 0; i < 4; ++i) na[i] = load_logit<float>(ra, tok + i);
   };
   issue_kv(w0 + 4 * g);
   stage_taps<D>(conv_w, P.heads, h, 0, P.W, tq);
@@ -375,7 +373,7 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
   stage_taps<D>(conv_w, P.heads, h, 2, P.W, tv);
   if (tid < D) gs[tid] = kNorm ? gamma[(size_t)h * D + tid] : 1.0f;
   float ml = -INFINITY;
-  for (int j = tid; j < len; j += kThreads) ml = fmaxf(ml, load_logit<T>(ra, j));
+  for (int j = tid; j < len; j += kThreads) ml = fmaxf(ml, load_logit<float>(ra, j));
   const float m = block_max(ml, red4);  // its barriers also publish the taps
 
   {
@@ -392,13 +390,13 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
       nv.conv(LdsTaps<D>{tv, n}, vt);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        w[i] = b0 + 4 * g + i < len && m != -INFINITY ? gate<kFull>(na[i] - m) : 0.0f;
+        w[i] = b0 + 4 * g + i < len && m != -INFINITY ? gate<true>(na[i] - m) : 0.0f;
       issue_kv(b0 + 16 + 4 * g);  // past the sequence they read 0; unused
 #pragma unroll
       for (int b = 0; b < NMB; ++b)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          kt[b][i] = w[i] * phi<kFull>(kt[b][i]);
+          kt[b][i] = w[i] * phi<true>(kt[b][i]);
           z[b] += kt[b][i];
         }
       token_product<D>(kt, vt, acc);
@@ -412,12 +410,12 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
     }
   }
   // the readout's first rows, in flight over the sums
-  Window<T, D> nq;
-  Row<T, D> nr[4];
+  Window<float, D> nq;
+  Row<float, D> nr[4];
   auto issue_r = [&](int tok) {
-    const uint32_t off = row_off<T, D>(tok, n);
+    const uint32_t off = row_off<float, D>(tok, n);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) nr[i].load(rr, off + (uint32_t)(i * D * sizeof(T)));
+    for (int i = 0; i < 4; ++i) nr[i].load(rr, off + (uint32_t)(i * D * 4));
   };
   nq.load(rq, w0 + 4 * g, n);
   if constexpr (kNorm) issue_r(w0 + 4 * g);
@@ -446,7 +444,7 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
       const float z = zs[slot_chan<D>(b, n)];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        x[b][i] = phi<kFull>(x[b][i]);
+        x[b][i] = phi<true>(x[b][i]);
         den[i] = fmaf(x[b][i], z, den[i]);
       }
     }
@@ -477,7 +475,7 @@ short_forward_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ ki
         for (int b = 0; b < NMB; ++b) {
           const float r = rv4[b][i];
           x[b][i] = x[b][i] * scale * gs[slot_chan<D>(b, n)] *
-                    (r * __builtin_amdgcn_rcpf(1.0f + gate<kFull>(-r)));
+                    (r * __builtin_amdgcn_rcpf(1.0f + gate<true>(-r)));
         }
       }
       store_row<D>(ro, off + (uint32_t)(i * D * 4), x, i);
@@ -805,8 +803,8 @@ gbla_status launch_short_forward(const Plan& p, const void* q, const KeyInputs& 
     if (p.d == 64) { if (norm) GBLA_SHORT(uint16_t, (short_forward_bf16_kernel<64, true>)); else GBLA_SHORT(uint16_t, (short_forward_bf16_kernel<64, false>)); }
     else { if (norm) GBLA_SHORT(uint16_t, (short_forward_bf16_kernel<32, true>)); else GBLA_SHORT(uint16_t, (short_forward_bf16_kernel<32, false>)); }
   } else {
-    if (p.d == 64) { if (norm) GBLA_SHORT(float, (short_forward_kernel<float, 64, true>)); else GBLA_SHORT(float, (short_forward_kernel<float, 64, false>)); }
-    else { if (norm) GBLA_SHORT(float, (short_forward_kernel<float, 32, true>)); else GBLA_SHORT(float, (short_forward_kernel<float, 32, false>)); }
+    if (p.d == 64) { if (norm) GBLA_SHORT(float, (short_forward_kernel<64, true>)); else GBLA_SHORT(float, (short_forward_kernel<64, false>)); }
+    else { if (norm) GBLA_SHORT(float, (short_forward_kernel<32, true>)); else GBLA_SHORT(float, (short_forward_kernel<32, false>)); }
   }
 #undef GBLA_SHORT
   return hipGetLastError() == hipSuccess ? GBLA_OK : GBLA_ERR_HIP;
