@@ -32,7 +32,7 @@ def kernel_source_hash() -> str:
     """Hash of the sources the forward pass is built from (kernels and plan)."""
     h = hashlib.sha256()
     for f in ("gbla_kernels.hip", "gbla_stream.hip", "gbla_state64.hip", "gbla_state128.hip",
-              "gbla_device.h", "gbla_plan.cpp", "gbla_plan.h"):
+              "gbla_rows.hip", "gbla_rows.h", "gbla_device.h", "gbla_plan.cpp", "gbla_plan.h"):
         with open(os.path.join(ROOT, "paper_2606_07317_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -426,9 +426,10 @@ def main():
     readout_call_ms = statistics.mean(a.elapsed_time(b) for a, b in calls)
     ach = algorithmic_bytes(inp, "readout", keep_gate, keep_norm) / (readout_ms * 1e-3) / 1e9
     fwd_gbps = algorithmic_bytes(inp, "forward", keep_gate, keep_norm) / (ms_per_step * 1e-3) / 1e9
-    # the kernel that ran: the streaming readout (bf16) or the channel-layout
-    # one (fp32) for slices under 2^31 bytes of fp32 output, the generic one
-    # otherwise
+    # the kernel of the readout stage timed above: the streaming readout (bf16)
+    # or the channel-layout one (fp32) for slices under 2^31 bytes of fp32 output,
+    # the generic one otherwise (the whole forward of short sequences, as of
+    # tiny_f32, runs one kernel instead: short_forward_kernel)
     slice_rows = inp.tokens if w.ragged else w.seqlen
     readout_kernel = ("readout_kernel" if slice_rows * w.head_dim * 4 >= (1 << 31)
                       else "readout_stream_kernel" if w.dtype == "bf16" else "readout_rows_kernel")

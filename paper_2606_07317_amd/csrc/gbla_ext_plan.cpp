@@ -7,13 +7,13 @@
 namespace gbla {
 namespace {
 
-constexpr int kMinUnit = 64;  // the backward's shortest unit, one tile a wave
+constexpr int kMinUnit = 64;  // the backward's shortest unit, two tiles
 
 }  // namespace
 
 gbla_status backward_plan(const Plan& p, Plan* out) {
   // Units of at most 512 tokens: long enough to amortise each workgroup's
-  // set-up (A operands, the ordered wave sums), short enough for two workgroups
+  // set-up (the constant operands' columns), short enough for two workgroups
   // per CU at n = 32768, H = 8.  Batches that would leave half of the CUs
   // without one take shorter units, down to kMinUnit tokens (whole backward,
   // units of 64 / 128 / 256 tokens: B = 4, n = 999, H = 4, d = 32 fp32 33 / 38 /

@@ -145,8 +145,8 @@ __device__ __forceinline__ int seq_end(const LayerPlan& P, const int32_t* cu, in
 // write): TM = 128 has the fewest halo rows and tap loads per token, shorter
 // tiles fill the chip where there are few tokens.  Measured, d_model = 1024,
 // against the two passes: 262144 tokens 224 us (4.8 TB/s; 357 before; TM = 64:
-// 250, TM = 32: 370), 16384 tokens 27 us (31 before; TM = 64: 31); 7700 tokens,
-// d_model = 256: 10.6 us (17 before).  TM = 128 needs more than the 168
+// 250, TM = 32: 370), 16384 tokens 27 us (31 before; TM = 64: 31); 9662 tokens,
+// d_model = 256: 11 us (17 before).  TM = 128 needs more than the 168
 // registers of three waves a SIMD (spilled: 560 us).
 // ---------------------------------------------------------------------------
 template <int TM>

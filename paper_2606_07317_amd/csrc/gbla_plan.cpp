@@ -139,7 +139,7 @@ gbla_status make_plan(const gbla_shape* s, bool ragged, Plan* p) {
   const size_t lane_bytes = q.dtype == GBLA_BF16 ? 16 : 32;
   q.frag_bytes = align_up(nmb * nkb * 64 * lane_bytes, 256);
   // bf16 readout tiles: 512 tokens, of a small batch down to 128 (four waves of
-  // 32), for a workgroup per CU where the batch has the tokens for it (7700
+  // 32), for a workgroup per CU where the batch has the tokens for it (9662
   // tokens, H = 4, d = 64: readout 10 us, 15 with 512; twice as many workgroups
   // 10, and B = 1, n = 32768, H = 8 then takes 29 us against 28)
   if (q.dtype == GBLA_F32) fp32_split(&q);

@@ -40,7 +40,10 @@ __device__ __forceinline__ float load_logit(__amdgpu_buffer_rsrc_t r, int tok) {
 // Each wave takes a contiguous quarter of the unit's tokens, 16 at a time, and
 // keeps its own D x D sum, so the waves never meet inside the loop; the
 // quarters are added as (w0 + w1) + (w2 + w3).  Measured against the kernel
-// that this replaced: B = 2, n = 8191, H = 8, d = 64 52 -> 29 us.
+// that this replaced: B = 2, n = 8191, H = 8, d = 64 52 -> 29 us.  At d = 128 a
+// wave's sum takes 256 accumulators, so one wave runs on a SIMD and 57 registers
+// spill; the whole forward there took 397 us with the kernels before these and
+// takes 178, n = 1000, H = 4 206 and 58.
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(kThreads, D >= 128 ? 1 : 2)

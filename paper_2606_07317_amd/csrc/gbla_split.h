@@ -1,11 +1,18 @@
 // gbla_split.h -- device helpers of the backward's kernels: products of fp32
-// operands on the bf16 matrix instructions, each operand split exactly into
-// three bf16 parts.
+// operands on the bf16 matrix instructions, each operand split into three bf16
+// parts.
 //
 // x = h + m + l with h, m, l bf16 (8 + 8 + 8 significant bits, rounded to
 // nearest, so the remainders are signed and the third part is exact).  Of the
-// nine products of two operands the three of order 2^-26 and below (m l, l m,
-// l l) are left out: less than the rounding of one fp32 addition.
+// nine products of two operands m l, l m and l l are left out: m l and l m are
+// up to 2^-25 of the product each, 2^-24 together, about the rounding of one
+// fp32 product.
+// The split is exact from about 2^-109 to bf16's largest value, 3.39e38.  Below,
+// the smaller parts leave bf16's normal range and the operand keeps fewer bits.
+// An infinite operand, or one that rounds to bf16's infinity, has NaN for its
+// remainders (inf - inf), so every product that it enters is NaN where fp32
+// products are infinite (or NaN, with a zero); sequences and heads other than its
+// own are not touched.
 // v_mfma_f32_16x16x32_bf16 takes 7.9 ns a SIMD and runs beside the vector unit
 // (two vector instructions hide under each), v_mfma_f32_16x16x4_f32 takes 15 ns
 // and does not: 32 K steps cost 47 ns as six bf16 products and 120 ns in fp32.
@@ -34,11 +41,13 @@ struct SP {
   static constexpr int NW = D / 16;           // waves
   static constexpr int NT = 64 * NW;
   static constexpr int KS = D / 32;           // K steps of a product over channels
-  // Rows of 64 bytes, their 16-byte units at unit ^ (row / 4 % 4): the four rows
-  // of a transposed read and the four that the lane groups beside it read lie on
-  // distinct banks, and so do eight rows of a 16-byte read.  (Rows 80 bytes apart
-  // without the swizzle: two cycles of conflict to three of access, and 61 KB
-  // instead of 49 for two operands at d = 128.)
+  // Rows of 64 bytes, their 16-byte units at unit ^ (row / 4 % 4), so that the
+  // four rows of a transposed read and the four that the lane groups beside it
+  // read lie on distinct banks.  The 16-byte accesses still meet: conflict cycles
+  // per LDS instruction at d = 64 are 3.5 in the state kernel, which has no
+  // others, 1.0 in the query kernel and 0.7 in the key kernel.  (Rows 80 bytes
+  // apart without the swizzle: two cycles of conflict to three of access in the
+  // query kernel, and 61 KB instead of 49 for two operands at d = 128.)
   static constexpr int kPitch = 64;
   static constexpr int kPlane = D * kPitch;
   static constexpr int kOperand = 3 * kPlane;  // bytes of the three planes

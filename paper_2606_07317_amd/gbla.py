@@ -226,6 +226,10 @@ def forward(q, k, v, gate_logits, out_gate, conv_w, norm_w, eps: float = 1e-6,
             flags: int = 0, kernel_events=None) -> torch.Tensor:
     """y = GBLA(q, k, v, a, r) on the GPU (o under NO_NORM); see include/gbla.h
     for the layouts and the ablation switches in ``flags``.
+    ``max_seqlen`` (ragged) is an upper bound of the lengths; the default is T.
+    It only chooses kernels, and decides a factor of two or more for batches of
+    short sequences (d = 32 and 64): with a tight bound they take one launch, whose
+    sums round in another order than the three launches of a loose one.
     ``kernel_events`` = (start, stop) torch.cuda.Events recorded just before
     the pass's first kernel and as its last kernel ends (gbla_forward_timed);
     each must have been recorded once before, so that its HIP event exists."""

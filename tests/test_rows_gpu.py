@@ -93,6 +93,26 @@ def test_backward_square_overflow(G, dev, d, dtype):
         assert bool((got[n] == 0).all()), n
 
 
+def test_backward_infinite_inputs_stay_in_their_sequence(G, dev):
+    """An infinite value or gradient spoils its own sequence and head only."""
+    say("backward, infinite inputs")
+    inp = inputs.make_inputs(_case(64, inputs.F32, 4, 62, heads=2), lengths=[40, 33, 70])
+    t = inputs.device_tensors(inp, dev)
+    dy = torch.from_numpy(inputs.make_cotangent(inp)).to(dev)
+    v2, dy2 = t["v"].clone(), dy.clone()
+    v2[0, 45, 3] = float("inf")    # second sequence, first head
+    dy2[1, 100, 60] = float("inf")  # third sequence, second head
+    a, b = (G.backward(t["q"], t["k"], v, t["a"], t["r"], t["conv_w"], t["gamma"], g, eps=inp.eps,
+                       cu_seqlens=t["cu_seqlens"], max_seqlen=t["max_seqlen"])
+            for v, g in ((t["v"], dy), (v2, dy2)))
+    torch.cuda.synchronize()
+    for n in ("dq", "dk", "dv", "da", "dr"):
+        same = torch.ones(2, 143, dtype=torch.bool, device=dev)
+        same[0, 40:73] = same[1, 73:] = False
+        assert bool((a[n][same] == b[n][same]).all()), n
+        assert not bool(b[n][0, 40:73].isfinite().all()), n
+
+
 def norm_of_infinite(y):
     """The output where channel 3 of o is infinite: the norm factor is 0."""
     other = [c for c in range(y.shape[-1]) if c != 3]
