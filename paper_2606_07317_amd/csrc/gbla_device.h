@@ -80,12 +80,15 @@ __device__ __forceinline__ void load_taps4(const float* conv_w, int H, int h, in
 
 // sum += x with Kahan's compensation: c carries the low-order bits that the
 // rounded sum lost, so a sum of n terms keeps an error of a few ulps instead
-// of growing with n.  Used for the fixed-order sums over chunks, which run to
+// of growing with n; an infinite sum stays infinite.  Used for the fixed-order sums over chunks, which run to
 // thousands of terms on long sequences.
 __device__ __forceinline__ void kahan_add(float& sum, float& c, float x) {
   const float y = x - c;
   const float t = sum + y;
-  c = (t - sum) - y;
+  // Half an ulp of the sum, at most 2^103; that of an infinite sum is inf - inf,
+  // NaN, which fmaxf replaces.  (A compare and select here cost the combine of 32
+  // records 6 us, summing such elements again 2 us of every forward.)
+  c = fmaxf((t - sum) - y, -0x1p110f);
   sum = t;
 }
 

@@ -532,21 +532,6 @@ combine_kernel(Plan P, const int32_t* __restrict__ cu, const float* __restrict__
     }
   }
 
-  // The compensation of an infinite sum is inf - inf: such elements (and those
-  // that are NaN in any case) are summed again without it.  Made safe in each
-  // addition instead, the chain of 32 partials cost the forward of B = 1, n = 32768,
-  // H = 8, d = 64 6 us of 58.
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    if (v[e] == v[e]) continue;
-    v[e] = 0.0f;
-    for (int p = 0; p < count; ++p) {
-      const float* r = recs + p * rf;
-      const float mp = r[kElems];
-      if (M != -INFINITY && mp != -INFINITY) v[e] = fmaf(gexp<T>(mp - M), r[xe[e]], v[e]);
-    }
-  }
-
   const size_t sh = (size_t)s * P.heads + h;
   unsigned char* fr = frags ? frags + sh * P.frag_bytes : nullptr;
   // bf16 fragments of a slice of S alone: the slice holds R whole rows c of S
