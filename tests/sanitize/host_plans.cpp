@@ -152,15 +152,32 @@ void choices() {
   }
   // state units of the fp32 forward and units of the backward, by tokens x heads
   // (2691 x 24: records of 128-token units past the fixed scratch)
-  const struct { int32_t T, H, fwd, bwd; } units[] = {
-      {2691, 1, 64, 64},       {2691, 13, 128, 256},    {2691, 24, 256, 256},    {2691, 25, 256, 512},    {16383, 1, 64, 64},
-      {16384, 1, 64, 128},     {65535, 1, 128, 256},    {65536, 1, 128, 512},    {16579, 5, 256, 512},
-      {16579, 10, 512, 512},   {16579, 20, 1024, 512},  {16579, 34, 2048, 512},  {1 << 20, 8, 2048, 512}};
+  const struct { int32_t T, H, d, fwd, bwd; } units[] = {
+      {2691, 1, 64, 64, 64},      {2691, 13, 64, 128, 128},   {2691, 24, 64, 256, 128},  {2691, 49, 64, 1024, 512},
+      {16383, 1, 64, 64, 64},     {32767, 1, 64, 64, 64},     {32768, 1, 64, 64, 128},   {65535, 1, 64, 128, 128},
+      {65536, 1, 64, 128, 256},   {131072, 1, 64, 256, 512},  {16579, 5, 64, 256, 256},  {16579, 10, 64, 512, 512},
+      {16579, 20, 64, 1024, 512}, {16579, 34, 64, 2048, 512}, {1 << 20, 8, 64, 2048, 512},
+      {65536, 1, 32, 128, 128},   {2691, 98, 32, 1024, 512},  {65535, 4, 32, 512, 256},  {65536, 4, 32, 512, 512},
+      {2691, 25, 128, 512, 512},  {65535, 1, 128, 256, 256},  {16383, 1, 128, 256, 64}};
   for (const auto& u : units) {
-    const gbla_shape s = shape(13, u.H, u.T, 64, 4, u.T, GBLA_F32);
+    const gbla_shape s = shape(13, u.H, u.T, u.d, 4, 2048, GBLA_F32);
     gbla::Plan p, b;
     REQUIRE(gbla::make_plan(&s, true, &p) == GBLA_OK && gbla::backward_plan(p, &b) == GBLA_OK);
+    if (p.chunk != u.fwd || b.chunk != u.bwd) fprintf(stderr, "T %d H %d d %d: units %d, %d\n", u.T, u.H, u.d, p.chunk, b.chunk);
     REQUIRE(p.chunk == u.fwd && b.chunk == u.bwd);
+  }
+  // longer units where one long sequence would have too many records
+  const struct { int32_t T, longest, bwd; } long_units[] = {
+      {10922, 10922, 64},  {10923, 10923, 128},  {30000, 0, 64},      {30000, 30000, 128},
+      {43691, 43691, 256}, {60000, 2048, 64},    {60000, 60000, 256}, {60000, INT32_MAX, 256}};
+  for (const auto& u : long_units) {
+    const gbla_shape s = shape(u.longest == u.T ? 1 : 13, 1, u.T, 32, 4, u.longest);
+    for (int r = u.longest == u.T ? 0 : 1; r < 2; ++r) {
+      gbla::Plan p, b;
+      REQUIRE(gbla::make_plan(&s, r != 0, &p) == GBLA_OK && gbla::backward_plan(p, &b) == GBLA_OK);
+      if (b.chunk != u.bwd) fprintf(stderr, "T %d longest %d: units of %d\n", u.T, u.longest, b.chunk);
+      REQUIRE(b.chunk == u.bwd);
+    }
   }
 }
 

@@ -41,10 +41,11 @@ def _case(d, dtype, width, seed, **kw):
     return small("ragged64_d128", head_dim=d, dtype=dtype, conv_width=width, seed=seed, **kw)
 
 
-def backward_unit(work):
-    """Tokens of the backward's units for `work` tokens x heads."""
+def backward_unit(work, d):
+    """Tokens of the backward's units for `work` tokens x heads: 1024 waves, d / 16
+    to a workgroup."""
     unit = 512
-    while unit > 64 and work < unit * 128:
+    while unit > 64 and work < unit * (1024 // (d // 16)):
         unit //= 2
     return unit
 
@@ -64,11 +65,12 @@ def fp32_state_unit(lengths, heads, d):
     return fine if size <= 16 << 20 else coarse
 
 
-@pytest.mark.parametrize("heads,unit", [(1, 64), (25, 512)])
+@pytest.mark.parametrize("unit", [64, 512])
 @pytest.mark.parametrize("d,dtype,width", DIMS)
-def test_backward_edges(G, dev, d, dtype, width, heads, unit):
+def test_backward_edges(G, dev, d, dtype, width, unit):
     from oracle import gbla_backward
-    assert backward_unit(sum(EDGES) * heads) == unit
+    heads = 1 if unit == 64 else {32: 98, 64: 49, 128: 25}[d]
+    assert backward_unit(sum(EDGES) * heads, d) == unit
     say("backward edges", d, dtype, width, heads)
     inp = inputs.make_inputs(_case(d, dtype, width, 51, heads=heads), lengths=EDGES)
     dy = inputs.make_cotangent(inp)
