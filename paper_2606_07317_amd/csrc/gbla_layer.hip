@@ -141,13 +141,15 @@ __device__ __forceinline__ int seq_end(const LayerPlan& P, const int32_t* cu, in
 // chunks XOR-swizzled by the row); the gate rows' channels are staged beside it.
 // On v_mfma_f32_32x32x16_bf16, gate rows as the first operand, wave w then
 // multiplies the 32 tokens w % (TM / 32), with TM < 128 a part of the slab's
-// channels (the parts are added at the end).  Bound by HBM (one read, one
-// write): TM = 128 has the fewest halo rows and tap loads per token, shorter
-// tiles fill the chip where there are few tokens.  Measured, d_model = 1024,
-// against the two passes: 262144 tokens 224 us (4.8 TB/s; 357 before; TM = 64:
-// 250, TM = 32: 370), 16384 tokens 27 us (31 before; TM = 64: 31); 9662 tokens,
-// d_model = 256: 11 us (17 before).  TM = 128 needs more than the 168
-// registers of three waves a SIMD (spilled: 560 us).
+// channels (the parts are added at the end).  A step's taps come through LDS,
+// loaded a step ahead, one channel a thread.  Bound by HBM (one read, one write):
+// TM = 128 has the fewest halo rows per token, shorter tiles fill the chip where
+// there are few tokens.  Measured, d_model = 1024, against the two passes: 262144
+// tokens 206 us (5.2 TB/s; 357 before), 16384 tokens 19 us (31 before); 9662
+// tokens, d_model = 256: 6.6 us (17 before).  With the taps loaded by every thread
+// that needs them, a load a tap where W < 4, those took 223, 26 and 10 us, and
+// 28176 tokens, d_model = 768, W = 3 77 us (19 now).  TM = 128 needs more than the
+// 168 registers of three waves a SIMD (spilled: 560 us).
 // ---------------------------------------------------------------------------
 template <int TM>
 __global__ void __launch_bounds__(kThreads, TM == 128 ? 2 : 3)
@@ -158,6 +160,7 @@ conv_gate_kernel(LayerPlan P, const uint16_t* __restrict__ x, const float* __res
   __shared__ __attribute__((aligned(16))) unsigned char slab[TM * 256];
   __shared__ __attribute__((aligned(16))) unsigned char wslab[32 * 256];
   __shared__ float sums[kParts > 1 ? 4 * 16 * 64 : 1];
+  __shared__ f32x4_t taps[2][128];  // of a step: channel 8 k + j in slot 16 j + k
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, half = lane >> 5;
   const int chunk = tid & 15, run = tid >> 4;
@@ -182,6 +185,28 @@ conv_gate_kernel(LayerPlan P, const uint16_t* __restrict__ x, const float* __res
       wg[j] = bload(rg, in ? ((uint32_t)(run + 16 * j) * (uint32_t)K + (uint32_t)c0) * 2u : kOutOfRange);
   };
   load(0);
+  // A step's taps, one channel a thread of the first 128 (out-of-range offsets,
+  // read as zero, for the taps before the first and the channels past the last)
+  f32x4_t tw;
+  auto load_taps = [&](int k0) {
+    if (tid >= 128) return;
+    const uint32_t row = (uint32_t)((k0 + tid) * P.W) * 4u;
+    if (P.W == 4) {
+      tw = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rw, row, 0, 0));
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int ti = t - (4 - P.W);
+        tw[t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, ti >= 0 ? row + 4u * ti : kOutOfRange, 0, 0));
+      }
+    }
+  };
+  auto put_taps = [&](int buf) {
+    if (tid < 128) taps[buf][16 * (tid & 7) + (tid >> 3)] = tw;
+  };
+  load_taps(0);
+  put_taps(0);
+  load_taps(128);
   // rows of each token's window inside its sequence: min(3, tokens before it)
   int back[RUN];
   bool whole = true;
@@ -200,6 +225,7 @@ conv_gate_kernel(LayerPlan P, const uint16_t* __restrict__ x, const float* __res
     }
   }
   const bool all_whole = __all(whole);
+  __syncthreads();  // the first taps
 
   f32x16_t acc = {};
   const int wtile = wave % kTiles, wpart = wave / kTiles;
@@ -208,24 +234,9 @@ conv_gate_kernel(LayerPlan P, const uint16_t* __restrict__ x, const float* __res
   const int nk = (K + 127) / 128;
   for (int s = 0; s < nk; ++s) {
     const int c0 = 128 * s + 8 * chunk;
-    // taps: one 16-byte load per channel at W = 4, else one load per tap (an
-    // out-of-range offset, read as zero, for the taps before the first)
-    float w[8][4];
+    f32x4_t w[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t row = (uint32_t)((c0 + j) * P.W) * 4u;
-      if (P.W == 4) {
-        const u32x4_t t4 = __builtin_amdgcn_raw_buffer_load_b128(rw, row, 0, 0);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) w[j][t] = __uint_as_float(t4[t]);
-      } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int ti = t - (4 - P.W);
-          w[j][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, ti >= 0 ? row + 4u * ti : kOutOfRange, 0, 0));
-        }
-      }
-    }
+    for (int j = 0; j < 8; ++j) w[j] = taps[s & 1][16 * j + chunk];
     u32x4_t o[RUN];
     auto conv = [&](auto checked) {
 #pragma unroll
@@ -260,6 +271,8 @@ conv_gate_kernel(LayerPlan P, const uint16_t* __restrict__ x, const float* __res
       const int row = run + 16 * j;
       *reinterpret_cast<u32x4_t*>(&wslab[row * 256 + ((chunk ^ (row & 15)) << 4)]) = wg[j];
     }
+    put_taps((s + 1) & 1);  // last read in step s - 1
+    load_taps(128 * (s + 2));
     load(128 * (s + 1));  // past the channels: zeros, unused
     __syncthreads();
 #pragma unroll
@@ -894,8 +907,9 @@ gbla_status launch_project(const LayerPlan& p, const void* x, const float* conv_
   if (p.tokens == 0) return GBLA_OK;
   const int64_t tiles = (int64_t)((4 * p.heads * p.d + kBN - 1) / kBN) * ((p.tokens + kBM - 1) / kBM);
   if (tiles > 2147483647LL) return GBLA_ERR_UNSUPPORTED;  // the grid's x extent; nothing enqueued
-  // the largest token tile that still gives the chip two workgroups per CU (at
-  // one per CU, 16384 tokens, TM = 64 takes 31 us and TM = 32 27)
+  // the largest token tile that still gives the chip two workgroups per CU (whole
+  // layer, d_model = 1024, H = 16, TM = 32 / 64 / 128: 14000 tokens 198 / 204 / 213
+  // us, 45000 620 / 617 / 623, 60000 852 / 850 / 841)
   const int tm = p.tokens >= 128 * 512 ? 128 : p.tokens >= 64 * 512 ? 64 : 32;
   auto* const conv = tm == 128 ? conv_gate_kernel<128> : tm == 64 ? conv_gate_kernel<64> : conv_gate_kernel<32>;
   hipLaunchKernelGGL(conv, dim3((unsigned)((p.tokens + (int64_t)tm - 1) / tm)), dim3(kThreads), 0, st, p,

@@ -306,6 +306,8 @@ LAYER_CASES = {
     "tile64": dict(lens=[1, 32767, 3, 0, 60, 129, 2, 5], d_model=192, heads=2, head_dim=32, conv_width=3),
     "tile64_full_width": dict(lens=[32764, 4, 1], d_model=256, heads=1, head_dim=64, conv_width=4),
     "gates40": dict(lens=[33, 95, 7], d_model=64, heads=40, head_dim=32, conv_width=4),
+    # taps of four steps through two buffers, one tap each
+    "one_tap": dict(lens=[70, 33, 1], d_model=448, heads=3, head_dim=32, conv_width=1),
     # projections on 128 x 128 tiles: one full tile and one feature tile, one K
     # step; a last tile of one token; and, past them, deferred stores over 32 K
     # steps (17 x 16 tiles of 256)
