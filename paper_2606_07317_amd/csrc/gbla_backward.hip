@@ -403,24 +403,8 @@ bwd_dscombine_kernel(Plan P, const int32_t* __restrict__ cu, const float* __rest
   if (x >= kElems) return;
   const float* recs = dsp + ((size_t)h * P.units + first) * P.rec_floats + x;
   const size_t rf = P.rec_floats;
-  // in unit order (compensated), a group of records added while the next is
-  // loaded (235 records of d = 32 10 us, 14 with eight at a time)
-  constexpr int G = 16;
-  float acc = 0.0f, cmp = 0.0f, next[G];
-  auto load = [&](int p) {
-#pragma unroll
-    for (int i = 0; i < G; ++i) next[i] = recs[(size_t)min(p + i, count - 1) * rf];
-  };
-  load(0);
-  for (int p = 0; p < count; p += G) {
-    float v[G];
-#pragma unroll
-    for (int i = 0; i < G; ++i) v[i] = next[i];
-    if (p + G < count) load(p + G);
-#pragma unroll
-    for (int i = 0; i < G; ++i)
-      if (p + i < count) kahan_add(acc, cmp, v[i]);
-  }
+  float acc = 0.0f, cmp = 0.0f;
+  sum_records(count, [&](int p) { return recs[(size_t)p * rf]; }, [](int, float x) { return x; }, acc, cmp);
   dS[(size_t)sh_idx * kElems + x] = acc;
 }
 

@@ -523,30 +523,8 @@ combine_kernel(Plan P, const int32_t* __restrict__ cu, const float* __restrict__
     }
     __syncthreads();
     if constexpr (E == 1) {
-      // a group of partials added while the next is loaded (469 records of d = 32
-      // 18 us, 22 with the unrolled loop below; 32 records the same)
-      constexpr int G = 16;
       const float* r = recs + p0 * rf + xe[0];
-      float next[G];
-      auto load = [&](int p) {
-#pragma unroll
-        for (int i = 0; i < G; ++i) next[i] = r[min(p + i, n - 1) * rf];
-      };
-      load(0);
-      int p = 0;
-      for (; p + G <= n; p += G) {
-        float x[G];
-#pragma unroll
-        for (int i = 0; i < G; ++i) x[i] = wst[p + i] * next[i];
-        load(p + G);
-#pragma unroll
-        for (int i = 0; i < G; ++i) kahan_add(v[0], cmp[0], x[i]);
-      }
-#pragma unroll
-      for (int i = 0; i < G; ++i) {
-        if (p + i >= n) break;
-        kahan_add(v[0], cmp[0], wst[p + i] * next[i]);
-      }
+      sum_records(n, [&](int p) { return r[p * rf]; }, [&](int p, float x) { return wst[p] * x; }, v[0], cmp[0]);
     } else {
       // unrolled so that many partials' loads are in flight at once
 #pragma unroll 16
