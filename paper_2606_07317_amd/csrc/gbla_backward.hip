@@ -701,12 +701,13 @@ bwd_state_split_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ 
   float z = 0.0f;
   int par = 0;
   float sign = 1.0f;
-  for (int b0 = t0; b0 < t1; b0 += 32, par ^= 1, sign = -sign) {
+  auto tile = [&](auto tail, int b0) {
     float kt[8], vt[8];
     nv.conv(wv, vt);
     nk.conv(wk, kt);
     nk.load(rk, b0 + 32 + 8 * g, c);  // past the slice they read 0; unused
     nv.load(rv, b0 + 32 + 8 * g, c);
+    zero_past(tail, t1 - b0 - 8 * g, vt);
     u32x4_t A[3];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -719,6 +720,7 @@ bwd_state_split_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ 
 #pragma unroll
     for (int x = 0; x < 3; ++x)
       *reinterpret_cast<u32x4_t*>(pv[par] + x * C::kPlane + plane_unit(c, g)) = A[x];
+    zero_past(tail, t1 - b0 - 8 * g, kt);  // phi of a zero: the weights do the rest
     const f32x4_t wa = *reinterpret_cast<const f32x4_t*>(&wts[b0 - t0 + 8 * g]);
     const f32x4_t wb = *reinterpret_cast<const f32x4_t*>(&wts[b0 - t0 + 8 * g + 4]);
     float zt = 0.0f;
@@ -745,7 +747,12 @@ bwd_state_split_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ 
 #pragma unroll
       for (int i = 0; i < 4; ++i) acc[b][i] = fmaf(sign, y[i], acc[b][i]);
     }
-  }
+    par ^= 1;
+    sign = -sign;
+  };
+  int b0 = t0;
+  for (; b0 + 32 <= t1; b0 += 32) tile(std::false_type{}, b0);
+  if (b0 < t1) tile(std::true_type{}, b0);
   float* rec = partials + ((size_t)h * P.units + unit) * P.rec_floats;
 #pragma unroll
   for (int b = 0; b < NW; ++b)
@@ -906,21 +913,27 @@ bwd_query_split_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ 
   };
 
   float sign = 1.0f;
-  for (; b0 >= t0 && t1 > t0; b0 -= 32, sign = -sign) {
+  auto tile = [&](auto tail) {
     const Column<T, D> xq = nq;
     nq.load(rq, b0 - 32 + 8 * g, c);  // the tile before (before the slice: reads 0, unused)
     float qh[8], o[8], v[8];
     xq.conv(w4, qh);
+    // Tokens past the sequence take no part, whatever their windows hold of it:
+    // zeros for Qh, o and dQh, and 1 / den and rs by the token's lanes.
+    const int live = t1 - b0 - 8 * g;
+    const bool past = decltype(tail)::value && b0 + tok32 >= t1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) qh[j] = phi_fast(qh[j]);
+    zero_past(tail, live, qh);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      qh[j] = phi_fast(qh[j]);
       v[j] = qh[j] * z;
     }
     put_part(0, v);
     put_planes<D>(pq, c, g, qh);
     __syncthreads();
     // num = S^T Qh, den = z . Qh
-    const float inv = 1.0f / total(0);
+    const float inv = past ? 0.0f : 1.0f / total(0);
     if (lane < 32) dist[wave][0][tok32] = inv;
     contract_planes<D>(pq, f1, lane, o);
     float dn[8], dd = 0.0f;  // dd: dden of token tok32
@@ -939,6 +952,7 @@ bwd_query_split_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ 
     get8(0, v);
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[j] *= v[j];
+    zero_past(tail, live, o);
     const uint32_t off = (uint32_t)((b0 + 8 * g) * D + c) * 4u;
     if constexpr (kNorm) {
 #pragma unroll
@@ -951,7 +965,7 @@ bwd_query_split_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ 
       // |o|^2 in the lower lanes, doh . o in the upper, then both in both
       const float x = total(lane < 32 ? 1 : 2), y = __shfl_xor(x, 32);
       const float s2 = lane < 32 ? x : y, s1 = lane < 32 ? y : x;
-      const float rs = rsqrt_nr(s2 * (1.0f / D) + P.eps);
+      const float rs = past ? 0.0f : rsqrt_nr(s2 * (1.0f / D) + P.eps);
       // do . o = rs s1 (1 - rs^2 |o|^2 / d) = eps rs^3 s1 exactly (rs^-2 = |o|^2/d + eps):
       // the RMSNorm leaves almost nothing along o, and summing do . o would
       // return mostly the rounding of its terms.
@@ -1014,7 +1028,8 @@ bwd_query_split_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ 
     // phi'(u) = 1 for u > 0 and e^u = phi(u) <= 1 otherwise: min(phi(u), 1)
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[j] = fmaf(z, v[j], o[j]) * fminf(qh[j], 1.0f);
-    conv_back8<T, D>(o, xq, w4, prev, lane, rdq, off, dw);
+    zero_past(tail, live, o);
+    conv_back8<T, D>(o, xq, w4, prev, lane, tail, live, rdq, off, dw);
     u32x4_t A[3];
     row_operand<D>(pq, c, g, A);
     const uint32_t flip = sign < 0.0f ? 0x80008000u : 0u;
@@ -1030,7 +1045,11 @@ bwd_query_split_kernel(Plan P, const T* __restrict__ qin, const T* __restrict__ 
 #pragma unroll
       for (int i = 0; i < 4; ++i) acc[b][i] = fmaf(sign, y[i], acc[b][i]);
     }
-  }
+    b0 -= 32;
+    sign = -sign;
+  };
+  if (b0 + 32 > t1 && t1 > t0) tile(std::true_type{});
+  while (b0 >= t0 && t1 > t0) tile(std::false_type{});
 
   const size_t ui = (size_t)h * P.units + unit;
   float* rec = dsp + ui * P.rec_floats;
@@ -1127,7 +1146,7 @@ bwd_key_split_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vi
   float pvk[3] = {0.0f, 0.0f, 0.0f}, pvv[3] = {0.0f, 0.0f, 0.0f};
   int turn = 0;  // the wave that writes the tile's da
 
-  for (; b0 >= t0 && t1 > t0; b0 -= 32) {
+  auto tile = [&](auto tail) {
     const Column<T, D> xk = nk, xv = nv;
     nk.load(rk, b0 - 32 + 8 * g, c);  // the tile before (before the slice: reads 0, unused)
     nv.load(rv, b0 - 32 + 8 * g, c);
@@ -1160,6 +1179,10 @@ bwd_key_split_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vi
       t[j] = gj[j] * t[j] * fminf(p[j], 1.0f);  // phi'(u) = min(phi(u), 1)
       v[j] *= gj[j];
     }
+    // tokens past the sequence take no part, whatever their windows hold of it
+    const int live = t1 - b0 - 8 * g;
+    zero_past(tail, live, t);
+    zero_past(tail, live, v);
     __syncthreads();  // the planes are read, the sums of da whole
     if (wave == turn && lane < 32) {
       float x = part[0][lane];
@@ -1169,9 +1192,12 @@ bwd_key_split_kernel(Plan P, const T* __restrict__ kin, const T* __restrict__ vi
                                             (uint32_t)(b0 + lane) * 4u, 0, 0);
     }
     turn = turn + 1 == NW ? 0 : turn + 1;
-    conv_back8<T, D>(t, xk, wk, pvk, lane, rdk, off, dwk);
-    conv_back8<T, D>(v, xv, wv, pvv, lane, rdv, off, dwv);
-  }
+    conv_back8<T, D>(t, xk, wk, pvk, lane, tail, live, rdk, off, dwk);
+    conv_back8<T, D>(v, xv, wv, pvv, lane, tail, live, rdv, off, dwv);
+    b0 -= 32;
+  };
+  if (b0 + 32 > t1 && t1 > t0) tile(std::true_type{});
+  while (b0 >= t0 && t1 > t0) tile(std::false_type{});
 
   const size_t ui = (size_t)h * P.units + unit;
 #pragma unroll

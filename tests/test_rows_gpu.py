@@ -115,6 +115,29 @@ def test_backward_infinite_inputs_stay_in_their_sequence(G, dev):
         assert not bool(b[n][0, 40:73].isfinite().all()), n
 
 
+@pytest.mark.parametrize("name", ["q", "k"])
+@pytest.mark.parametrize("d,W", [(32, 4), (64, 3), (128, 4)])
+def test_backward_infinite_last_token(G, dev, d, W, name):
+    """phi of -inf is 0, so a -inf in a sequence's last token leaves finite gradients
+    (but the tap's that multiplies it): the tile's tokens past the sequence, whose
+    windows hold it too, take no part."""
+    from oracle import gbla_backward
+    say("backward, infinite last token", d, W, name)
+    lengths = [40, 33, 70, 128, 5]
+    inp = inputs.make_inputs(_case(d, inputs.F32, W, 63, heads=2), lengths=lengths)
+    getattr(inp, name)[0, np.cumsum(lengths) - 1, 3] = -np.inf
+    dy = inputs.make_cotangent(inp)
+    got = run_backward(G, inp, dy, dev)
+    with np.errstate(invalid="ignore"):
+        ref = gbla_backward.backward_inputs(inp, dy)
+    for n in NAMES:
+        nan = np.zeros(ref[n].shape, bool)
+        if n == "dconv_w":
+            nan["qkv".index(name), 0, 3, W - 1] = True  # 0 * inf
+        assert (np.isnan(got[n]) == nan).all() and (np.isnan(ref[n]) == nan).all(), n
+        close_scaled(np.where(nan, 0, got[n]), np.where(nan, 0, ref[n]), TOL[inputs.F32], n)
+
+
 def norm_of_infinite(y):
     """The output where channel 3 of o is infinite: the norm factor is 0."""
     other = [c for c in range(y.shape[-1]) if c != 3]
