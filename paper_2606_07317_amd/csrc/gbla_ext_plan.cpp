@@ -9,31 +9,35 @@ namespace {
 
 constexpr int kMinUnit = 64;  // the backward's shortest unit, two tiles
 
+// Units of at most 512 tokens: long enough to amortise each workgroup's
+// set-up (the constant operands' columns), short enough for two workgroups
+// per CU at n = 32768, H = 8.  A workgroup has d / 16 waves; batches that would
+// not give every SIMD one take shorter units, down to kMinUnit tokens, unless
+// the longest sequence then has so many records that adding them up (0.11 to
+// 0.27 us a record, by d) costs more than the shorter walk saves (0.15 to 0.32
+// us a token): halving u pays below n = u^2 / 1.5.  Whole backward in us, units
+// of 64 / 128 / 256 / 512:
+//   d = 32: B = 4, n = 2000, H = 8 46 / 51 / 64 / 103; n = 30000, H = 4 109 / 80
+//   / 89 / 111; n = 60000, H = 4 188 / 135 / 106 / 140; H = 8 281 / 211 / 182 /
+//   167; one head, n = 8000 45 / 50 / 60 / 98; 30000 86 / 67 / 74 / 108; 120000
+//   248 / 150 / 124 / 127.
+//   d = 64: B = 4, n = 2000, H = 8 77 / 64 / 76 / 123; n = 16000, H = 8 145 / 117
+//   / 106 / 123; n = 30000 276 / 213 / 186 / 176; one head, n = 60000 162 / 109 /
+//   98 / 134.
+//   d = 128: n = 2000, H = 8 66 / 79 / 119 / 200; n = 8000 209 / 158 / 129 / 203;
+//   n = 16000 404 / 299 / 249 / 229; one head, n = 60000 271 / 187 / 148 / 215.
+int32_t unit_tokens(const Plan& p, int64_t longest) {
+  const int64_t work = p.tokens * p.heads, least = 1024 / (p.d / 16);
+  int64_t unit = 512;
+  while (unit > kMinUnit && work < unit * least && 3 * longest < 2 * unit * unit) unit /= 2;
+  return (int32_t)unit;
+}
+
 }  // namespace
 
 gbla_status backward_plan(const Plan& p, Plan* out) {
-  // Units of at most 512 tokens: long enough to amortise each workgroup's
-  // set-up (the constant operands' columns), short enough for two workgroups
-  // per CU at n = 32768, H = 8.  A workgroup has d / 16 waves; batches that would
-  // not give every SIMD one take shorter units, down to kMinUnit tokens, unless
-  // the longest sequence then has so many records that adding them up (0.11 to
-  // 0.27 us a record, by d) costs more than the shorter walk saves (0.15 to 0.32
-  // us a token): halving u pays below n = u^2 / 1.5.  Whole backward in us, units
-  // of 64 / 128 / 256 / 512:
-  //   d = 32: B = 4, n = 2000, H = 8 46 / 51 / 64 / 103; n = 30000, H = 4 109 / 80
-  //   / 89 / 111; n = 60000, H = 4 188 / 135 / 106 / 140; H = 8 281 / 211 / 182 /
-  //   167; one head, n = 8000 45 / 50 / 60 / 98; 30000 86 / 67 / 74 / 108; 120000
-  //   248 / 150 / 124 / 127.
-  //   d = 64: B = 4, n = 2000, H = 8 77 / 64 / 76 / 123; n = 16000, H = 8 145 / 117
-  //   / 106 / 123; n = 30000 276 / 213 / 186 / 176; one head, n = 60000 162 / 109 /
-  //   98 / 134.
-  //   d = 128: n = 2000, H = 8 66 / 79 / 119 / 200; n = 8000 209 / 158 / 129 / 203;
-  //   n = 16000 404 / 299 / 249 / 229; one head, n = 60000 271 / 187 / 148 / 215.
   Plan b = p;
-  const int64_t work = p.tokens * p.heads, least = 1024 / (p.d / 16);
-  const int64_t longest = p.ragged && p.max_seqlen < p.rows ? p.max_seqlen : p.rows;
-  b.chunk = 512;
-  while (b.chunk > kMinUnit && work < b.chunk * least && 3 * longest < 2 * (int64_t)b.chunk * b.chunk) b.chunk /= 2;
+  b.chunk = unit_tokens(p, p.ragged && p.max_seqlen < p.rows ? p.max_seqlen : p.rows);
   int64_t units;
   if (p.ragged) {
     units = b.tokens / b.chunk + b.nseq;
@@ -104,7 +108,10 @@ gbla_status make_layer_plan(const gbla_layer_shape* s, bool ragged, LayerPlan* p
 BwdLayout make_bwd_layout(const Plan& p) {
   BwdLayout L{};
   const size_t pairs = (size_t)p.nseq * p.heads, d = p.d, f = sizeof(float);
-  const size_t unit_recs = (size_t)p.units * p.heads;
+  // Ragged: the records of the shortest units that any max_seqlen gives, so that a
+  // workspace serves batches of one T whatever their longest sequence.
+  const size_t units = p.ragged ? (size_t)(p.tokens / unit_tokens(p, 0) + p.nseq) : (size_t)p.units;
+  const size_t unit_recs = units * p.heads;
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t at = off;

@@ -1,5 +1,6 @@
 """The split rules of the plans on the CPU, through the C ABI: a finer split
-never takes a shape away from the entry point with the fixed scratch."""
+never takes a shape away from the entry point with the fixed scratch, nor from a
+workspace that is kept while max_seqlen changes."""
 import ctypes
 
 import pytest
@@ -46,3 +47,30 @@ def test_fp32_noalloc_still_takes_what_the_coarse_split_fits(lib, d, ragged):
                 assert lib.gbla_forward_noalloc(ctypes.byref(s), *args) != 4, (batch, heads, n)
                 taken += 1
     assert taken > 50
+
+
+def _backward_need(lib, shape):
+    """Smallest workspace that the ragged gbla_backward call does not refuse."""
+    lo, hi = 0, 1 << 33
+    while lo < hi:
+        mid = (lo + hi) // 2
+        args = [ALIGNED] * 7 + [ALIGNED] * 3 + [mid] + [ALIGNED] * 7 + [None]
+        if lib.gbla_backward(ctypes.byref(shape), *args) == 4:
+            lo = mid + 1
+        else:
+            hi = mid
+    return lo
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_backward_workspace_serves_every_max_seqlen(lib, d):
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch on the fake pointers")
+    for heads, batch, T in ((1, 1, 60000), (4, 3, 2000), (8, 40, 30000), (3, 7, 255)):
+        need = set()
+        for longest in (0, 1, 100, 700, 5000, 20000, T, 1 << 30):
+            s = gbla.Shape(batch, heads, T, d, 4, longest, gbla.GBLA_BF16, 1e-6, 0)
+            need.add(_backward_need(lib, s))
+            assert gbla.backward_workspace_bytes(s) >= max(need)
+        assert len(need) == 1, (heads, batch, T, need)
