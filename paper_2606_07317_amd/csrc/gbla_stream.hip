@@ -493,9 +493,15 @@ readout_stream_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16_t* 
   seq_geometry(P, cu, s, h, &len, &base_row);
   const int64_t tt0 = (int64_t)tile * P.rtile;
   const int64_t tt1 = min(len, tt0 + (int64_t)P.rtile);
-  // a quarter of the tile's tokens a wave, in whole groups (short sequences
-  // would otherwise leave three waves idle)
-  const int per_wave = ((int)(tt1 - tt0) + 4 * C::kGroup - 1) / (4 * C::kGroup) * C::kGroup;
+  // A quarter of the tile's tokens a wave, in whole groups, for sequences of one
+  // tile (three waves would otherwise idle) and at d = 128 for every last tile (64
+  // packed sequences, T = 231,233, H = 8 849 us, 860 with quarters of a whole tile;
+  // 200, T = 108,130 501 / 508).  Below, a last tile of 128 to 240 tokens so
+  // divided is slower (B = 8, n = 9456, H = 8, d = 64 135.2 against 133.4; ragged
+  // batches the same either way to 0.5%).
+  const int per_wave = D < 128 && tile > 0
+                           ? P.rtile >> 2
+                           : ((int)(tt1 - tt0) + 4 * C::kGroup - 1) / (4 * C::kGroup) * C::kGroup;
   const int r0 = (int)(tt0 + (int64_t)wave * per_wave);  // slice-relative
   const int r1 = (int)min(tt1, (int64_t)r0 + per_wave);
   const int ngroups = (r1 - r0 + C::kGroup - 1) / C::kGroup;  // < 1: the wave has no rows
