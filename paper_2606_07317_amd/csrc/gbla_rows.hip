@@ -491,8 +491,11 @@ short_forward_kernel(Plan P, const float* __restrict__ qin, const float* __restr
 // eight consecutive tokens 8 g + j, products on v_mfma_f32_16x16x32_bf16 (which,
 // unlike the fp32 one, runs beside the vector unit).  As in the other bf16
 // kernels the gated keys, phi(qt) and the readout's S are rounded to bf16 and
-// the values enter without rounding error (here as bf16 + bf16 residue); z stays
-// in fp32.  S is normalised by the sum of the gates before it is rounded, as the
+// the values enter without rounding error (here as bf16 + bf16 residue).  Without
+// the norm the denominators take the rounded z and phi(qt), as the readout kernel's
+// products do: the roundings then cancel in part in o (sequences of 1 to 10 tokens
+// 5.2e-4 from 64 bits, 5.7e-4 with both in fp32); the norm takes the
+// denominators out, and z stays in fp32.  S is normalised by the sum of the gates before it is rounded, as the
 // combine does, so that both forms round the same values: rounded as summed, the
 // output was 4.2e-4 (2-norm) from the three launches' on these sequences, as far
 // as either is from the exact result.  256 packed sequences, T = 39,470 (5 to 1,019 tokens), H = 8, d = 64:
@@ -649,7 +652,10 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
   __syncthreads();
   const float l = (red4[0] + red4[1]) + (red4[2] + red4[3]);
   const float inv_l = l > 0.0f ? 1.0f / l : 0.0f;
-  if (tid < D) zs[tid] = ((red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid])) * inv_l;
+  if (tid < D) {
+    const float z = ((red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid])) * inv_l;
+    zs[tid] = kNorm ? z : bf16_lo(pack_bf16x2(z, 0.0f));
+  }
   // B operands of S: vector (nb * KS + ks) * 64 + lane holds S[32 ks + 8 g + i]
   // [slot_chan(nb, n)], i < 8
   constexpr int kPer = (kOps + kThreads - 1) / kThreads;
@@ -687,6 +693,7 @@ short_forward_bf16_kernel(Plan P, const uint16_t* __restrict__ qin, const uint16
 #pragma unroll
         for (int t = 1; t < 4; ++t) a = fmaf(t4[t], xq[j + t].at(b), a);
         x[b][j] = phi<false>(a);
+        if constexpr (!kNorm) x[b][j] = bf16_lo(pack_bf16x2(x[b][j], 0.0f));
         den[j] = fmaf(x[b][j], z, den[j]);
       }
     }
