@@ -82,8 +82,8 @@ __device__ __forceinline__ void load_taps4(const float* conv_w, int H, int h, in
 
 // sum += x with Kahan's compensation: c carries the low-order bits that the
 // rounded sum lost, so a sum of n terms keeps an error of a few ulps instead
-// of growing with n; an infinite sum stays infinite.  Used for the fixed-order sums over chunks, which run to
-// thousands of terms on long sequences.
+// of growing with n; an infinite sum stays infinite.  Used for the fixed-order
+// sums over chunks, which run to thousands of terms on long sequences.
 __device__ __forceinline__ void kahan_add(float& sum, float& c, float x) {
   const float y = x - c;
   const float t = sum + y;

@@ -436,8 +436,9 @@ __device__ __forceinline__ void frag_put(void* frag_sh, int mb, int kb, int lane
 // weights w_p = exp(m_p - M) of its (sequence, head) in LDS and forms
 // Z = sum_p w_p l_p; each thread then sums element x of every partial in the
 // order p = 0, 1, ... (compensated, so that thousands of chunks keep the sum
-// to a few ulps), scales by 1/Z and writes S, z and the readout fragments.  Every reduction order is fixed by the shape alone (not by E or
-// the grid), so every call gives the same bits.
+// to a few ulps), scales by 1/Z and writes S, z and the readout fragments.  Every
+// reduction order is fixed by the shape alone (not by E or the grid), so every
+// call gives the same bits.
 constexpr int kCombineStage = 1024;  // chunk weights staged in LDS per round
 
 template <typename T, int D, int E>
@@ -877,7 +878,8 @@ struct ConvRun {
 // loads in flight and whole fragment slots to write).  fp32 (the backward's
 // 512-token units, so more partials a pair): always one; 128 pairs of d = 128,
 // 57,511 tokens 31 us against 48 with four; 512 pairs, 177,929 tokens 123 us
-// against 244 with sixteen.  The result does not depend on the choice.
+// against 244 with sixteen (94 with sum_records' loads a group ahead).  The result
+// does not depend on the choice.
 template <typename T, int D>
 gbla_status run_combine(const Plan& p, const int32_t* cu, const float* partials, float* S,
                         float* z, unsigned char* frags, float* mz, hipStream_t st) {

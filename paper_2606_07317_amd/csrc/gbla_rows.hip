@@ -498,11 +498,11 @@ short_forward_kernel(Plan P, const float* __restrict__ qin, const float* __restr
 // denominators out, and z stays in fp32.  S is normalised by the sum of the gates before it is rounded, as the
 // combine does, so that both forms round the same values: rounded as summed, the
 // output was 4.2e-4 (2-norm) from the three launches' on these sequences, as far
-// as either is from the exact result.  256 packed sequences, T = 39,470 (5 to 1,019 tokens), H = 8, d = 64:
-// 75 us against 164 us for the three launches, whose partial records and
-// operands (70 MB) and one workgroup per CU this avoids; 243 MB of inputs and
-// outputs are 48 us of plain copy.  117 us in sequence order (long_first), 216
-// us with fp32 products.
+// as either is from the exact result.  256 packed sequences, T = 39,470 (5 to
+// 1,019 tokens), H = 8, d = 64: 72 us against 164 us for the three launches,
+// whose partial records and operands (70 MB) and one workgroup per CU this
+// avoids; 243 MB of inputs and outputs are 48 us of plain copy.  117 us in
+// sequence order (long_first), 216 us with fp32 products.
 // ---------------------------------------------------------------------------
 template <int D, bool kNorm>
 __global__ void __launch_bounds__(kThreads, 3)
@@ -802,11 +802,11 @@ gbla_status launch_short_forward(const Plan& p, const void* q, const KeyInputs& 
     const TT *qq = (const TT*)q, *kk = (const TT*)in.k, *vv = (const TT*)in.v, *aa = (const TT*)in.a, \
              *rr = (const TT*)r;                                                                     \
     if (ev.any())                                                                                    \
-      hipExtLaunchKernelGGL(KERNEL, grid, dim3(kThreads), 0, st,       \
-                            ev.start, ev.stop, 0, p, qq, kk, vv, aa, rr, conv_w, gamma, cu, out);    \
+      hipExtLaunchKernelGGL(KERNEL, grid, dim3(kThreads), 0, st, ev.start, ev.stop, 0, p, qq, kk,    \
+                            vv, aa, rr, conv_w, gamma, cu, out);                                     \
     else                                                                                             \
-      hipLaunchKernelGGL(KERNEL, grid, dim3(kThreads), 0, st, p, qq,   \
-                         kk, vv, aa, rr, conv_w, gamma, cu, out);                                    \
+      hipLaunchKernelGGL(KERNEL, grid, dim3(kThreads), 0, st, p, qq, kk, vv, aa, rr, conv_w, gamma,  \
+                         cu, out);                                                                   \
   } while (0)
   const bool norm = gamma != nullptr;  // NULL gamma: the no-gated-norm switch
   if (p.dtype == GBLA_BF16) {
