@@ -211,8 +211,9 @@ gbla_status gbla_readout_timed(const gbla_shape* shape, const void* q, const voi
 
 /*
  * Bytes of device scratch that gbla_backward needs for this shape (the
- * larger of the accepted dense and ragged readings; 0 if neither is).  About 12 * tokens * H * d bytes (fp32
- * gradients of the convolved q, k, v) plus per-chunk partials.
+ * larger of the accepted dense and ragged readings; 0 if neither is), the same
+ * for every max_seqlen.  About 12 * tokens * H * d bytes (fp32 gradients of the
+ * convolved q, k, v) plus per-chunk partials.
  */
 size_t gbla_backward_workspace_bytes(const gbla_shape* shape);
 
