@@ -34,6 +34,30 @@ void halve_rtile(Plan* q, int32_t least) {
     q->rtile /= 2;
 }
 
+// Readout tile of the bf16 kernel at d = 128, where one workgroup runs on a CU:
+// of the tiles that halve_rtile would go through, the one whose rounds of 256
+// workgroups take least.  A round is its longest tile and about 105 tokens of
+// set-up (4 us; 0.038 us a token).  Whole forward in us, tiles of 512 / 256 / 128,
+// H = 8: B = 9, n = 971 57 / 61 / -; B = 1, n = 16000 67 / 74 / -; B = 1, n = 5000 48
+// / 38 / 42; B = 4, n = 971 48 / 39 / 34; B = 24, n = 300 62 / 71 / 69; packed, 24
+// sequences, T = 24,659, H = 4 103 / 88 / -; 30, T = 15,617, H = 3 71 / 74 / 66.
+void rtile_by_rounds(Plan* q) {
+  int64_t best = -1;
+  int32_t tile = q->rtile;
+  for (int32_t t = q->rtile; t >= 128; t /= 2) {
+    if (q->tokens / t + q->nseq > kMaxGridX) break;  // the grid would refuse the batch
+    const int64_t units = q->ragged ? q->tokens / t + q->nseq : (int64_t)q->nseq * (((int64_t)q->rows + t - 1) / t);
+    const int64_t longest = !q->ragged && q->rows < t ? q->rows : t;
+    const int64_t cost = (units * q->heads + 255) / 256 * (longest + 105);
+    if (best < 0 || cost < best) {
+      best = cost;
+      tile = t;
+    }
+    if (q->tokens * q->heads >= (int64_t)t * 256) break;
+  }
+  q->rtile = tile;
+}
+
 // Split of the fp32 kernels, whose workgroups are smaller (four waves, two
 // workgroups per CU up to d = 64).  Small batches are cut finer: state units
 // of down to 64 tokens, readout tiles of down to 64 (whole forward, chunk 256 /
@@ -141,8 +165,11 @@ gbla_status make_plan(const gbla_shape* s, bool ragged, Plan* p) {
   // bf16 readout tiles: 512 tokens, of a small batch down to 128 (four waves of
   // 32), for a workgroup per CU where the batch has the tokens for it (9662
   // tokens, H = 4, d = 64: readout 10 us, 15 with 512; twice as many workgroups
-  // 10, and B = 1, n = 32768, H = 8 then takes 29 us against 28)
+  // 10, and B = 1, n = 32768, H = 8 then takes 29 us against 28).  Up to d = 64
+  // several workgroups run on a CU and a few past 256 cost nothing (whole forward,
+  // n = 16000, H = 8, d = 64 35.7 us with 256, 35.8 with 512).
   if (q.dtype == GBLA_F32) fp32_split(&q);
+  else if (q.d == 128) rtile_by_rounds(&q);
   else halve_rtile(&q, 128);
 
   // Upper bounds valid for both layouts: sum_s max(1, ceil(len_s / u)) <=

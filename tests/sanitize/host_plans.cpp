@@ -166,6 +166,20 @@ void choices() {
     if (p.chunk != u.fwd || b.chunk != u.bwd) fprintf(stderr, "T %d H %d d %d: units %d, %d\n", u.T, u.H, u.d, p.chunk, b.chunk);
     REQUIRE(p.chunk == u.fwd && b.chunk == u.bwd);
   }
+  // bf16 readout tiles at d = 128: no second round of 256 workgroups for shorter
+  // tiles, where a batch of few tokens does not need one (shape: B, n, H; B packed
+  // sequences of B * n tokens where n is negative)
+  const struct { int32_t B, n, H, tile; } tiles[] = {
+      {9, 971, 8, 512},  {1, 16000, 8, 512}, {1, 5000, 8, 256}, {8, 1000, 8, 256}, {4, 971, 8, 128}, {1, 4000, 8, 128},
+      {24, 300, 8, 512}, {32, 200, 8, 512},  {1, 20000, 1, 128}, {24, -1027, 4, 256}, {30, -520, 3, 128},
+      {1, 32768, 8, 512}};
+  for (const auto& u : tiles) {
+    const gbla_shape s = shape(u.B, u.H, u.n < 0 ? -u.n * u.B : u.n, 128);
+    gbla::Plan p;
+    REQUIRE(gbla::make_plan(&s, u.n < 0, &p) == GBLA_OK);
+    if (p.rtile != u.tile) fprintf(stderr, "B %d n %d H %d: readout tile %d\n", u.B, u.n, u.H, p.rtile);
+    REQUIRE(p.rtile == u.tile);
+  }
   // longer units where one long sequence would have too many records
   const struct { int32_t T, longest, bwd; } long_units[] = {
       {10922, 10922, 64},  {10923, 10923, 128},  {30000, 0, 64},      {30000, 30000, 128},
